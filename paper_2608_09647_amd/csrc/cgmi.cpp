@@ -258,6 +258,7 @@ extern "C" int cg_create(int32_t n, int64_t nnz, const int32_t *row_ptr, const i
     // device copy of the GPU row block, row pointers rebased (Section 3.2)
     hipError_t e = hipSuccess;
     auto chk = [&](hipError_t x) { if (e == hipSuccess) e = x; };
+    h->A.konst_allowed = true;
     {
         const int rc2 = dm_upload(h->A, m, h->h_rp.data() + h->rb, h->h_ci.data(), h->h_val.data(), h->rb);
         if (rc2) return bail(rc2);

@@ -135,6 +135,9 @@ struct DevMatrix {
     uint8_t *d_st_mask = nullptr;
     double *d_st_val = nullptr;
     size_t st_slots = 0;
+    StenGlobal stg{};                 //   global stencil (konst: no slot values are stored)
+    uint8_t *d_st_fast = nullptr;     //   its fast tiles
+    bool konst_allowed = false;       //   the owner's kernels take constant values
     std::vector<DevMatrix> blocks;    // column-blocked layout: one CSR per column block
     ColBlocks *cb = nullptr;          //   and their launch operands
     int32_t block_cols = 0;           //   columns per block
@@ -145,7 +148,7 @@ struct DevMatrix {
                       d_sell_off, d_sell_ci, d_sell_val, d_val32, d_sell_val32,
                       d_sell_idx, d_sell_dict, pad_col_base, cb,
                       d_st_off, d_st_offs, d_st_mask, d_st_val, d_sell_len, d_tile_row,
-                      use_gap ? d_sell_lenx : nullptr, use_gap ? d_sell_gap : nullptr};
+                      use_gap ? d_sell_lenx : nullptr, use_gap ? d_sell_gap : nullptr, stg, d_st_fast};
     }
 };
 

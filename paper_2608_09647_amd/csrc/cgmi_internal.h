@@ -100,8 +100,33 @@ constexpr int32_t kColBlockCols = 1 << 18;
 // of the row's byte st_mask[64t + l] says whether the entry exists.  Slots are
 // in ascending column order, so rows are summed exactly in CSR order.
 // Values slot-major from st_off[t], float64 only.
+// Global stencil (a form of kTileStencil, StenGlobal): where the whole block
+// has at most kSliceMaxWidth distinct offsets, every slice takes all of them
+// as its slots, so slot j's column is the row plus a launch argument and
+// slice t's values start at t * width * 64.
+// A byte per 128-row tile (two slices) marks the fast tiles, which are the
+// rule: all their rows exist, every slot's 128 consecutive columns lie inside
+// the vector, and no row lacks a slot but those of glob_partial(width) (the
+// neighbours along a line, which its end rows lack); such a tile loads a slot
+// for all rows without looking at their masks.  Where moreover every entry at an offset holds the same value bit
+// for bit (constant-coefficient operators), the values are launch arguments
+// too and none are stored.
+// Slots that rows of a fast tile may lack, for the widths that have such
+// tiles: a lower or upper factor (3), 5-point and 7-point operators.
+CGMI_HD constexpr inline uint32_t glob_partial(int width) {
+    return width == 3 ? 0x2u : width == 5 ? 0xAu : width == 7 ? 0x14u : 0u;
+}
 enum { kTileVector = 0, kTileStream = 1, kTileSliced = 2, kTileSlicedDict = 3, kTileColBlocked = 4,
        kTileStencil = 5 };
+
+// Offsets (ascending) of a global stencil (width 0: the block has none) and,
+// with konst, the value of each.
+struct StenGlobal {
+    int32_t width;
+    int32_t konst;
+    int32_t offs[kSliceMaxWidth];
+    double val[kSliceMaxWidth];
+};
 
 struct Schedule {
     Bin bins[kMaxBins];
@@ -156,6 +181,8 @@ struct CsrDev {
     const int32_t *tile_row;  // adaptive stream tiles: first row of each tile (ntiles + 1)
     const uint8_t *sell_lenx; // gap-coded slices: length and offset bits per row (64 per slice)
     const uint16_t *sell_gap; //   slot-major 16-bit column codes
+    StenGlobal stg;           // global stencil (konst: st_off, st_offs and st_val do not exist)
+    const uint8_t *st_fast;   //   its fast tiles, one byte per 128 rows
 };
 
 // Per-block operands of the column-blocked tiling (kept on the host by the

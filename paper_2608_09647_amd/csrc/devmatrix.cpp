@@ -48,6 +48,9 @@ void free_sliced(DevMatrix &M) {
     M.d_st_mask = nullptr;
     M.d_st_val = nullptr;
     M.st_slots = 0;
+    M.stg = StenGlobal{};
+    (void)hipFree(M.d_st_fast);
+    M.d_st_fast = nullptr;
     (void)hipFree(M.d_sell_lenx);
     (void)hipFree(M.d_sell_gap);
     M.d_sell_lenx = nullptr;
@@ -71,23 +74,132 @@ void slice_offsets(const DevMatrix &M, int32_t nt, std::vector<int32_t> &off) {
     for (int32_t t = 0; t < nt; ++t) off[t + 1] += off[t];
 }
 
+// The global stencil of the block, if it has one (see StenGlobal): the union
+// of all rows' column offsets, at most kSliceMaxWidth, with konst where each
+// has one value bit for bit.  Every thread collects its rows' offsets and
+// values; a block with too many offsets costs each thread a few rows' work.
+bool find_global_stencil(const DevMatrix &M, StenGlobal &C) {
+    C = StenGlobal{};
+    if (M.m < 2) return false;
+    constexpr int W = kSliceMaxWidth;
+    const bool vals = M.konst_allowed && !M.h_val.empty();
+    // false: more than W offsets; konst is cleared at a second value
+    auto add = [](StenGlobal &S, int32_t o, double v) {
+        int e = 0;
+        while (e < S.width && S.offs[e] != o) ++e;
+        if (e < S.width) {
+            if (S.konst && std::memcmp(&S.val[e], &v, sizeof v) != 0) S.konst = 0;
+            return true;
+        }
+        if (S.width == W) return false;
+        S.offs[S.width] = o;
+        S.val[S.width++] = v;
+        return true;
+    };
+    C.konst = vals;
+    std::atomic<bool> ok{true};
+#pragma omp parallel
+    {
+        StenGlobal mine{};
+        mine.konst = vals;
+#pragma omp for schedule(static)
+        for (int32_t i = 0; i < M.m; ++i) {
+            if (!ok.load(std::memory_order_relaxed)) continue;
+            for (int32_t k = M.h_rp[i]; k < M.h_rp[i + 1]; ++k)
+                if (!add(mine, M.h_ci[k] - (M.pad_col_base + i), vals ? M.h_val[k] : 0.0)) {
+                    ok = false;
+                    break;
+                }
+        }
+#pragma omp critical(cgmi_global_stencil)
+        {
+            if (!mine.konst) C.konst = 0;
+            for (int e = 0; e < mine.width; ++e)
+                if (!add(C, mine.offs[e], mine.val[e])) ok = false;
+        }
+    }
+    if (!ok.load() || C.width == 0) {
+        C = StenGlobal{};
+        return false;
+    }
+    for (int a = 1; a < C.width; ++a)   // offsets ascending: slots in CSR order
+        for (int b = a; b > 0 && C.offs[b] < C.offs[b - 1]; --b) {
+            std::swap(C.offs[b], C.offs[b - 1]);
+            std::swap(C.val[b], C.val[b - 1]);
+        }
+    return true;
+}
+
+// Whether storing every slot of a global stencil in every slice costs at
+// most an eighth more than the slots the slices use (a 7-point operator's
+// first and last planes lack one slot each); otherwise each slice keeps its
+// own offsets.
+bool global_stencil_dense(const DevMatrix &M, const StenGlobal &C) {
+    const int32_t nt = (M.m + kWaveSize - 1) / kWaveSize;
+    int64_t used = 0;
+#pragma omp parallel for reduction(+ : used) schedule(static)
+    for (int32_t t = 0; t < nt; ++t) {
+        uint32_t any = 0;
+        for (int32_t i = t * kWaveSize; i < std::min(M.m, (t + 1) * kWaveSize); ++i)
+            for (int32_t k = M.h_rp[i], e = 0; k < M.h_rp[i + 1]; ++k) {
+                while (C.offs[e] != M.h_ci[k] - (M.pad_col_base + i)) ++e;
+                any |= 1u << e;
+            }
+        used += std::max(1, __builtin_popcount(any));
+    }
+    return (int64_t)nt * C.width <= used + used / 8;
+}
+
+// The fast tiles of a global stencil (see StenGlobal) from the rows' masks.
+// (m < 2^28: the kernel's 32-bit byte offsets.)
+void fast_tiles(const DevMatrix &M, const StenGlobal &C, const std::vector<uint8_t> &mask,
+                std::vector<uint8_t> &fast) {
+    const int32_t m = M.m, rows = 2 * kWaveSize;
+    const uint32_t all = (1u << C.width) - 1, part = glob_partial(C.width);
+    int32_t last = 0;   // the last column the vector is known to have
+#pragma omp parallel for reduction(max : last) schedule(static)
+    for (int32_t i = 0; i < m; ++i)
+        if (M.h_rp[i + 1] > M.h_rp[i]) last = std::max(last, M.h_ci[M.h_rp[i + 1] - 1]);
+    const int32_t nt = (m + rows - 1) / rows;
+    fast.assign((size_t)nt, 0);
+    if (!part || m >= (1 << 28)) return;
+#pragma omp parallel for schedule(static)
+    for (int32_t u = 0; u < m / rows; ++u) {
+        uint32_t full = all;
+        for (int32_t i = u * rows; i < (u + 1) * rows; ++i) full &= mask[(size_t)i];
+        const int64_t lo = (int64_t)M.pad_col_base + (int64_t)u * rows + C.offs[0];
+        const int64_t hi = (int64_t)M.pad_col_base + (int64_t)u * rows + C.offs[C.width - 1] + rows - 1;
+        fast[(size_t)u] = (full | part) == all && lo >= 0 && hi <= last;
+    }
+}
+
 // Stencil-sliced copy (see kTileStencil): per 64-row slice the sorted union
 // of the rows' column offsets, slot j of each row at offset j (value 0 where
 // absent) and a byte of slot bits per row.  false (nothing uploaded) when a
 // slice has more than kSliceMaxWidth distinct offsets; needs the host values.
 int build_stencil(DevMatrix &M, bool *fits) {
     *fits = false;
-    if (M.d_st_val) {
+    if (M.d_st_val || (M.stg.width > 0 && M.stg.konst)) {
         *fits = true;
         return CG_OK;
     }
     const int32_t m = M.m, nt = (m + kWaveSize - 1) / kWaveSize;
     constexpr int W = kSliceMaxWidth;
-    std::vector<int32_t> offs((size_t)nt * W, 0), width((size_t)nt, 1), off((size_t)nt + 1, 0);
+    StenGlobal G;
+    const bool global = find_global_stencil(M, G) &&
+                        (G.konst || (glob_partial(G.width) && global_stencil_dense(M, G)));
+    const bool konst = global && G.konst;
+    std::vector<int32_t> offs(konst ? 0 : (size_t)nt * W, 0), width(konst ? 0 : (size_t)nt, 1),
+        off(konst ? 0 : (size_t)nt + 1, 0);
     std::atomic<bool> ok{true};
 #pragma omp parallel for schedule(static)
-    for (int32_t t = 0; t < nt; ++t) {
+    for (int32_t t = 0; t < (konst ? 0 : nt); ++t) {
         if (!ok.load(std::memory_order_relaxed)) continue;
+        if (global) {   // every slice takes the block's offsets
+            for (int e = 0; e < G.width; ++e) offs[(size_t)t * W + e] = G.offs[e];
+            width[(size_t)t] = G.width;
+            continue;
+        }
         int32_t u[W];
         int nu = 0;
         for (int32_t i = t * kWaveSize; i < std::min(m, (t + 1) * kWaveSize) && nu <= W; ++i)
@@ -112,16 +224,21 @@ int build_stencil(DevMatrix &M, bool *fits) {
         width[(size_t)t] = std::max(nu, 1);
     }
     if (!ok.load()) return CG_OK;
-    for (int32_t t = 0; t < nt; ++t) off[t + 1] = off[t] + width[(size_t)t] * kWaveSize;
-    if ((int64_t)off[nt] >= INT32_MAX) return CG_OK;
-    const size_t slots = (size_t)off[nt];
-    const bool host_vals = !M.h_val.empty();
+    if (!konst) {
+        int64_t total = 0;
+        for (int32_t t = 0; t < nt; ++t) total += (int64_t)width[(size_t)t] * kWaveSize;
+        if (total >= INT32_MAX) return CG_OK;
+        for (int32_t t = 0; t < nt; ++t) off[t + 1] = off[t] + width[(size_t)t] * kWaveSize;
+    }
+    const size_t slots = konst ? 0 : (size_t)off[nt];
+    const bool host_vals = !konst && !M.h_val.empty();
     std::vector<double> sval(host_vals ? slots : 0, 0.0);
-    std::vector<uint8_t> mask((size_t)nt * kWaveSize, 0);
+    // whole 128-row tiles
+    std::vector<uint8_t> mask(((size_t)nt + 1) / 2 * 2 * kWaveSize, 0);
 #pragma omp parallel for schedule(static)
     for (int32_t t = 0; t < nt; ++t) {
-        const int32_t *u = &offs[(size_t)t * W];
-        const int w = width[(size_t)t];
+        const int32_t *u = konst ? G.offs : &offs[(size_t)t * W];
+        const int w = konst ? G.width : width[(size_t)t];
         for (int32_t l = 0; l < kWaveSize; ++l) {
             const int32_t i = t * kWaveSize + l;
             if (i >= m) break;
@@ -137,16 +254,25 @@ int build_stencil(DevMatrix &M, bool *fits) {
             mask[(size_t)i] = bits;
         }
     }
-    hipError_t e = dmalloc(&M.d_st_off, off.size());
-    if (e == hipSuccess) e = dmalloc(&M.d_st_offs, offs.size());
+    std::vector<uint8_t> fast;
+    if (global) fast_tiles(M, G, mask, fast);
+    hipError_t e = hipSuccess;
+    if (!konst) {
+        e = dmalloc(&M.d_st_off, off.size());
+        if (e == hipSuccess) e = dmalloc(&M.d_st_offs, offs.size());
+        if (e == hipSuccess) e = dmalloc(&M.d_st_val, slots);
+        if (e == hipSuccess)
+            e = hipMemcpy(M.d_st_off, off.data(), sizeof(int32_t) * off.size(), hipMemcpyHostToDevice);
+        if (e == hipSuccess)
+            e = hipMemcpy(M.d_st_offs, offs.data(), sizeof(int32_t) * offs.size(), hipMemcpyHostToDevice);
+    }
     if (e == hipSuccess) e = dmalloc(&M.d_st_mask, mask.size());
-    if (e == hipSuccess) e = dmalloc(&M.d_st_val, slots);
-    if (e == hipSuccess) e = hipMemcpy(M.d_st_off, off.data(), sizeof(int32_t) * off.size(), hipMemcpyHostToDevice);
-    if (e == hipSuccess)
-        e = hipMemcpy(M.d_st_offs, offs.data(), sizeof(int32_t) * offs.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(M.d_st_mask, mask.data(), mask.size(), hipMemcpyHostToDevice);
+    if (e == hipSuccess && global) e = dmalloc(&M.d_st_fast, fast.size());
+    if (e == hipSuccess && global)
+        e = hipMemcpy(M.d_st_fast, fast.data(), fast.size(), hipMemcpyHostToDevice);
     // values from the host copy, or zero until the owner writes them on the device
-    if (e == hipSuccess)
+    if (e == hipSuccess && !konst)
         e = host_vals ? hipMemcpy(M.d_st_val, sval.data(), sizeof(double) * slots, hipMemcpyHostToDevice)
                       : hipMemset(M.d_st_val, 0, sizeof(double) * slots);
     if (e != hipSuccess) {
@@ -156,9 +282,12 @@ int build_stencil(DevMatrix &M, bool *fits) {
         (void)hipFree(M.d_st_val);
         M.d_st_off = M.d_st_offs = nullptr;
         M.d_st_mask = nullptr;
+        (void)hipFree(M.d_st_fast);
         M.d_st_val = nullptr;
+        M.d_st_fast = nullptr;
         return fail(CG_ENOMEM, "stencil layout upload failed: %s", hipGetErrorString(e));
     }
+    if (global) M.stg = G;
     M.st_slots = slots;
     *fits = true;
     return CG_OK;
@@ -727,8 +856,8 @@ int dm_schedule(DevMatrix &M, int kind_opt, int grid_opt, int cus, int grid_cap,
         if (rc) return rc;
         M.use_gap = fits;
     }
-    if (M.sched.kind == kTileStencil)
-        M.sched.stream_nt = (int64_t)M.st_slots * (int64_t)sizeof(double) + (int64_t)M.m > kStreamNtBytes;
+    if (M.sched.kind == kTileStencil)   // constant values: the masks alone, always cached
+        M.sched.stream_nt = M.st_slots > 0 && (int64_t)M.st_slots * (int64_t)sizeof(double) + (int64_t)M.m > kStreamNtBytes;
     else if (M.sched.kind == kTileSliced)
         M.sched.stream_nt = (int64_t)M.sell_slots * (int64_t)(sizeof(double) + (M.use_gap ? 2 : 4)) + M.m >
                             kStreamNtBytes;

@@ -21,6 +21,8 @@
 #include <hip/hip_runtime.h>
 #include <math.h>
 
+#include <type_traits>
+
 #include "cgmi_internal.h"
 
 namespace cgmi {
@@ -611,18 +613,21 @@ __device__ __forceinline__ void spmv_dict_wave(const CsrDev &A, TileWalk &walk, 
 // summed in CSR order with rounded products (the slots ascend with the
 // column), so results are bit-exact against the oracle.  One tile at a time:
 // 54 registers, 8 waves per SIMD.  float64 only.
-template <int MODE, bool NT>
+// KONST: a global stencil with constant values, whose offsets and values come
+// from A.stg.
+template <int MODE, bool NT, bool KONST>
 __device__ __forceinline__ void spmv_sten_wave(const CsrDev &A, TileWalk &walk,
                                                const SpmvArgs<double> &a, double &acc0, double &acc1) {
     const int lane = threadIdx.x & (kWave - 1);
     for (int t = walk.next(); t >= 0; t = walk.next()) {
         const int r0 = __builtin_amdgcn_readfirstlane(t * kWave);
         const int nrows = min(kWave, A.m - r0);
-        const int off = A.st_off[t];
-        const int width = (A.st_off[t + 1] - off) / kWave;
+        const int off = KONST ? 0 : A.st_off[t];
+        const int width = KONST ? A.stg.width : (A.st_off[t + 1] - off) / kWave;
         int offs[kSliceMaxWidth];
 #pragma unroll
-        for (int j = 0; j < kSliceMaxWidth; ++j) offs[j] = A.st_offs[t * kSliceMaxWidth + j];
+        for (int j = 0; j < kSliceMaxWidth; ++j)
+            offs[j] = KONST ? A.stg.offs[j] : A.st_offs[t * kSliceMaxWidth + j];
         const int myrow = r0 + min(lane, nrows - 1);
         const int gcol = A.col_base + myrow;
         const uint8_t *mp = &A.st_mask[(int64_t)t * kWave + lane];
@@ -634,7 +639,7 @@ __device__ __forceinline__ void spmv_sten_wave(const CsrDev &A, TileWalk &walk,
             v[j] = pv[j] = 0.0;
             if (j < width) {
                 const int k = off + j * kWave + lane;
-                v[j] = NT ? __builtin_nontemporal_load(&A.st_val[k]) : A.st_val[k];
+                v[j] = KONST ? A.stg.val[j] : NT ? __builtin_nontemporal_load(&A.st_val[k]) : A.st_val[k];
                 pv[j] = a.p[(mask >> j) & 1u ? gcol + offs[j] : gcol];
             }
         }
@@ -716,6 +721,55 @@ __device__ __forceinline__ double x_owed(int xmode, double x, double alpha, doub
     return x;
 }
 
+// The two-row tiles' end: rows ra, ra + 1 (va, vb: inside the block) with
+// their sums sa, sb.
+template <int MODE, bool NT>
+__device__ __forceinline__ void sten2_emit(const SpmvArgs<double> &a, const DirArgs &D, int ra, bool va, bool vb,
+                                           double sa, double sb, double &acc0) {
+    if (MODE == kSpmvDir && va && vb) {
+        const dbl2v pk = *reinterpret_cast<const dbl2v *>(&a.p[ra]);
+        const dbl2v dv = *reinterpret_cast<const dbl2v *>(&D.d[ra]);
+        dbl2v *po = reinterpret_cast<dbl2v *>(&D.p_oth[ra]);
+        if (D.xmode) {
+            dbl2v *xp = reinterpret_cast<dbl2v *>(&D.x[ra]);
+            const dbl2v pp = D.xmode == 2 ? *po : dbl2v{0.0, 0.0};
+            dbl2v xv = *xp;
+            xv.x = x_owed(D.xmode, xv.x, D.alpha, pk.x, D.alpha_prev, pp.x);
+            xv.y = x_owed(D.xmode, xv.y, D.alpha, pk.y, D.alpha_prev, pp.y);
+            *xp = xv;
+        }
+        const dbl2v pn{fma(D.beta, pk.x, dv.x), fma(D.beta, pk.y, dv.y)};
+        *po = pn;
+        acc0 = fma(pn.x, sa, acc0);
+        acc0 = fma(pn.y, sb, acc0);
+        dbl2v qv{sa, sb};
+        dbl2v *qp = reinterpret_cast<dbl2v *>(&a.q[ra]);
+        if (NT) __builtin_nontemporal_store(qv, qp);
+        else *qp = qv;
+    } else if (MODE == kSpmvDir && va) {   // the last row of an odd row count
+        const double pk = a.p[ra];
+        if (D.xmode)
+            D.x[ra] = x_owed(D.xmode, D.x[ra], D.alpha, pk, D.alpha_prev, D.xmode == 2 ? D.p_oth[ra] : 0.0);
+        const double pn = fma(D.beta, pk, D.d[ra]);
+        D.p_oth[ra] = pn;
+        acc0 = fma(pn, sa, acc0);
+        a.q[ra] = sa;
+    } else if (va && vb) {
+        if (MODE == kSpmvDot) {
+            const dbl2v po = *reinterpret_cast<const dbl2v *>(&a.p_own[ra]);
+            acc0 = fma(po.x, sa, acc0);
+            acc0 = fma(po.y, sb, acc0);
+        }
+        dbl2v qv{sa, sb};
+        dbl2v *qp = reinterpret_cast<dbl2v *>(&a.q[ra]);
+        if (NT) __builtin_nontemporal_store(qv, qp);
+        else *qp = qv;
+    } else if (va) {   // the last row of an odd row count
+        if (MODE == kSpmvDot) acc0 = fma(a.p_own[ra], sa, acc0);
+        a.q[ra] = sa;
+    }
+}
+
 template <int MODE, bool NT>
 __device__ __forceinline__ void spmv_sten2_wave(const CsrDev &A, TileWalk &walk, const SpmvArgs<double> &a,
                                                 double &acc0, const DirArgs &D) {
@@ -779,49 +833,181 @@ __device__ __forceinline__ void spmv_sten2_wave(const CsrDev &A, TileWalk &walk,
                 if ((mb >> j) & 1u) sb = sb + v[j].y * pb[j];
             }
         }
-        if (MODE == kSpmvDir && va && vb) {
-            const dbl2v pk = *reinterpret_cast<const dbl2v *>(&a.p[ra]);
-            const dbl2v dv = *reinterpret_cast<const dbl2v *>(&D.d[ra]);
-            dbl2v *po = reinterpret_cast<dbl2v *>(&D.p_oth[ra]);
-            if (D.xmode) {
-                dbl2v *xp = reinterpret_cast<dbl2v *>(&D.x[ra]);
-                const dbl2v pp = D.xmode == 2 ? *po : dbl2v{0.0, 0.0};
-                dbl2v xv = *xp;
-                xv.x = x_owed(D.xmode, xv.x, D.alpha, pk.x, D.alpha_prev, pp.x);
-                xv.y = x_owed(D.xmode, xv.y, D.alpha, pk.y, D.alpha_prev, pp.y);
-                *xp = xv;
-            }
-            const dbl2v pn{fma(D.beta, pk.x, dv.x), fma(D.beta, pk.y, dv.y)};
-            *po = pn;
-            acc0 = fma(pn.x, sa, acc0);
-            acc0 = fma(pn.y, sb, acc0);
-            dbl2v qv{sa, sb};
-            dbl2v *qp = reinterpret_cast<dbl2v *>(&a.q[ra]);
-            if (NT) __builtin_nontemporal_store(qv, qp);
-            else *qp = qv;
-        } else if (MODE == kSpmvDir && va) {   // the last row of an odd row count
-            const double pk = a.p[ra];
-            if (D.xmode)
-                D.x[ra] = x_owed(D.xmode, D.x[ra], D.alpha, pk, D.alpha_prev, D.xmode == 2 ? D.p_oth[ra] : 0.0);
-            const double pn = fma(D.beta, pk, D.d[ra]);
-            D.p_oth[ra] = pn;
-            acc0 = fma(pn, sa, acc0);
-            a.q[ra] = sa;
-        } else if (va && vb) {
-            if (MODE == kSpmvDot) {
-                const dbl2v po = *reinterpret_cast<const dbl2v *>(&a.p_own[ra]);
-                acc0 = fma(po.x, sa, acc0);
-                acc0 = fma(po.y, sb, acc0);
-            }
-            dbl2v qv{sa, sb};
-            dbl2v *qp = reinterpret_cast<dbl2v *>(&a.q[ra]);
-            if (NT) __builtin_nontemporal_store(qv, qp);
-            else *qp = qv;
-        } else if (va) {   // the last row of an odd row count
-            if (MODE == kSpmvDot) acc0 = fma(a.p_own[ra], sa, acc0);
-            a.q[ra] = sa;
+        sten2_emit<MODE, NT>(a, D, ra, va, vb, sa, sb, acc0);
+    }
+}
+
+// Global stencil, two rows per lane (every mode): lane l of the 128-row tile
+// u owns the rows 128 u + 2 l and the next, and each slot's operands of p are
+// one 16-byte load per lane at a uniform base plus the tile's offset.
+// What bounds it is the issue of instructions, not memory, until both the
+// addresses and the selects are out of the loop (a wave64 instruction takes
+// four cycles): so the fast tiles (see StenGlobal) load every slot for every
+// row, all loads in flight at once, and look at the mask byte only for the
+// slots glob_partial names; the other tiles gather under their masks.
+// Every row is summed as in spmv_sten_wave (CSR order, rounded products); the
+// p^T q partial adds the lane's rows in order.  KONST: the values are
+// A.stg.val; otherwise slot j's values of the tile's two slices are 64
+// entries apart, read as 16-byte pairs (NT: nontemporally).  Direction mode:
+// as spmv_sten2_wave.  W: the stencil's width, or its bound (unused slots are
+// in no mask) where the width has no fast tiles.
+__device__ __forceinline__ dbl2v load_pair_at(const double *base, uint32_t bytes) {
+    return load_pair(reinterpret_cast<const double *>(reinterpret_cast<const char *>(base) + bytes));
+}
+
+// s + c x with the product rounded first.
+__device__ __forceinline__ double add_rounded(double s, double c, double x) {
+#pragma clang fp contract(off)
+    return s + c * x;
+}
+
+template <int MODE, bool NT>
+struct Glob2Rows {   // the lane's own entries of its two rows, loaded with the rest
+    dbl2v own{0.0, 0.0}, own2{0.0, 0.0}, xv{0.0, 0.0}, pp{0.0, 0.0};
+    __device__ __forceinline__ void load(const SpmvArgs<double> &a, const DirArgs &D, int ra) {
+        if (MODE == kSpmvDot) own = *reinterpret_cast<const dbl2v *>(a.p_own + ra);
+        if (MODE == kSpmvResidual) own = *reinterpret_cast<const dbl2v *>(a.b + ra);
+        if (MODE == kSpmvDir) {
+            own = *reinterpret_cast<const dbl2v *>(a.p + ra);
+            own2 = *reinterpret_cast<const dbl2v *>(D.d + ra);
+            if (D.xmode) xv = *reinterpret_cast<const dbl2v *>(D.x + ra);
+            if (D.xmode == 2) pp = *reinterpret_cast<const dbl2v *>(D.p_oth + ra);
         }
     }
+    __device__ __forceinline__ void finish(const SpmvArgs<double> &a, const DirArgs &D, int ra, double sa, double sb,
+                                           double &acc0, double &acc1) {
+        dbl2v out{sa, sb};
+        if (MODE == kSpmvDir) {
+            if (D.xmode)
+                *reinterpret_cast<dbl2v *>(D.x + ra) =
+                    dbl2v{x_owed(D.xmode, xv.x, D.alpha, own.x, D.alpha_prev, pp.x),
+                          x_owed(D.xmode, xv.y, D.alpha, own.y, D.alpha_prev, pp.y)};
+            own = dbl2v{fma(D.beta, own.x, own2.x), fma(D.beta, own.y, own2.y)};
+            *reinterpret_cast<dbl2v *>(D.p_oth + ra) = own;
+        }
+        if (MODE == kSpmvDot || MODE == kSpmvDir) {
+            acc0 = fma(own.x, sa, acc0);
+            acc0 = fma(own.y, sb, acc0);
+        }
+        if (MODE == kSpmvResidual) {
+            out = dbl2v{own.x - sa, own.y - sb};
+            *reinterpret_cast<dbl2v *>(a.p_dst + ra) = out;
+            acc0 = fma(out.x, out.x, acc0);
+            acc0 = fma(out.y, out.y, acc0);
+            acc1 = fma(own.x, own.x, acc1);
+            acc1 = fma(own.y, own.y, acc1);
+        }
+        dbl2v *qp = reinterpret_cast<dbl2v *>(a.q + ra);
+        if (NT) __builtin_nontemporal_store(out, qp);
+        else *qp = out;
+    }
+};
+
+template <int MODE, bool NT, bool KONST, int W>
+__device__ __forceinline__ void spmv_glob2_wave(const CsrDev &A, TileWalk &walk, const SpmvArgs<double> &a,
+                                                double &acc0, double &acc1, const DirArgs &D) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const StenGlobal &C = A.stg;
+    const int vlane = (lane >> 5) * (kWave * W) + 2 * (lane & 31);   // the lane's values in its tile
+    int u = walk.next();
+    if (u < 0) return;
+    uint32_t fast = A.st_fast[u], next = 0;
+    for (int un; u >= 0; u = un, fast = next) {
+        un = walk.next();
+        next = A.st_fast[un >= 0 ? un : u];
+        const int r0 = u * 2 * kWave, ra = r0 + 2 * lane;
+        if (glob_partial(W) && fast) {
+            const uint32_t at = (uint32_t)ra * 8u;
+            const uint32_t m2 = *reinterpret_cast<const uint16_t *>(&A.st_mask[ra]);
+            const double *vb = KONST ? nullptr : A.st_val + (int64_t)r0 * W;
+            dbl2v w[W], dv[W], v[W];
+#pragma unroll
+            for (int j = 0; j < W; ++j) {
+                w[j] = load_pair_at(a.p + A.col_base + C.offs[j], at);
+                if (MODE == kSpmvDir) dv[j] = load_pair_at(D.d + C.offs[j], at);
+                if (!KONST) {
+                    const dbl2v *vp = reinterpret_cast<const dbl2v *>(vb + j * kWave + vlane);
+                    v[j] = NT ? __builtin_nontemporal_load(vp) : *vp;
+                }
+            }
+            Glob2Rows<MODE, NT> R;
+            R.load(a, D, ra);
+            double sa = 0.0, sb = 0.0;
+#pragma unroll
+            for (int j = 0; j < W; ++j) {
+                dbl2v x = w[j];
+                if (MODE == kSpmvDir) x = dbl2v{fma(D.beta, x.x, dv[j].x), fma(D.beta, x.y, dv[j].y)};
+                const dbl2v c = KONST ? dbl2v{C.val[j], C.val[j]} : v[j];
+                const double ta = add_rounded(sa, c.x, x.x), tb = add_rounded(sb, c.y, x.y);
+                if ((glob_partial(W) >> j) & 1u) {
+                    sa = (m2 >> j) & 1u ? ta : sa;
+                    sb = (m2 >> (8 + j)) & 1u ? tb : sb;
+                } else {
+                    sa = ta;
+                    sb = tb;
+                }
+            }
+            R.finish(a, D, ra, sa, sb, acc0, acc1);
+            continue;
+        }
+        const bool va = ra < A.m, vb = ra + 1 < A.m;
+        const int rc[2] = {min(ra, A.m - 1), min(ra + 1, A.m - 1)};
+        const uint32_t mk[2] = {va ? A.st_mask[rc[0]] : 0u, vb ? A.st_mask[rc[1]] : 0u};
+        double w[2][W], dw[2][W], vv[2][W];
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int j = 0; j < W; ++j) {
+                const int g = A.col_base + rc[h];
+                const int c = (mk[h] >> j) & 1u ? g + C.offs[j] : g;   // a slot the row lacks: its own entry
+                w[h][j] = a.p[c];
+                if (MODE == kSpmvDir) dw[h][j] = D.d[c];
+                if (!KONST)
+                    vv[h][j] = A.st_val[((int64_t)(rc[h] / kWave) * W + j) * kWave + rc[h] % kWave];
+            }
+        double s2[2] = {0.0, 0.0};
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int j = 0; j < W; ++j) {
+                const double x = MODE == kSpmvDir ? fma(D.beta, w[h][j], dw[h][j]) : w[h][j];
+                const double t = add_rounded(s2[h], KONST ? C.val[j] : vv[h][j], x);
+                if ((mk[h] >> j) & 1u) s2[h] = t;
+            }
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            if (!(h ? vb : va)) continue;
+            const int row = ra + h;
+            if (MODE == kSpmvDir) {
+                const double pk = a.p[row];
+                if (D.xmode)
+                    D.x[row] = x_owed(D.xmode, D.x[row], D.alpha, pk, D.alpha_prev,
+                                      D.xmode == 2 ? D.p_oth[row] : 0.0);
+                const double pn = fma(D.beta, pk, D.d[row]);
+                D.p_oth[row] = pn;
+                acc0 = fma(pn, s2[h], acc0);
+                a.q[row] = s2[h];
+            } else {
+                emit_row<MODE, double>(a, row, s2[h], acc0, acc1);
+            }
+        }
+    }
+}
+
+// Launches with the width of stencil C and its form F (0 values cached, 1
+// values nontemporal, 2 constant values) as constants; widths without fast
+// tiles only occur with constant values.
+template <class L>
+void glob_form(const StenGlobal &C, bool nt, L &&launch) {
+    auto form = [&](auto w) {
+        if (C.konst) launch(w, std::integral_constant<int, 2>{});
+        else if (nt) launch(w, std::integral_constant<int, 1>{});
+        else launch(w, std::integral_constant<int, 0>{});
+    };
+    if (C.width == 3) form(std::integral_constant<int, 3>{});
+    else if (C.width == 5) form(std::integral_constant<int, 5>{});
+    else if (C.width == 7) form(std::integral_constant<int, 7>{});
+    else launch(std::integral_constant<int, kSliceMaxWidth>{}, std::integral_constant<int, 2>{});
 }
 
 // Sliced tiles, two rows per lane (float64, slices of at most kSliceMaxWidth
@@ -1006,7 +1192,10 @@ __device__ __forceinline__ void spmv_row_wg(const CsrDev &A, int pos, bool ident
 // same with two rows per lane and 16-byte accesses (plain and dot modes);
 // -10 / -11: sliced tiles with two rows per lane, cached / nontemporal
 // (float64, plain and dot modes); -12 / -13: the same with gap-coded columns;
-// -14: sliced tiles (one row per lane) with gap-coded columns.
+// -14: sliced tiles (one row per lane) with gap-coded columns;
+// -15: global stencil with constant values, one row per lane;
+// -100 - 10 F - W: global stencil of width W (glob_form), two rows per lane,
+// F = 0 cached, 1 nontemporal, 2 constant values.
 template <int MODE, int TILE, class T>
 __global__ __launch_bounds__(kBlock) void k_spmv(int32_t m, const int32_t *__restrict__ rp,
                                                  const int32_t *__restrict__ ci,
@@ -1025,12 +1214,12 @@ __global__ __launch_bounds__(kBlock) void k_spmv(int32_t m, const int32_t *__res
                                                  const int32_t *__restrict__ tile_row,
                                                  const uint8_t *__restrict__ sell_lenx,
                                                  const uint16_t *__restrict__ sell_gap,
-                                                 Schedule S, SpmvArgs<T> a, double *__restrict__ out,
+                                                 StenGlobal stg, const uint8_t *__restrict__ st_fast, Schedule S, SpmvArgs<T> a, double *__restrict__ out,
                                                  Partials in0, Partials in1,
                                                  DevState *__restrict__ st, int flags) {
     CsrDev A{m, rp, ci, nullptr, rows, sell_off, sell_ci, nullptr, nullptr, nullptr,
              sell_idx, sell_dict, col_base, nullptr, st_off, st_offs, st_mask, st_val, sell_len, tile_row,
-             sell_lenx, sell_gap};
+             sell_lenx, sell_gap, stg, st_fast};
     if constexpr (sizeof(T) == 8) {
         A.val = reinterpret_cast<const double *>(val);
         A.sell_val = reinterpret_cast<const double *>(sell_val);
@@ -1060,7 +1249,7 @@ __global__ __launch_bounds__(kBlock) void k_spmv(int32_t m, const int32_t *__res
     }
     double acc0 = 0.0, acc1 = 0.0;
     const bool identity = S.identity != 0;
-    TileWalk walk(TILE <= -8 && TILE >= -13 ? (S.ntiles + 1) / 2 : S.ntiles);   // slice pairs
+    TileWalk walk((TILE <= -8 && TILE >= -13) || TILE <= -100 ? (S.ntiles + 1) / 2 : S.ntiles);   // slice pairs
     if constexpr (TILE == -2 || TILE == -3) {
         spmv_sliced_wave<MODE, T, false>(A, walk, a, TILE == -3, acc0, acc1);
     } else if constexpr (TILE == -14) {
@@ -1068,7 +1257,12 @@ __global__ __launch_bounds__(kBlock) void k_spmv(int32_t m, const int32_t *__res
     } else if constexpr (TILE == -4 || TILE == -5) {
         spmv_dict_wave<MODE, T, TILE == -5>(A, walk, a, acc0, acc1);
     } else if constexpr (TILE == -6 || TILE == -7) {
-        if constexpr (sizeof(T) == 8) spmv_sten_wave<MODE, TILE == -7>(A, walk, a, acc0, acc1);
+        if constexpr (sizeof(T) == 8) spmv_sten_wave<MODE, TILE == -7, false>(A, walk, a, acc0, acc1);
+    } else if constexpr (TILE == -15) {
+        if constexpr (sizeof(T) == 8) spmv_sten_wave<MODE, false, true>(A, walk, a, acc0, acc1);
+    } else if constexpr (TILE <= -100) {
+        constexpr int F = (-100 - TILE) / 10, W = (-100 - TILE) % 10;
+        spmv_glob2_wave<MODE, F == 1, F == 2, W>(A, walk, a, acc0, acc1, DirArgs{});
     } else if constexpr (TILE == -8 || TILE == -9) {
         if constexpr (sizeof(T) == 8 && (MODE == kSpmvPlain || MODE == kSpmvDot))
             spmv_sten2_wave<MODE, TILE == -9>(A, walk, a, acc0, DirArgs{});
@@ -1684,8 +1878,11 @@ __global__ __launch_bounds__(kBlock) void k_update_p_pcg(int32_t m, const double
 // kernel's stop path does, and records no partial.  x, p, q and the
 // partials are bitwise those of the separate kernels on the same grid.
 // Workgroup 0 records iteration k+1 in spmv_iter when its SpMV runs.
-template <bool NT, bool PCG>
-__global__ __launch_bounds__(kBlock) void k_spmv_dir(int32_t m, const int32_t *__restrict__ st_off,
+// FORM: 0 stencil slices with their own offsets; 1 global stencil; 2 global
+// stencil with constant values (W as in spmv_glob2_wave).
+template <bool NT, bool PCG, int FORM, int W>
+__global__ __launch_bounds__(kBlock) void k_spmv_dir(int32_t m, StenGlobal stg, const uint8_t *__restrict__ st_fast,
+                                                     const int32_t *__restrict__ st_off,
                                                      const int32_t *__restrict__ st_offs,
                                                      const uint8_t *__restrict__ st_mask,
                                                      const double *__restrict__ st_val,
@@ -1727,10 +1924,14 @@ __global__ __launch_bounds__(kBlock) void k_spmv_dir(int32_t m, const int32_t *_
     A.st_offs = st_offs;
     A.st_mask = st_mask;
     A.st_val = st_val;
+    A.stg = stg;
+    A.st_fast = st_fast;
     const SpmvArgs<double> a{p_cur, q, nullptr, nullptr, nullptr};
     double acc0 = 0.0;
     TileWalk walk(((m + kWave - 1) / kWave + 1) / 2);   // slice pairs
-    spmv_sten2_wave<kSpmvDir, NT>(A, walk, a, acc0, D);
+    double acc1 = 0.0;
+    if constexpr (FORM > 0) spmv_glob2_wave<kSpmvDir, NT, FORM == 2, W>(A, walk, a, acc0, acc1, D);
+    else spmv_sten2_wave<kSpmvDir, NT>(A, walk, a, acc0, D);
     const double s0 = block_sum<kBlock>(acc0, sh);
     if (threadIdx.x == 0) out[blockIdx.x] = s0;
 }
@@ -1870,7 +2071,8 @@ void launch_spmv_mode(const CsrDev &A, const Schedule &S, int grid, const SpmvAr
     // stencil slices with two rows per lane where the 16-byte accesses are aligned
     const bool wide = sizeof(T) == 8 && (MODE == kSpmvPlain || MODE == kSpmvDot) &&
                       ((uintptr_t)a.q & 15) == 0 && (MODE != kSpmvDot || ((uintptr_t)a.p_own & 15) == 0);
-    const int L = S.kind == kTileStencil ? (wide ? (S.stream_nt ? -9 : -8) : (S.stream_nt ? -7 : -6))
+    const int L = S.kind == kTileStencil && A.stg.konst ? -15
+                  : S.kind == kTileStencil ? (wide ? (S.stream_nt ? -9 : -8) : (S.stream_nt ? -7 : -6))
                   : S.kind == kTileSlicedDict ? (S.stream_nt ? -5 : -4)
                   : S.kind == kTileSliced ? (S.bins[0].lanes <= kSliceMaxWidth
                                                  ? (wide && A.sell_len
@@ -1892,7 +2094,18 @@ void launch_spmv_mode(const CsrDev &A, const Schedule &S, int grid, const SpmvAr
     hipLaunchKernelGGL((k_spmv<MODE, FL, T>), dim3(grid), dim3(kBlock), 0, s, A.m, A.rp, A.ci, val, \
                        A.rows, A.sell_off, A.sell_ci, sval, A.sell_idx, A.sell_dict, A.col_base,       \
                        A.st_off, A.st_offs, A.st_mask, A.st_val, A.sell_len, A.tile_row, A.sell_lenx,   \
-                       A.sell_gap, S, a, out, in0, in1, st, flags)
+                       A.sell_gap, A.stg, A.st_fast, S, a, out, in0, in1, st, flags)
+    // global stencils, in the residual mode too
+    if constexpr (sizeof(T) == 8 && MODE != kSpmvAccum) {
+        const bool aligned = (((uintptr_t)a.q | (MODE == kSpmvDot ? (uintptr_t)a.p_own : 0) |
+                               (MODE == kSpmvResidual ? (uintptr_t)a.b | (uintptr_t)a.p_dst : 0)) & 15) == 0;
+        if (S.kind == kTileStencil && A.stg.width > 0 && aligned) {
+            glob_form(A.stg, S.stream_nt, [&](auto w, auto f) {
+                CGMI_SPMV((-100 - 10 * decltype(f)::value - decltype(w)::value));
+            });
+            return;
+        }
+    }
     switch (L) {
         case 1: CGMI_SPMV(1); break;
         case 2: CGMI_SPMV(2); break;
@@ -1915,6 +2128,7 @@ void launch_spmv_mode(const CsrDev &A, const Schedule &S, int grid, const SpmvAr
         case -12: CGMI_SPMV(-12); break;
         case -13: CGMI_SPMV(-13); break;
         case -14: CGMI_SPMV(-14); break;
+        case -15: CGMI_SPMV(-15); break;
         default: CGMI_SPMV(0); break;
     }
 #undef CGMI_SPMV
@@ -2058,7 +2272,7 @@ hipError_t launch_update_pxb(int32_t m, int grid, double *x, const double *r, co
 bool spmv_dir_applies(const CsrDev &A, const Schedule &S, int grid, const void *p_cur, const void *d,
                       const void *p_oth, const void *x, const void *q) {
     auto a16 = [](const void *v) { return ((uintptr_t)v & 15) == 0; };
-    return S.kind == kTileStencil && A.st_val && A.col_base == 0 && A.m >= 2 && S.ntiles == (A.m + kWave - 1) / kWave &&
+    return S.kind == kTileStencil && (A.st_val || A.stg.konst) && A.col_base == 0 && A.m >= 2 && S.ntiles == (A.m + kWave - 1) / kWave &&
            grid >= 8 && (grid & 7) == 0 && a16(p_cur) && a16(d) && a16(p_oth) && a16(x) && a16(q);
 }
 
@@ -2067,16 +2281,25 @@ hipError_t launch_spmv_dir(const CsrDev &A, const Schedule &S, int grid, const d
                            DevState *st, int32_t k, int pcg, hipStream_t s) {
     if (A.m == 0) return hipSuccess;
     if (!spmv_dir_applies(A, S, grid, p_cur, d, p_oth, x, q) || !st || !out) return hipErrorInvalidValue;
-#define CGMI_SPMV_DIR(NT, PCG)                                                                        \
-    hipLaunchKernelGGL((k_spmv_dir<NT, PCG>), dim3(grid), dim3(kBlock), 0, s, A.m, A.st_off, A.st_offs,  \
-                       A.st_mask, A.st_val, p_cur, d, p_oth, x, q, out, rr, rz, st, k)
-    if (S.stream_nt) {
-        if (pcg) CGMI_SPMV_DIR(true, true);
-        else CGMI_SPMV_DIR(true, false);
+#define CGMI_SPMV_DIR(NT, PCG, FORM, W)                                                               \
+    hipLaunchKernelGGL((k_spmv_dir<NT, PCG, FORM, W>), dim3(grid), dim3(kBlock), 0, s, A.m, A.stg, A.st_fast, \
+                       A.st_off, A.st_offs, A.st_mask, A.st_val, p_cur, d, p_oth, x, q, out, rr, rz, st, k)
+#define CGMI_SPMV_DIR_PCG(NT, FORM, W)                                                                \
+    do {                                                                                              \
+        if (pcg) CGMI_SPMV_DIR(NT, true, FORM, W);                                                    \
+        else CGMI_SPMV_DIR(NT, false, FORM, W);                                                       \
+    } while (0)
+    if (A.stg.width > 0) {
+        glob_form(A.stg, S.stream_nt, [&](auto w, auto f) {
+            constexpr int W = decltype(w)::value, F = decltype(f)::value;
+            CGMI_SPMV_DIR_PCG(F == 1, F == 2 ? 2 : 1, W);
+        });
+    } else if (S.stream_nt) {
+        CGMI_SPMV_DIR_PCG(true, 0, 0);
     } else {
-        if (pcg) CGMI_SPMV_DIR(false, true);
-        else CGMI_SPMV_DIR(false, false);
+        CGMI_SPMV_DIR_PCG(false, 0, 0);
     }
+#undef CGMI_SPMV_DIR_PCG
 #undef CGMI_SPMV_DIR
     return hipGetLastError();
 }

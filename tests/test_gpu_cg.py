@@ -1084,3 +1084,57 @@ def test_small_path_launch_is_event_timed(cg):
         x1, r1 = s.solve(dev(p.b), tol=1e-10, maxit=20000)
     assert r1["n_spmv"] == 1 and 0.0 < r1["t_spmv"] <= r1["t_gpu"]
     assert r1["iterations"] == r0["iterations"] and np.array_equal(host(x0), host(x1))
+
+
+def banded(n, offs, values, seed=0):
+    """Symmetric operator with entries at the given offsets (0 among them),
+    line ends cut like a grid's: an entry at +-1 is absent where the row
+    starts or ends a line of the next larger offset."""
+    line = min([o for o in offs if o > 1], default=n)
+    i = np.arange(n)
+    diags, pos = [], []
+    rng = np.random.default_rng(seed)
+    for o in sorted(o for o in offs if o > 0):
+        v = np.full(n - o, -1.0) if values == "const" else -rng.uniform(0.5, 1.5, n - o)
+        if o == 1:
+            v = np.where((i[:-1] + 1) % line == 0, 0.0, v)
+        diags += [v, v]
+        pos += [-o, o]
+    S = sp.diags(diags, pos, shape=(n, n)).tocsr() if pos else sp.csr_matrix((n, n))
+    S.eliminate_zeros()
+    S = (S + sp.diags(np.full(n, 2.0 * len(offs)))).tocsr()
+    if values == "one_differs":
+        S.data[:] = np.where(S.data > 0, S.data, -1.0)
+        S[n // 2, n // 2] = 31.0
+    S.sort_indices()
+    return I.CSR(n, S.indptr.astype(np.int32), S.indices.astype(np.int32), S.data)
+
+
+@pytest.mark.parametrize("values", ["const", "one_differs", "random"])
+@pytest.mark.parametrize("n,offs", [
+    (2, (-1, 0, 1)), (127, (-1, 0, 1)), (128, (0,)), (640, (-1, 0, 1)), (1001, (-64, -1, 0, 1, 64)),
+    (1280, (-100, -1, 0, 1, 100)), (4097, (-1024, -32, -1, 0, 1, 32, 1024)), (5000, (-777, -31, -1, 0, 1, 31, 777)),
+    (900, (-9, -3, 0, 3, 9)), (700, (-5, 0, 5)), (1500, (-200, -20, -3, 0, 3, 20, 200))])
+def test_global_stencil_forms(cg, n, offs, values):
+    """Operators whose block has at most 8 distinct offsets, with constant
+    values, all but one constant, and varying ones, of every width class,
+    tiles inside and at the ends of the vector: SpMV (aligned and 8 bytes off)
+    bit-exact, and a solve with the direction update fused and separate equal
+    bit for bit."""
+    if n == 2 and values == "one_differs":
+        pytest.skip("a diagonal of two values on two rows is covered by random")
+    A = banded(n, offs, values)
+    x = np.random.default_rng(23).uniform(-1, 1, n)
+    ref = oracle.spmv(A, x)
+    b = I.rhs_of(A, I.uniform_vector(n, [29, 1]))
+    out = {}
+    for fuse in (1, 2):
+        with cg.Solver(A) as s:
+            s.set_opts(spmv_kind=6, small_path=0, fuse_dir=fuse)
+            assert used_kind(s, n) == 6
+            assert np.array_equal(host(s.spmv(dev(x))), ref)
+            off = torch.zeros(n + 1, dtype=torch.float64, device="cuda")[1:]
+            assert np.array_equal(host(s.spmv(dev(x), off)), ref)
+            xs, res = s.solve(dev(b), tol=0.0, maxit=5)
+            out[fuse] = (host(xs), res["rel_res_true"])
+    assert np.array_equal(out[1][0], out[2][0]) and out[1][1] == out[2][1]
