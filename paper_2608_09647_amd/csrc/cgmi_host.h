@@ -16,6 +16,7 @@
 
 #include "../../include/cgmi.h"
 #include "cgmi_internal.h"
+#include "staged_internal.h"
 
 namespace cgmi {
 
@@ -107,6 +108,14 @@ hipError_t dmalloc(T **p, size_t count) {
             return ::cgmi::fail(CG_EDEVICE, "%s failed: %s", #expr, hipGetErrorString(e_));     \
     } while (0)
 
+// Staged column segments of a block (staged.cpp): 0 not built, 1 built, -1
+// the block does not take them.
+template <class T>
+struct StagedMem {
+    StagedDev<T> dev{};
+    int8_t state = 0;
+};
+
 // A block of CSR rows on the device: rebased row pointers, global column
 // indices, float64 values (col/val padded by kStreamNnz entries), its SpMV
 // schedule, and on demand the sliced copy and float32 copies of the values.
@@ -138,6 +147,9 @@ struct DevMatrix {
     StenGlobal stg{};                 //   global stencil (konst: no slot values are stored)
     uint8_t *d_st_fast = nullptr;     //   its fast tiles
     bool konst_allowed = false;       //   the owner's kernels take constant values
+    StagedMem<double> st64;           // staged column segments (state 1: the products run on them)
+    StagedMem<float> st32;
+    bool use_st64 = false, use_st32 = false;   // for the current options
     std::vector<DevMatrix> blocks;    // column-blocked layout: one CSR per column block
     ColBlocks *cb = nullptr;          //   and their launch operands
     int32_t block_cols = 0;           //   columns per block
@@ -148,7 +160,8 @@ struct DevMatrix {
                       d_sell_off, d_sell_ci, d_sell_val, d_val32, d_sell_val32,
                       d_sell_idx, d_sell_dict, pad_col_base, cb,
                       d_st_off, d_st_offs, d_st_mask, d_st_val, d_sell_len, d_tile_row,
-                      use_gap ? d_sell_lenx : nullptr, use_gap ? d_sell_gap : nullptr, stg, d_st_fast};
+                      use_gap ? d_sell_lenx : nullptr, use_gap ? d_sell_gap : nullptr, stg, d_st_fast,
+                      use_st64 ? &st64.dev : nullptr, use_st32 ? &st32.dev : nullptr};
     }
 };
 
@@ -167,6 +180,20 @@ int dm_upload(DevMatrix &M, int32_t m, const int32_t *rp, const int32_t *ci, con
 int dm_schedule(DevMatrix &M, int kind_opt, int grid_opt, int cus, int grid_cap, bool need_f32,
                 int32_t block_cols = 0);
 int dm_ensure_f32(DevMatrix &M);
+// Row blocks of at most kStagedRows rows on average and groups of segments:
+// one workgroup (a block and a group) per compute unit, as many groups (at
+// most 8) as the blocks' size allows.
+struct StagedShape {
+    int32_t nblocks, ngroups;
+};
+StagedShape staged_shape(int32_t m, int cus);
+// Builds the staged column segments of M with values of type T (S.state 1),
+// or leaves S.state -1 where they do not apply: rows over kHugeRow entries, a
+// vector of few segments, too much padding.  Rows are summed in float64.
+template <class T>
+void staged_build(DevMatrix &M, int cus, StagedMem<T> &S);
+template <class T>
+void staged_free(StagedMem<T> &S);
 void dm_free(DevMatrix &M);
 
 }  // namespace cgmi

@@ -790,6 +790,23 @@ int dm_ensure_f32(DevMatrix &M) {
     return CG_OK;
 }
 
+// Whether staged column segments beat the kernels that gather from the L2 for
+// values of `elem` bytes, by what both take on matrices of random columns
+// (200K-2M rows of 15-81 entries): the staged sums 18 us, 1/14 us per MB of
+// segments and 1/350 us per 1000 entries; the gathers 1/140 us per 1000
+// entries, 1/120 where the vector exceeds an L2.  Measured at the two sides of
+// the line (float64): 1M rows of 15 entries 120 us staged against 122 us, of
+// 21 entries 142 against 170 us; 1.5M rows of 17 entries 299 against 244 us.
+// Under 196608 rows, where a wave's lists come to a step or two, little is
+// won: 150K rows of 51 entries 51 against 52 us (float32 50 against 48), 70K
+// rows of 81 entries 39 against 40 us.
+static bool staged_pays(const DevMatrix &M, int32_t ncols, int cus, size_t elem) {
+    const StagedShape S = staged_shape(M.m, cus);
+    const double staged = (double)S.nblocks * ncols * (double)elem / 14e12 + (double)M.nnz / 350e9 + 18e-6;
+    const double gathers = (double)M.nnz / ((double)ncols * (double)elem > (4 << 20) ? 120e9 : 140e9);
+    return M.m >= 196608 && staged < 0.95 * gathers;
+}
+
 int dm_schedule(DevMatrix &M, int kind_opt, int grid_opt, int cus, int grid_cap, bool need_f32,
                 int32_t block_cols) {
     std::vector<int32_t> rows;
@@ -800,7 +817,27 @@ int dm_schedule(DevMatrix &M, int kind_opt, int grid_opt, int cus, int grid_cap,
         const int rc = set_stream_tiles(M, M.sched, tiles);
         if (rc) return rc;
     }
-    if (M.sched.kind == kTileColBlocked) {
+    const int waves_needed = M.sched.ntiles + M.sched.huge_count * (kBlock / kWaveSize);
+    const int auto_grid = ((waves_needed / (kBlock / kWaveSize) + 8) / 8) * 8;
+    const int grid = std::max(8, std::min(grid_opt > 0 ? grid_opt : std::min(cus * 8, auto_grid), grid_cap) / 8 * 8);
+    // staged column segments in place of vector bins chosen automatically and
+    // of column blocks of the default width; float32 products beside them, not
+    // instead of the float64 ones (the residual of mixed precision)
+    M.use_st64 = M.use_st32 = false;
+    if (((M.sched.kind == kTileColBlocked && (kind_opt == 0 || kind_opt == 5) && block_cols <= 0) ||
+         (M.sched.kind == kTileVector && kind_opt == 0)) && !M.h_val.empty()) {
+        int32_t ncols = 0;
+#pragma omp parallel for reduction(max : ncols) schedule(static)
+        for (int32_t i = 0; i < M.m; ++i)
+            if (M.h_rp[i + 1] > M.h_rp[i]) ncols = std::max(ncols, M.h_ci[M.h_rp[i + 1] - 1] + 1);
+        const bool w64 = staged_pays(M, ncols, cus, sizeof(double));
+        const bool w32 = need_f32 && staged_pays(M, ncols, cus, sizeof(float));
+        if (w64 && M.st64.state == 0) staged_build<double>(M, cus, M.st64);
+        if (w32 && M.st32.state == 0) staged_build<float>(M, cus, M.st32);
+        M.use_st64 = w64 && M.st64.state > 0;
+        M.use_st32 = w32 && M.st32.state > 0;
+    }
+    if (M.sched.kind == kTileColBlocked && !(M.use_st64 && (M.use_st32 || !need_f32))) {
         const int32_t bc = block_cols > 0 ? block_cols : kColBlockCols;
         if (M.cb && M.block_cols == bc && need_f32)
             for (int b = 0; b < M.cb->nb; ++b) {
@@ -873,11 +910,7 @@ int dm_schedule(DevMatrix &M, int kind_opt, int grid_opt, int cus, int grid_cap,
         const int rc = dm_ensure_f32(M);
         if (rc) return rc;
     }
-    const int waves_needed = M.sched.ntiles + M.sched.huge_count * (kBlock / kWaveSize);
-    const int auto_grid = ((waves_needed / (kBlock / kWaveSize) + 8) / 8) * 8;
-    int g = grid_opt > 0 ? grid_opt : std::min(cus * 8, auto_grid);
-    g = std::min(g, grid_cap);
-    M.grid = std::max(8, (g / 8) * 8);
+    M.grid = grid;
     return CG_OK;
 }
 
@@ -891,6 +924,9 @@ void dm_free(DevMatrix &M) {
     (void)hipFree(M.d_val);
     (void)hipFree(M.d_val32);
     free_sliced(M);
+    staged_free(M.st64);
+    staged_free(M.st32);
+    M.use_st64 = M.use_st32 = false;
     M.d_rp = M.d_ci = M.d_rows = nullptr;
     M.d_val = nullptr;
     M.d_val32 = nullptr;

@@ -1,0 +1,63 @@
+// Staged column segments (kernels_staged.hip): the layout shared by the
+// kernels and the host code that builds it (staged.cpp).
+#pragma once
+#include <hip/hip_runtime_api.h>
+#include <stdint.h>
+
+#include "cgmi_internal.h"
+
+namespace cgmi {
+
+constexpr int kStagedWaves = 16;                     // waves per workgroup
+constexpr size_t kStagedLds = 158 * 1024;            // of 160 KB per compute unit
+constexpr int kStagedChunks = 4;                     // 16-byte pieces of a segment per thread, at most
+constexpr int kStagedAhead = 6;                      // steps of a list loaded ahead, at most
+constexpr int kStagedSlack = kStagedAhead * kWaveSize;   // entries past the last list that may be loaded
+constexpr int kStagedPerSlot = 4;                    // entries of a row and segment per slot, at most on average
+constexpr int kStagedRows = 8192;                    // rows per block aimed at (64 KB of sums)
+
+// An entry's word: column in the segment (15 bits), turn (3), slot of its
+// row's sum in the block (14; the slot after the block's last is a dummy).
+constexpr int kStagedColBits = 15, kStagedTurnBits = 3;
+constexpr uint32_t kStagedTurns = 1u << kStagedTurnBits;
+constexpr int kStagedMaxSlots = (1 << (32 - kStagedColBits - kStagedTurnBits)) - 1;
+CGMI_HD constexpr inline uint32_t staged_word(uint32_t col, uint32_t turn, uint32_t slot) {
+    return col | turn << kStagedColBits | slot << (kStagedColBits + kStagedTurnBits);
+}
+CGMI_HD constexpr inline uint32_t staged_col(uint32_t w) { return w & ((1u << kStagedColBits) - 1); }
+CGMI_HD constexpr inline uint32_t staged_turn(uint32_t w) { return w >> kStagedColBits & (kStagedTurns - 1); }
+CGMI_HD constexpr inline uint32_t staged_slot(uint32_t w) { return w >> (kStagedColBits + kStagedTurnBits); }
+
+// LDS of a workgroup: two segments, and the block's slots with the dummy.
+CGMI_HD constexpr inline size_t staged_lds(int seg_cols, size_t elem, int max_slots) {
+    return 2 * elem * (size_t)seg_cols + sizeof(double) * ((size_t)max_slots + 1);
+}
+
+template <class T>
+struct StagedDev {
+    int32_t m;
+    int32_t nblocks, ngroups;     // row blocks, groups of segments (a workgroup takes one of each)
+    int32_t nseg, seg_cols;       // segments, columns per segment
+    int32_t max_slots;            // slots of the longest block
+    int32_t ncols;                // columns the vector is known to have
+    int32_t ahead;                // steps of a list that the average one has, and one more
+    const int32_t *row0;          // [nblocks * kStagedWaves + 1] first row of every wave
+    const int32_t *nslots;        // [nblocks] slots of every block
+    const int32_t *off;           // [nblocks * kStagedWaves * nseg + 1] first entry of every wave's list per segment
+    const uint32_t *idx;          // staged_word of every entry
+    const T *val;
+    const uint32_t *slots;        // per row: its first slot in the block | its slots << 16; null: one each, in order
+    double *part;                 // [ngroups * m] the groups' sums of every row
+};
+
+// Lets the kernels use kStagedLds bytes of LDS on the current device.
+hipError_t staged_setup();
+// The modes of launch_spmv / launch_spmv_f32; grid: workgroups of the second
+// kernel, and the partials in out (twice that in the residual mode).
+hipError_t launch_spmv_staged(const StagedDev<double> &D, int grid, const double *p, double *q, const double *p_own,
+                              const double *b, double *p_dst, double *out, Partials in0, Partials in1,
+                              DevState *st, int mode, int k0_check, hipStream_t s);
+hipError_t launch_spmv_staged_f32(const StagedDev<float> &D, int grid, const float *p, float *q, const float *p_own,
+                                  double *out, DevState *st, int mode, hipStream_t s);
+
+}  // namespace cgmi

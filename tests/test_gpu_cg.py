@@ -1138,3 +1138,73 @@ def test_global_stencil_forms(cg, n, offs, values):
             xs, res = s.solve(dev(b), tol=0.0, maxit=5)
             out[fuse] = (host(xs), res["rel_res_true"])
     assert np.array_equal(out[1][0], out[2][0]) and out[1][1] == out[2][1]
+
+
+def scattered(n, per_row, long_rows, seed=5):
+    """Random columns over the whole vector, about per_row entries a row, a few
+    rows of 1,500 entries, some empty rows (not symmetric: products only)."""
+    rng = np.random.default_rng(seed)
+    cnt = rng.poisson(per_row, n)
+    cnt[rng.integers(0, n, n // 50)] = 0
+    cnt[rng.choice(n, long_rows, replace=False)] = 1500
+    cnt[0] = cnt[-1] = max(per_row, 1)
+    rows = np.repeat(np.arange(n), cnt)
+    key = np.unique(rows * n + rng.integers(0, n, rows.size))
+    key = np.unique(np.append(key, n * n - 1))   # the last column is read
+    r, c = key // n, key % n
+    rp = np.zeros(n + 1, np.int64)
+    np.cumsum(np.bincount(r, minlength=n), out=rp[1:])
+    return I.CSR(n, rp.astype(np.int32), c.astype(np.int32), rng.uniform(-1, 1, key.size))
+
+
+@pytest.mark.parametrize("n,per_row,long_rows", [(200_003, 40, 30), (262_144, 40, 1), (524_287, 36, 7)])
+def test_staged_segments_match_oracle(cg, n, per_row, long_rows):
+    """Rows of many scattered columns (products on staged column segments:
+    8, 8 and 4 groups of segments on 256 compute units,
+    rows over several slots, empty rows, an odd last column): float64 and
+    float32 products, a block of rows that starts inside the matrix, and
+    integer values, whose sums are exact in any order."""
+    A = scattered(n, per_row, long_rows)
+    x = np.random.default_rng(7).uniform(-1, 1, n)
+    ref = oracle.spmv(A, x)
+    with cg.Solver(A) as s:
+        kind = used_kind(s, n)
+        assert kind in (1, 5)
+        y = host(s.spmv(dev(x)))
+        again = host(s.spmv(dev(x)))
+        off = torch.zeros(n + 1, dtype=torch.float64, device="cuda")[1:]
+        xo = torch.zeros(n + 1, dtype=torch.float64, device="cuda")[1:]
+        xo.copy_(dev(x))
+        shifted = host(s.spmv(xo, off))
+        s.set_opts(precision=cg.PREC_MIXED)
+        y32 = host(s.spmv_f32(torch.from_numpy(x.astype(np.float32)).cuda())).astype(np.float64)
+    assert spmv_err(A, x, y, ref) <= 1e-12
+    assert np.array_equal(y, again) and np.array_equal(y, shifted)
+    # float32 operands summed in float64, one rounding to float32 at the end:
+    # half an ulp of the result, and half an ulp of each rounded operand
+    absA = sp.csr_matrix((np.abs(A.val), A.col, A.row_ptr), shape=(n, n))
+    assert np.all(np.abs(y32 - ref) <= 3.0 * 2.0 ** -24 * (absA @ np.abs(x)) * (1 + 1e-6) + 1e-30)
+    B = I.CSR(n, A.row_ptr, A.col, np.random.default_rng(9).integers(-8, 9, A.nnz).astype(np.float64))
+    xi = np.random.default_rng(8).integers(-8, 9, n).astype(np.float64)
+    refi = oracle.spmv(B, xi)
+    with cg.Solver(B) as s:
+        assert np.array_equal(host(s.spmv(dev(xi))), refi)
+    rb, re = 1001, n - 77
+    with cg.Solver(B, rb, re) as s:
+        s.set_opts(host_threads=2)
+        assert np.array_equal(host(s.spmv(dev(xi))), refi)
+
+
+def test_staged_segments_solve(cg):
+    """CG and mixed precision on staged column segments against the oracle."""
+    A = I.random_spd_lognormal(200_000, 7, mean_degree=20.0)
+    b = I.rhs_of(A, I.uniform_vector(A.n, [31, 1]))
+    ref = oracle.cg(A, b, tol=1e-10, maxit=5000)
+    for prec in (cg.PREC_FP64, cg.PREC_MIXED):
+        with cg.Solver(A) as s:
+            s.set_opts(precision=prec)
+            x, res = s.solve(dev(b), tol=1e-10, maxit=5000)
+        assert res["code"] == cg.CG_OK
+        assert np.linalg.norm(b - oracle.spmv(A, host(x))) <= 1.01e-10 * np.linalg.norm(b)
+        if prec == cg.PREC_FP64:
+            assert abs(res["iterations"] - ref["iterations"]) <= max(2, 0.05 * ref["iterations"])
