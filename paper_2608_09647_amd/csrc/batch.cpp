@@ -30,8 +30,8 @@ struct cg_batch {
     int32_t *d_rp = nullptr, *d_ci = nullptr;
     double *d_val = nullptr;
     double *d_R = nullptr, *d_P = nullptr, *d_Q = nullptr;
-    double *d_part = nullptr;
-    int32_t *d_bar = nullptr, *d_err = nullptr, *d_episodes = nullptr;
+    uint64_t *d_part = nullptr;      // the grid's partial sums, then its barrier words and the error flag
+    int32_t *d_episodes = nullptr;
     int32_t *d_wg_item = nullptr, *d_item_sys = nullptr, *d_item_rank = nullptr;
     int32_t *d_team_first = nullptr, *d_team_size = nullptr;
     int64_t item_cap = 0;       // entries of d_item_sys / d_item_rank
@@ -40,7 +40,7 @@ struct cg_batch {
     BatchOutDev *d_out = nullptr;
     int grid_cap = 0;                // workgroups the buffers are sized for
     // current team assignment
-    int grid = 0;
+    int grid = 0, threads = 0;       // workgroups, threads of each
     std::vector<int32_t> team_size;
 };
 
@@ -48,8 +48,7 @@ namespace {
 
 void batch_free(cg_batch *b) {
     for (void *p : {(void *)b->d_rp, (void *)b->d_ci, (void *)b->d_val, (void *)b->d_R, (void *)b->d_P,
-                    (void *)b->d_Q, (void *)b->d_part, (void *)b->d_bar, (void *)b->d_err,
-                    (void *)b->d_episodes, (void *)b->d_wg_item, (void *)b->d_item_sys, (void *)b->d_item_rank,
+                    (void *)b->d_Q, (void *)b->d_part, (void *)b->d_episodes, (void *)b->d_wg_item, (void *)b->d_item_sys, (void *)b->d_item_rank,
                     (void *)b->d_team_first, (void *)b->d_team_size, (void *)b->d_row_off,
                     (void *)b->d_strip, (void *)b->d_out})
         (void)hipFree(p);
@@ -93,6 +92,25 @@ int lanes_variant(const cg_batch *b, const cg_batch_sched &s) {
     return (s.rhs_per_lane == 1 || (b->nrhs & 1)) ? 1 : 2;
 }
 
+// Words of d_part for a grid: the partial sums, a barrier word per workgroup
+// and the error flag (32 bits each).
+size_t part_words(int grid) { return (size_t)grid * kBatchSlots * 2 * kBatchLanes + ((size_t)grid + 2) / 2; }
+
+// Threads per workgroup: 1024, one workgroup per compute unit, so that teams
+// have few members to wait for and few caches to write back (24 diffusion
+// systems of side 32-256, 16 right-hand sides, us per iteration: 181 against
+// 203 with 256 threads; 3 systems of side <= 64: 22 against 36).  256 where
+// many tiny systems each leave most of 1024 threads idle (2000 systems of
+// 16-100 rows: 87 against 166; 1000 of 100-1600 rows the same, 411 and 410),
+// and where the phases are long against the team waits, which several
+// workgroups per unit then overlap with each other's work (60 systems of side
+// <= 512, 29K rows per unit: 2292 against 2424; 24 such systems, 8.7K rows per
+// unit: 715 against 708).
+int batch_threads(const cg_batch *b) {
+    if (b->nsys > b->cus && b->n_total < 512 * (int64_t)b->nsys) return 256;
+    return b->n_total <= 16384 * (int64_t)b->cus ? 1024 : 256;
+}
+
 // Workgroups per system, with w_k = n_k^exponent as a system's cost: the
 // smallest per-workgroup load L for which the batch fits the grid, where a
 // system heavier than L gets ceil(w_k / L) workgroups of its own (at most one
@@ -102,7 +120,8 @@ int lanes_variant(const cg_batch *b, const cg_batch_sched &s) {
 // with the largest load per workgroup that may still grow.  With few systems
 // every one is heavier than L and has a team of its own.
 int assign_teams(cg_batch *b, const cg_batch_sched &s) {
-    const int occ = batch_blocks_per_cu(s.rows_per_thread, lanes_variant(b, s));
+    b->threads = batch_threads(b);
+    const int occ = batch_blocks_per_cu(b->threads, s.rows_per_thread, lanes_variant(b, s));
     if (occ <= 0) return fail(CG_EDEVICE, "occupancy query of the batched kernel failed");
     int grid = std::min(s.blocks_per_cu, occ) * b->cus;
     grid = std::max(1, std::min(grid, b->grid_cap));
@@ -115,7 +134,7 @@ int assign_teams(cg_batch *b, const cg_batch_sched &s) {
         wgt[k] = std::pow((double)std::max<int64_t>(n, 1), s.team_exponent);
         wsum += wgt[k];
         wmax = std::max(wmax, wgt[k]);
-        int64_t c = std::max<int64_t>(1, n / kBatchRowsPerStep);
+        int64_t c = std::max<int64_t>(1, n / (b->threads / kBatchLanes));
         if (s.max_team > 0) c = std::min<int64_t>(c, s.max_team);
         cap[k] = (int32_t)std::min<int64_t>(c, grid);
     }
@@ -284,7 +303,7 @@ extern "C" int cg_batch_create(int32_t nsys, const int32_t *n, const int64_t *nn
     rp[r] = (int32_t)z;
     int occ = 0;
     for (int u = 1; u <= 2; ++u)
-        for (int v = 1; v <= 2; ++v) occ = std::max(occ, batch_blocks_per_cu(u, v));
+        for (int v = 1; v <= 2; ++v) occ = std::max(occ, batch_blocks_per_cu(batch_threads(b), u, v));
     if (occ <= 0) return bail(fail(CG_EDEVICE, "occupancy query of the batched kernel failed"));
     b->grid_cap = occ * b->cus;
     const size_t vec = (size_t)rows * nrhs;
@@ -294,9 +313,7 @@ extern "C" int cg_batch_create(int32_t nsys, const int32_t *n, const int64_t *nn
     if (e == hipSuccess) e = dmalloc(&b->d_R, vec);
     if (e == hipSuccess) e = dmalloc(&b->d_P, vec);
     if (e == hipSuccess) e = dmalloc(&b->d_Q, vec);
-    if (e == hipSuccess) e = dmalloc(&b->d_part, (size_t)b->grid_cap * kBatchSlots * kBatchLanes);
-    if (e == hipSuccess) e = dmalloc(&b->d_bar, (size_t)nsys);
-    if (e == hipSuccess) e = dmalloc(&b->d_err, 1);
+    if (e == hipSuccess) e = dmalloc(&b->d_part, part_words(b->grid_cap));
     if (e == hipSuccess) e = dmalloc(&b->d_episodes, (size_t)nsys);
     b->item_cap = (int64_t)b->grid_cap + nsys;   // one item per team member plus one per shared system
     if (e == hipSuccess) e = dmalloc(&b->d_wg_item, (size_t)b->grid_cap + 1);
@@ -375,8 +392,7 @@ extern "C" int cg_batch_solve(cg_batch *b, const double *B, double *X, double to
     if (maxit < 0) return fail(CG_EINVAL, "maxit must be >= 0");
     HIP_TRY(hipSetDevice(b->dev));
     hipStream_t st = b->stream;
-    HIP_TRY(hipMemsetAsync(b->d_bar, 0, sizeof(int32_t) * b->nsys, st));
-    HIP_TRY(hipMemsetAsync(b->d_err, 0, sizeof(int32_t), st));
+    HIP_TRY(hipMemsetAsync(b->d_part, 0, sizeof(uint64_t) * part_words(b->grid), st));
     int rate_khz = 0;
     if (hipDeviceGetAttribute(&rate_khz, hipDeviceAttributeWallClockRate, b->dev) != hipSuccess || rate_khz <= 0)
         rate_khz = 100000;
@@ -390,8 +406,8 @@ extern "C" int cg_batch_solve(cg_batch *b, const double *B, double *X, double to
     a.P = b->d_P;
     a.Q = b->d_Q;
     a.part = b->d_part;
-    a.bar = b->d_bar;
-    a.err = b->d_err;
+    a.sync = reinterpret_cast<int32_t *>(b->d_part + (size_t)b->grid * kBatchSlots * 2 * kBatchLanes);
+    a.err = a.sync + b->grid;
     a.wg_item = b->d_wg_item;
     a.item_sys = b->d_item_sys;
     a.item_rank = b->d_item_rank;
@@ -413,7 +429,7 @@ extern "C" int cg_batch_solve(cg_batch *b, const double *B, double *X, double to
     if (V == 2 && ((reinterpret_cast<uintptr_t>(B) | reinterpret_cast<uintptr_t>(X)) & 15)) {
         // unaligned vectors: one right-hand side per lane, if that variant
         // keeps the grid resident
-        if (batch_blocks_per_cu(b->sched.rows_per_thread, 1) * b->cus < b->grid) {
+        if (batch_blocks_per_cu(b->threads, b->sched.rows_per_thread, 1) * b->cus < b->grid) {
             (void)hipEventDestroy(e0);
             (void)hipEventDestroy(e1);
             return fail(CG_EINVAL, "B and X must be 16-byte aligned for this schedule");
@@ -422,7 +438,7 @@ extern "C" int cg_batch_solve(cg_batch *b, const double *B, double *X, double to
     }
     // the grid is within the kernel's occupancy (assign_teams), so every
     // workgroup is resident at once in either launch form
-    const hipError_t le = launch_batch_cg(a, b->grid, b->sched.rows_per_thread, V,
+    const hipError_t le = launch_batch_cg(a, b->grid, b->threads, b->sched.rows_per_thread, V,
                                           b->sched.launch == CG_BATCH_LAUNCH_COOPERATIVE, st);
     if (le != hipSuccess) {
         (void)hipEventDestroy(e0);
@@ -436,7 +452,7 @@ extern "C" int cg_batch_solve(cg_batch *b, const double *B, double *X, double to
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     int32_t err = 0;
-    HIP_TRY(hipMemcpy(&err, b->d_err, sizeof(int32_t), hipMemcpyDeviceToHost));
+    HIP_TRY(hipMemcpy(&err, a.err, sizeof(int32_t), hipMemcpyDeviceToHost));
     if (err) return fail(CG_EDEVICE, "a team barrier timed out; the launch was abandoned");
     std::vector<BatchOutDev> o((size_t)b->nsys * b->nrhs);
     std::vector<int32_t> ep(b->nsys);

@@ -6,9 +6,7 @@
 
 namespace cgmi {
 
-constexpr int kBatchThreads = 256;                  // threads per workgroup
 constexpr int kBatchLanes = 16;                     // lanes per row: one per right-hand side
-constexpr int kBatchRowsPerStep = kBatchThreads / kBatchLanes;
 constexpr int kBatchSlots = 4;                      // partial sums per workgroup: p^T q, r^T r, b^T b, true r^T r
 
 struct BatchOutDev {
@@ -25,9 +23,9 @@ struct BatchArgs {
     const double *val;
     const double *B;            // n_total x nrhs, right-hand sides fastest
     double *X, *R, *P, *Q;
-    double *part;               // [grid][kBatchSlots][kBatchLanes] partial sums
-    int32_t *bar;               // [nsys] team barrier counters (0 at launch)
-    int32_t *err;               // [1] set when a team wait times out
+    uint64_t *part;             // [grid][kBatchSlots][2][kBatchLanes] tagged halves of the partial sums (0 at launch)
+    int32_t *sync;              // [grid] last team barrier each workgroup has arrived at (0 at launch)
+    int32_t *err;               // [1] set when a team wait times out (0 at launch)
     const int32_t *wg_item;     // [grid + 1] the workgroup's items are wg_item[w] .. wg_item[w+1]-1
     const int32_t *item_sys;    // [items] system of an item
     const int32_t *item_rank;   // [items] rank of the workgroup in that system's team
@@ -44,12 +42,12 @@ struct BatchArgs {
 };
 
 // Occupancy of the persistent kernel (workgroups per compute unit) for a
-// variant: rows a thread advances per step (1, 2), right-hand sides per lane
+// variant: threads per workgroup (256, 1024), rows a thread advances per step (1, 2), right-hand sides per lane
 // (1; 2 needs an even nrhs and 16-byte aligned vectors).
-int batch_blocks_per_cu(int rows_per_thread, int rhs_per_lane);
+int batch_blocks_per_cu(int threads, int rows_per_thread, int rhs_per_lane);
 // Launch of the persistent kernel over `grid` workgroups: cooperative, or
 // ordinary (cooperative = 0) for a grid already checked to be resident.
-hipError_t launch_batch_cg(const BatchArgs &a, int grid, int rows_per_thread, int rhs_per_lane, int cooperative,
-                           hipStream_t s);
+hipError_t launch_batch_cg(const BatchArgs &a, int grid, int threads, int rows_per_thread, int rhs_per_lane,
+                           int cooperative, hipStream_t s);
 
 }  // namespace cgmi

@@ -24,14 +24,14 @@
 // the same p, so the x update is done there and B does not read p.
 // Every workgroup of a team sums the team's partials itself in a fixed order,
 // so all of them take identical decisions (and results are reproducible for
-// a fixed schedule).  A barrier is a counter in device memory: every wave
-// makes its stores visible device-wide (device-scope release fence), the
-// workgroup synchronises, one thread adds 1 to the team's counter and waits
-// until the team's count is reached, and device-scope acquire fences (the
-// waiting thread's, then every wave's after a second workgroup barrier)
-// drop stale cache lines before the workgroup reads what the team wrote.  A
-// wait is bounded by a wall-clock limit; on expiry the error flag ends every
-// team.
+// a fixed schedule).  Of the three barriers only the one after C has to move
+// vectors between workgroups (the p that A gathers); the other two exchange
+// partial sums alone, in words that carry their own validity (publish), and
+// leave every cache as it is.  With a cache write-back and invalidation by
+// every wave at all three, and 256 threads to a workgroup, an iteration of 24
+// diffusion systems of side 32-256 with 16 right-hand sides took 607 us, 330 of
+// them in the barriers; so, and with 1024 threads, it takes 181 us.  Waits are
+// bounded by a wall-clock limit; on expiry the error flag ends every team.
 #include <hip/hip_runtime.h>
 #include <math.h>
 
@@ -41,16 +41,14 @@ namespace cgmi {
 
 namespace {
 
-constexpr int kT = kBatchThreads;
 constexpr int kL = kBatchLanes;
-constexpr int kRS = kBatchRowsPerStep;
-constexpr int kWaves = kT / 64;
 enum { kSlotPQ = 0, kSlotRR = 1, kSlotBB = 2, kSlotTrue = 3 };
 enum { kStOk = 0, kStMaxit = 1, kStBreakdown = -4 };
 
+template <int NT>
 struct Shared {
-    double red[kWaves][kL];
-    double tmp[kT];
+    double red[NT / 64][kL];
+    double tmp[NT];
     double sum[kL];
     double rho[kL], bb[kL], alpha[kL], beta[kL], rr_last[kL];
     int active[kL], status[kL], iter[kL], zero_b[kL];
@@ -59,11 +57,11 @@ struct Shared {
     int ok;
 };
 
-// Partial sum over the workgroup for each right-hand side: a lane holds V
-// consecutive right-hand sides j0 .. j0+V-1 (acc[v] for j0 + v); lanes with
-// the same j0 are 16/V apart.  Stored at dst[0..15] by threads 0..15.
-template <int V>
-__device__ __forceinline__ void wg_partial(const double (&acc)[V], double *dst, Shared &S) {
+// Sum over the workgroup for each right-hand side: a lane holds V consecutive
+// right-hand sides j0 .. j0+V-1 (acc[v] for j0 + v); lanes with the same j0
+// are 16/V apart.  The sums are returned to threads 0 .. 15.
+template <int NT, int V>
+__device__ __forceinline__ double wg_partial(const double (&acc)[V], Shared<NT> &S) {
     constexpr int LPR = kL / V;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     double v[V];
@@ -77,75 +75,135 @@ __device__ __forceinline__ void wg_partial(const double (&acc)[V], double *dst, 
 #pragma unroll
         for (int q = 0; q < V; ++q) S.red[wv][lane * V + q] = v[q];
     __syncthreads();
+    double s = 0.0;
     if (threadIdx.x < kL) {
-        double s = S.red[0][threadIdx.x];
+        s = S.red[0][threadIdx.x];
 #pragma unroll
-        for (int q = 1; q < kWaves; ++q) s += S.red[q][threadIdx.x];
-        dst[threadIdx.x] = s;
+        for (int q = 1; q < NT / 64; ++q) s += S.red[q][threadIdx.x];
     }
-    __syncthreads();   // S.red is reused by the next call
+    return s;
 }
 
-// Team sum of one slot for every j, in a fixed order, into S.sum.
-__device__ __forceinline__ void team_sum(const BatchArgs &a, int first, int T, int slot, Shared &S) {
-    const int j = threadIdx.x & (kL - 1), g = threadIdx.x >> 4;
+// One step of a bounded wait: false when the launch is being abandoned (the
+// error flag is set, or the wait that began at t0 exceeds its limit).
+__device__ __forceinline__ bool wait_on(const BatchArgs &a, uint64_t t0) {
+    if (__hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) return false;
+    if ((int64_t)(wall_clock64() - t0) > a.timeout_ticks) {
+        __hip_atomic_store(a.err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return false;
+    }
+    __builtin_amdgcn_s_sleep(1);
+    return true;
+}
+
+__device__ __forceinline__ uint64_t *part_words(const BatchArgs &a, int wg, int slot) {
+    return a.part + ((int64_t)wg * kBatchSlots + slot) * 2 * kL;
+}
+
+// Publishes the workgroup's sums of a slot (value v of threads 0 .. 15) for
+// the team, tagged with the episode (> 0, higher in every use of the slot):
+// two relaxed 64-bit words, each half of the value's bits beside the tag.  A
+// reader takes a word for the episode it waits for only with that tag, so
+// neither side needs an ordering between different words: no fence, no
+// counter, one trip through memory instead of two.
+__device__ __forceinline__ void publish(const BatchArgs &a, int slot, int episode, double v) {
+    if (threadIdx.x >= kL) return;
+    uint64_t *const w = part_words(a, blockIdx.x, slot) + threadIdx.x;
+    const uint64_t bits = (uint64_t)__double_as_longlong(v), tag = (uint64_t)(uint32_t)episode << 32;
+    __hip_atomic_store(w, tag | (bits & 0xFFFFFFFFu), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(w + kL, tag | bits >> 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Team sum of one slot for every j, in a fixed order, into S.sum: waits for
+// the words of every member (first .. first + T - 1) with the episode's tag.
+// A slot is written again only after its writer has seen every member's words
+// of a later episode of another slot, hence after every member has read it.
+// False when the launch is being abandoned.
+template <int NT>
+__device__ __forceinline__ bool team_sum(const BatchArgs &a, int first, int T, int slot, int episode, double mine,
+                                         Shared<NT> &S) {
+    if (T == 1) {
+        if (threadIdx.x < kL) S.sum[threadIdx.x] = mine;
+        __syncthreads();
+        return true;
+    }
+    publish(a, slot, episode, mine);
+    const int j = threadIdx.x & (kL - 1), g = threadIdx.x / kL;
     double v = 0.0;
-    for (int r = g; r < T; r += kT / kL)
-        v += a.part[((int64_t)(first + r) * kBatchSlots + slot) * kL + j];
+    bool ok = true;
+    if (g < T) {
+        const uint64_t t0 = wall_clock64();
+        for (int r = g; r < T && ok; r += NT / kL) {
+            const uint64_t *const w = part_words(a, first + r, slot) + j;
+            uint64_t lo, hi;
+            for (;;) {
+                lo = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                hi = __hip_atomic_load(w + kL, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if ((uint32_t)(lo >> 32) == (uint32_t)episode && (uint32_t)(hi >> 32) == (uint32_t)episode) break;
+                if (!wait_on(a, t0)) {
+                    ok = false;
+                    break;
+                }
+            }
+            v += __longlong_as_double((long long)(hi << 32 | (lo & 0xFFFFFFFFu)));
+        }
+    }
+    if (!ok) S.ok = 0;
     S.tmp[threadIdx.x] = v;
     __syncthreads();
     if (threadIdx.x < kL) {
         double s = 0.0;
-        for (int q = 0; q < kT / kL; ++q) s += S.tmp[q * kL + threadIdx.x];
+        const int groups = min(T, NT / kL);
+        for (int q = 0; q < groups; ++q) s += S.tmp[q * kL + threadIdx.x];
         S.sum[threadIdx.x] = s;
     }
     __syncthreads();
+    return S.ok != 0;
 }
 
-// Barrier of the team of system `sys` (T workgroups).  Returns false when the
-// launch is being abandoned (time limit or error flag).
+// Barrier of a team (T workgroups) that makes the vectors its members wrote
+// visible to all of them.  Returns false when the launch is being abandoned.
 //
-// Memory model: team members sit on different XCDs, whose L2 caches are not
-// coherent with each other, so what one workgroup writes must be released at
-// agent scope before the counter moves and acquired at agent scope before
-// another workgroup reads it.  Every wave issues its own agent-scope release
-// fence (its stores are written back past its XCD's L2 and complete before
-// the fence returns) before the workgroup barrier, so the one thread that
-// moves the counter does so after every wave's release; after the counter
-// reaches the team's count, thread 0 issues an agent-scope acquire fence and,
-// past the second workgroup barrier, every wave issues its own, so each
-// wave's following loads come after its own invalidation of stale lines.
-__device__ __forceinline__ bool team_sync(const BatchArgs &a, int sys, int T, int &episode,
-                                          Shared &S) {
-    ++episode;
+// Team members sit on different XCDs, whose L2 caches are not coherent with
+// each other: what a member wrote has to leave its XCD's L2 before another
+// reads it, and the reader's XCD has to drop what it holds of it.  Both act on
+// a whole L2, so one wave of each workgroup does them for the workgroup; their
+// cost grows with the number of waves that do (every wave of 768 workgroups
+// of 4: 111 us per barrier).  Every wave waits until its stores have reached
+// the L2 (the wait is spelled out: a workgroup barrier alone orders the waves
+// of a workgroup, which share a CU's L1, and need not wait for the L2), the
+// workgroup synchronises, and wave 0's agent-scope release fence writes the L2
+// back before its first thread marks the episode in the workgroup's word.  The
+// waves that wait for the members' words then issue the agent-scope acquire
+// fence, wait for it, and the second workgroup barrier lets the others read
+// through the L1 and L2 they have invalidated.
+template <int NT>
+__device__ __forceinline__ bool team_sync(const BatchArgs &a, int first, int T, int episode, Shared<NT> &S) {
     if (T == 1) {
         __syncthreads();
         return true;
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    if (threadIdx.x == 0) {
-        int ok = 1;
-        __hip_atomic_fetch_add(&a.bar[sys], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const int target = episode * T;
+    if (threadIdx.x < 64) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+        if (threadIdx.x == 0)
+            __hip_atomic_store(a.sync + blockIdx.x, episode, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if ((int)(threadIdx.x & ~63u) < T) {   // the waves with a member to wait for
+        bool ok = true;
         const uint64_t t0 = wall_clock64();
-        while (__hip_atomic_load(&a.bar[sys], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
-            if (__hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
-                ok = 0;
-                break;
-            }
-            if ((int64_t)(wall_clock64() - t0) > a.timeout_ticks) {
-                __hip_atomic_store(a.err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                ok = 0;
-                break;
-            }
-            __builtin_amdgcn_s_sleep(2);
-        }
+        for (int r = threadIdx.x; r < T && ok; r += NT)
+            while (__hip_atomic_load(a.sync + first + r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < episode)
+                if (!wait_on(a, t0)) {
+                    ok = false;
+                    break;
+                }
+        if (!ok) S.ok = 0;
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        S.ok = ok;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     }
     __syncthreads();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     return S.ok != 0;
 }
 
@@ -404,19 +462,17 @@ __device__ __forceinline__ void spmv_rows_strips(const BatchArgs &a, int64_t off
 // One system's solve by this workgroup as member `rank` of its team (the
 // whole solve when the team is the workgroup alone).  False when the launch
 // is being abandoned (a team wait gave up).
-template <int U, int V>
-__device__ __forceinline__ bool batch_solve_one(const BatchArgs &a, int sys, int rank, Shared &S) {
+template <int NT, int U, int V>
+__device__ __forceinline__ bool batch_solve_one(const BatchArgs &a, int sys, int rank, Shared<NT> &S) {
     constexpr int LPR = kL / V;          // lanes per row
-    constexpr int RS = kT / LPR;         // rows per workgroup step
-    const int w = blockIdx.x;
+    constexpr int RS = NT / LPR;         // rows per workgroup step
     const int T = a.team_size[sys], first = a.team_first[sys];
     const int64_t off = a.row_off[sys], n = a.row_off[sys + 1] - off;
     const int64_t lo = off + n * rank / T, hi = off + n * (rank + 1) / T;
     const int nr = a.nrhs;
     const int j0 = (threadIdx.x % LPR) * V, rsub = threadIdx.x / LPR;
     const bool lane_on = j0 < nr;
-    double *mypart = a.part + (int64_t)w * kBatchSlots * kL;
-    int episode = 0;
+    int episode = 1;
 
     // setup: r = b - A x, p = r; partial r^T r and b^T b
     {
@@ -443,14 +499,13 @@ __device__ __forceinline__ bool batch_solve_one(const BatchArgs &a, int sys, int
                         stv<V>(a.P, idx, rv);
                     }
                 }
-        wg_partial<V>(arr, mypart + kSlotRR * kL, S);
-        wg_partial<V>(abb, mypart + kSlotBB * kL, S);
+        const double rr = wg_partial<NT, V>(arr, S);
+        if (!team_sync<NT>(a, first, T, episode, S)) return false;
+        if (!team_sum<NT>(a, first, T, kSlotRR, episode, rr, S)) return false;
+        if (threadIdx.x < kL) S.rr_last[threadIdx.x] = S.sum[threadIdx.x];
+        const double bb = wg_partial<NT, V>(abb, S);
+        if (!team_sum<NT>(a, first, T, kSlotBB, episode, bb, S)) return false;
     }
-    if (!team_sync(a, sys, T, episode, S)) return false;
-    team_sum(a, first, T, kSlotRR, S);
-    if (threadIdx.x < kL) S.rr_last[threadIdx.x] = S.sum[threadIdx.x];
-    __syncthreads();
-    team_sum(a, first, T, kSlotBB, S);
     if (threadIdx.x < kL) {
         const int t = threadIdx.x;
         const double rr = S.rr_last[t], bb = S.sum[t];
@@ -495,10 +550,9 @@ __device__ __forceinline__ bool batch_solve_one(const BatchArgs &a, int sys, int
                 else
                     spmv_rows_pipelined<V>(a, lo, hi, RS, rsub, nr, j0, on, acc);
             }
-            wg_partial<V>(acc, mypart + kSlotPQ * kL, S);
+            const double pq = wg_partial<NT, V>(acc, S);
+            if (!team_sum<NT>(a, first, T, kSlotPQ, ++episode, pq, S)) return false;
         }
-        if (!team_sync(a, sys, T, episode, S)) return false;
-        team_sum(a, first, T, kSlotPQ, S);
         if (threadIdx.x < kL) {
             const int t = threadIdx.x;
             S.alpha[t] = 0.0;
@@ -548,10 +602,9 @@ __device__ __forceinline__ bool batch_solve_one(const BatchArgs &a, int sys, int
                             stv<V>(a.R, idx, rv);
                         }
                     }
-            wg_partial<V>(acc, mypart + kSlotRR * kL, S);
+            const double rr = wg_partial<NT, V>(acc, S);
+            if (!team_sum<NT>(a, first, T, kSlotRR, ++episode, rr, S)) return false;
         }
-        if (!team_sync(a, sys, T, episode, S)) return false;
-        team_sum(a, first, T, kSlotRR, S);
         if (threadIdx.x < kL) {
             const int t = threadIdx.x;
             S.beta[t] = 0.0;
@@ -618,7 +671,7 @@ __device__ __forceinline__ bool batch_solve_one(const BatchArgs &a, int sys, int
                     }
         }
         if (!S.any) break;       // the x updates above reach the team at the next barrier
-        if (!team_sync(a, sys, T, episode, S)) return false;
+        if (!team_sync<NT>(a, first, T, ++episode, S)) return false;
     }
 
     // b = 0: the solution is x = 0
@@ -627,7 +680,7 @@ __device__ __forceinline__ bool batch_solve_one(const BatchArgs &a, int sys, int
 #pragma unroll
             for (int q = 0; q < V; ++q)
                 if (S.zero_b[j0 + q]) a.X[row * nr + j0 + q] = 0.0;
-    if (!team_sync(a, sys, T, episode, S)) return false;
+    if (!team_sync<NT>(a, first, T, ++episode, S)) return false;
     // true residual ||b - A x||^2
     {
         double acc[V];
@@ -645,10 +698,9 @@ __device__ __forceinline__ bool batch_solve_one(const BatchArgs &a, int sys, int
                     acc[q] = fma(rv, rv, acc[q]);
                 }
             }
-        wg_partial<V>(acc, mypart + kSlotTrue * kL, S);
+        const double tr = wg_partial<NT, V>(acc, S);
+        if (!team_sum<NT>(a, first, T, kSlotTrue, ++episode, tr, S)) return false;
     }
-    if (!team_sync(a, sys, T, episode, S)) return false;
-    team_sum(a, first, T, kSlotTrue, S);
     if (rank == 0) {
         if (threadIdx.x < nr) {
             const int t = threadIdx.x;
@@ -669,48 +721,54 @@ __device__ __forceinline__ bool batch_solve_one(const BatchArgs &a, int sys, int
 // team of several workgroups has one, a workgroup hosting small systems
 // (teams of one) several, so their rows share workgroups instead of each
 // taking one.
-template <int U, int V>
-__global__ __launch_bounds__(kT) void k_batch_cg(BatchArgs a) {
-    __shared__ Shared S;
+template <int NT, int U, int V>
+__global__ __launch_bounds__(NT) void k_batch_cg(BatchArgs a) {
+    __shared__ Shared<NT> S;
+    if (threadIdx.x == 0) S.ok = 1;
     const int i0 = __builtin_amdgcn_readfirstlane(a.wg_item[blockIdx.x]);
     const int i1 = __builtin_amdgcn_readfirstlane(a.wg_item[blockIdx.x + 1]);
     for (int it = i0; it < i1; ++it) {
         const int sys = __builtin_amdgcn_readfirstlane(a.item_sys[it]);
         const int rank = __builtin_amdgcn_readfirstlane(a.item_rank[it]);
-        if (!batch_solve_one<U, V>(a, sys, rank, S)) return;
+        if (!batch_solve_one<NT, U, V>(a, sys, rank, S)) return;
         __syncthreads();   // S is set up afresh by the next system
     }
 }
 
-template <int U, int V>
-int occupancy_of() {
-    int nb = 0;
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_batch_cg<U, V>, kT, 0) == hipSuccess ? nb : 0;
+const void *kernel_of(int threads, int rows_per_thread, int rhs_per_lane) {
+#define CGMI_BATCH(NT, U, V)                                             \
+    if (threads == NT && rows_per_thread == U && rhs_per_lane == V) return reinterpret_cast<const void *>(k_batch_cg<NT, U, V>)
+    CGMI_BATCH(256, 1, 1);
+    CGMI_BATCH(256, 1, 2);
+    CGMI_BATCH(256, 2, 1);
+    CGMI_BATCH(256, 2, 2);
+    CGMI_BATCH(1024, 1, 1);
+    CGMI_BATCH(1024, 1, 2);
+    CGMI_BATCH(1024, 2, 1);
+    CGMI_BATCH(1024, 2, 2);
+#undef CGMI_BATCH
+    return nullptr;
 }
 
 }  // namespace
 
-int batch_blocks_per_cu(int rows_per_thread, int rhs_per_lane) {
-    if (rhs_per_lane == 2) return rows_per_thread == 2 ? occupancy_of<2, 2>() : occupancy_of<1, 2>();
-    return rows_per_thread == 2 ? occupancy_of<2, 1>() : occupancy_of<1, 1>();
+int batch_blocks_per_cu(int threads, int rows_per_thread, int rhs_per_lane) {
+    int nb = 0;
+    const void *fn = kernel_of(threads, rows_per_thread, rhs_per_lane);
+    return fn && hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fn, threads, 0) == hipSuccess ? nb : 0;
 }
 
-hipError_t launch_batch_cg(const BatchArgs &a, int grid, int rows_per_thread, int rhs_per_lane, int cooperative,
-                          hipStream_t s) {
+hipError_t launch_batch_cg(const BatchArgs &a, int grid, int threads, int rows_per_thread, int rhs_per_lane,
+                          int cooperative, hipStream_t s) {
     if (grid <= 0) return hipSuccess;
     BatchArgs args = a;
     void *params[] = {&args};
-    const void *fn;
-    if (rhs_per_lane == 2)
-        fn = rows_per_thread == 2 ? reinterpret_cast<const void *>(k_batch_cg<2, 2>)
-                                  : reinterpret_cast<const void *>(k_batch_cg<1, 2>);
-    else
-        fn = rows_per_thread == 2 ? reinterpret_cast<const void *>(k_batch_cg<2, 1>)
-                                  : reinterpret_cast<const void *>(k_batch_cg<1, 1>);
-    if (cooperative) return hipLaunchCooperativeKernel(fn, dim3(grid), dim3(kT), params, 0, s);
+    const void *fn = kernel_of(threads, rows_per_thread, rhs_per_lane);
+    if (!fn) return hipErrorInvalidValue;
+    if (cooperative) return hipLaunchCooperativeKernel(fn, dim3(grid), dim3(threads), params, 0, s);
     // ordinary launch of a grid the caller has checked to be resident (the
     // team waits give up after their time limit if it were not)
-    return hipLaunchKernel(fn, dim3(grid), dim3(kT), params, 0, s);
+    return hipLaunchKernel(fn, dim3(grid), dim3(threads), params, 0, s);
 }
 
 }  // namespace cgmi

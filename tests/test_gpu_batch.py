@@ -214,6 +214,31 @@ def test_fixed_work_matches_oracle_iterates(cg):
             assert np.linalg.norm(X[k][:, j] - ref["x"]) <= 1e-9 * np.linalg.norm(ref["x"])
 
 
+@pytest.mark.parametrize("shapes, nrhs", [
+    ([(130, 131)], 3),                          # one team of all workgroups, over 64 members
+    ([(72, 71), (9, 7)], 16),                   # 64 members or so beside a workgroup of its own
+    ([(5 + k % 7, 9) for k in range(300)], 2),  # more systems than compute units, all tiny
+    ([(400, 129), (128, 300)], 5),              # rows and vectors past what stays on chip
+])
+def test_team_sizes_match_oracle_iterates(cg, shapes, nrhs):
+    """Fixed work on Poisson systems, from teams of one workgroup to one team
+    of the whole grid: as test_fixed_work_matches_oracle_iterates, and the
+    same bits from a second run."""
+    systems = [I.poisson2d(*s) for s in shapes]
+    xs, bs = make_batch(systems, nrhs, seed=11)
+    X, res, st, code = run_batch(cg, systems, bs, nrhs, tol=0.0, maxit=15)
+    X2, _, _, _ = run_batch(cg, systems, bs, nrhs, tol=0.0, maxit=15)
+    assert code == cg.CG_MAXIT and np.all(res["iterations"] == 15)
+    if len(systems) == 1:
+        assert st["max_team"] > 64
+    for k in range(len(systems)):
+        assert np.array_equal(X[k], X2[k])
+    for k in list(range(len(systems)))[:4]:
+        for j in range(nrhs):
+            ref = oracle.cg(systems[k], bs[k][:, j], tol=0.0, maxit=15)
+            assert np.linalg.norm(X[k][:, j] - ref["x"]) <= 1e-9 * np.linalg.norm(ref["x"]), (k, j)
+
+
 def test_long_rows_match_oracle(cg):
     """Rows longer than the row width phase A keeps in flight (7-point
     stencil rows of 7 entries, random SPD rows of tens to hundreds) take its
