@@ -97,7 +97,12 @@ typedef struct cg_opts {
                               brackets the one launch of the whole solve
                               (n_spmv = 1); 0: off                               */
     int32_t small_path;    /* 1 (default): systems that fit one workgroup's LDS
-                              run the whole solve in one single-workgroup kernel */
+                              run the whole solve in one single-workgroup
+                              kernel; larger ones of rows of at most 7 entries
+                              and at most 1024 rows per compute unit in one
+                              cooperative launch, where the tiling, grid and
+                              fusion options below and profile are left
+                              automatic or off; 0: always several kernels  */
     int32_t spmv_grid;     /* workgroups of the SpMV kernels (0: automatic)      */
     int32_t spmv_kind;     /* SpMV tiling: 0 automatic, 1 vector CSR row-length
                               bins (L lanes per row), 2 stream tiles (runs of

@@ -645,6 +645,40 @@ int plain_fused_loop(cg_handle *h, const PlainWork &w, double *const pbuf[2], in
     return CG_OK;
 }
 
+// Longest row of A (found once per handle).
+int32_t max_row_len(cg_handle *h) {
+    if (h->max_row_len < 0) {
+        int32_t L = 0;
+        for (int32_t i = 0; i < h->n; ++i) L = std::max(L, h->A.h_rp[i + 1] - h->A.h_rp[i]);
+        h->max_row_len = L;
+    }
+    return h->max_row_len;
+}
+
+// The result of a solve that ran in one launch, from the state it left.
+int one_launch_result(const DevState &s, double t_gpu, cg_result *res) {
+    const int status = status_of(s.done);
+    if (res) {
+        res->status = status;
+        res->iterations = s.iter;
+        res->converged = status == CG_OK;
+        res->rel_res_recur = s.bb > 0.0 ? std::sqrt(s.rr) / std::sqrt(s.bb) : 0.0;
+        res->rel_res_true = s.bb > 0.0 ? std::sqrt(s.rr_true) / std::sqrt(s.bb) : 0.0;
+        res->t_gpu = t_gpu;
+    }
+    return status;
+}
+
+// Whether the automatic choices may take the one launch with a row per
+// thread: the options that name a multi-kernel solve's parts leave them.
+bool resident_wanted(cg_handle *h, const PlainWork &w) {
+    const cg_opts &o = h->opts;
+    if (!o.small_path || o.precision != CG_PREC_FP64 || o.precond != CG_PC_NONE || h->shared_p()) return false;
+    if (o.profile || o.spmv_kind || o.spmv_grid || o.spmv_colblock || o.fuse_dir != CG_FUSE_AUTO) return false;
+    // rows first: the longest one takes a pass over the matrix
+    return resident_groups(h->n, 0, h->cus) > 0 && resident_groups(h->n, max_row_len(h), h->cus) > 0;
+}
+
 int solve_plain(cg_handle *h, const PlainWork &w, const double *b, double *x, double tol, int32_t maxit,
                 cg_result *res) {
     const int32_t n = h->n;
@@ -655,11 +689,6 @@ int solve_plain(cg_handle *h, const PlainWork &w, const double *b, double *x, do
     if (small) {
         // one launch: x0 read from x, the solution and the true residual
         // written by the kernel, one read-back of the state
-        if (h->max_row_len < 0) {
-            int32_t L = 0;
-            for (int32_t i = 0; i < n; ++i) L = std::max(L, h->A.h_rp[i + 1] - h->A.h_rp[i]);
-            h->max_row_len = L;
-        }
         // cg_opts.profile: an event pair around the one launch
         struct EventPair {
             hipEvent_t a = nullptr, b = nullptr;
@@ -673,27 +702,47 @@ int solve_plain(cg_handle *h, const PlainWork &w, const double *b, double *x, do
         const double t0 = now();
         if (timed) HIP_TRY(hipEventRecord(evp.a, st));
         HIP_TRY(launch_cg_small(n, h->A.d_rp, h->A.d_ci, h->A.d_val, b, x, tol, maxit, w.state,
-                                h->max_row_len, st));
+                                max_row_len(h), st));
         if (timed) HIP_TRY(hipEventRecord(evp.b, st));
         const int rc = work_state_read(h, w);
         if (rc) return rc;
-        const DevState &s = *w.h_state;
-        const int status = status_of(s.done);
-        if (res) {
-            res->status = status;
-            res->iterations = s.iter;
-            res->converged = status == CG_OK;
-            res->rel_res_recur = s.bb > 0.0 ? std::sqrt(s.rr) / std::sqrt(s.bb) : 0.0;
-            res->rel_res_true = s.bb > 0.0 ? std::sqrt(s.rr_true) / std::sqrt(s.bb) : 0.0;
-            res->t_gpu = now() - t0;
-            if (timed) {
-                float ms = 0.0f;
-                HIP_TRY(hipEventElapsedTime(&ms, evp.a, evp.b));
-                res->t_spmv = 1e-3 * ms;
-                res->n_spmv = 1;
-            }
+        const int status = one_launch_result(*w.h_state, now() - t0, res);
+        if (res && timed) {
+            float ms = 0.0f;
+            HIP_TRY(hipEventElapsedTime(&ms, evp.a, evp.b));
+            res->t_spmv = 1e-3 * ms;
+            res->n_spmv = 1;
         }
         return status;
+    }
+    if (resident_wanted(h, w)) {
+        const int groups = resident_groups(n, max_row_len(h), h->cus);
+        ResidentArgs a{};
+        a.n = n;
+        a.rp = h->A.d_rp;
+        a.ci = h->A.d_ci;
+        a.val = h->A.d_val;
+        a.b = b;
+        a.x = x;
+        a.r = w.r;
+        a.words = reinterpret_cast<uint64_t *>(w.q);
+        a.err = reinterpret_cast<int32_t *>(a.words + resident_words(groups) - 1);
+        a.st = w.state;
+        a.tol = tol;
+        a.maxit = maxit;
+        int rate_khz = 0;
+        if (hipDeviceGetAttribute(&rate_khz, hipDeviceAttributeWallClockRate, h->dev) != hipSuccess || rate_khz <= 0)
+            rate_khz = 100000;
+        a.timeout_ticks = (int64_t)rate_khz * 1000 * 20;   // 20 s
+        const double t0 = now();
+        HIP_TRY(hipMemsetAsync(a.words, 0, sizeof(uint64_t) * resident_words(groups), st));
+        if (launch_cg_resident(a, h->max_row_len, h->cus, st) == hipSuccess) {
+            const int rc = work_state_read(h, w);
+            if (rc) return rc;
+            if (w.h_state->done == kDoneRunning) return fail(CG_EDEVICE, "a wait of the one-launch solve timed out");
+            return one_launch_result(*w.h_state, now() - t0, res);
+        }
+        (void)hipGetLastError();   // not launchable here: the kernels below
     }
     HIP_TRY(hipMemcpyAsync(w.x, x, sizeof(double) * n, hipMemcpyDeviceToDevice, st));
     int rc = work_state_init(h, w, tol, maxit);

@@ -340,6 +340,33 @@ hipError_t launch_cg_small(int32_t n, const int32_t *rp, const int32_t *ci, cons
                            const double *b, double *x, double tol, int32_t maxit, DevState *st,
                            int32_t max_row_len, hipStream_t s);
 
+// Whole solve in one cooperative launch with a row per thread
+// (kernels_resident.hip).  Limits: a workgroup of 1024 threads per compute
+// unit, and the row lengths whose entries and copies of p fit 128 registers
+// (8 entries spilled).
+constexpr int kResidentMaxGroups = 256;   // workgroups at most
+constexpr int kResidentMaxRow = 7;        // entries of a row at most
+constexpr int kResidentCopies = 8;        // copies of an exchanged sum, each read by its share of the workgroups
+struct ResidentArgs {
+    int32_t n;
+    const int32_t *rp, *ci;
+    const double *val;
+    const double *b;
+    double *x;                // x0, then the solution
+    double *r;                // [n] the residual the workgroups exchange
+    uint64_t *words;          // [resident_words(groups)] (0 at launch); the error flag last
+    int32_t *err;             // the error flag: set when a wait times out
+    DevState *st;             // done stays kDoneRunning when the launch was abandoned
+    double tol;
+    int32_t maxit;
+    int64_t timeout_ticks;    // wall-clock ticks a wait may take
+};
+// 64-bit words of the exchanged sums and the error flag behind them.
+constexpr inline size_t resident_words(int groups) { return 4 * kResidentCopies * (size_t)groups + 1; }
+// Workgroups of the launch; 0: the system does not fit it (rows, row length).
+int resident_groups(int32_t n, int32_t max_row_len, int cus);
+hipError_t launch_cg_resident(const ResidentArgs &a, int32_t max_row_len, int cus, hipStream_t s);
+
 // Gather / scatter of p entries for the halo exchange.
 hipError_t launch_gather(int32_t cnt, const int32_t *idx, const double *src, double *dst,
                          hipStream_t s);

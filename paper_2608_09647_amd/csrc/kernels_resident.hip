@@ -1,0 +1,307 @@
+// kernels_resident.hip -- the whole of Algorithm 1 in one cooperative launch
+// for systems above one workgroup's size whose rows fit the GPU's threads, one
+// each (gfx950).
+//
+// With two kernels per iteration such a system spends most of an iteration
+// between kernels: launches, and a first and last wave of loads that nothing
+// overlaps (us per iteration, two kernels and here: 4200 rows of 5 entries 9.7
+// and 4.5, 20K 9.3 and 4.6, 62K 9.4 and 4.8, 262K 12.5 and 6.5; of 7 entries,
+// 32K rows 9.6 and 5.3, 262K 12.7 and 7.0).  What remains is two trips of the
+// sums through memory, 1.5 to 2.5 us each, and one of r.  Here thread t of workgroup w owns row w NT + t for the whole
+// solve and keeps its entries, x, r, p and q in registers, p also in LDS for
+// its workgroup.  What crosses workgroups is the residual, written through to
+// memory by its owner, and the partial sums.  A thread keeps its own copy of p
+// for every column of another workgroup and advances it as the owner does,
+// p = r + beta p, from the r it reads there, so p itself is never exchanged
+// and an iteration has two waits: for the sum p^T q, and for r^T r, behind
+// which every r is visible.
+//
+// Partial sums travel in 64-bit words that carry half of a value beside the
+// number of the sum, so a reader knows a word as the one it waits for without
+// any ordering between words, and no cache is written back or invalidated:
+// r is stored and loaded with agent-scope atomics, which act beyond the XCDs'
+// L2 caches, and every wave waits for its stores before its workgroup's sum
+// is posted.  (r in such words too, needing no wait and loaded while r^T r is
+// still being summed, gained nothing at 20K rows and lost 1.4 us per iteration
+// at 262K, for twice the bytes.)  Waits are bounded by a wall-clock limit; on
+// expiry the error flag ends every workgroup.
+#include <hip/hip_runtime.h>
+#include <math.h>
+
+#include <algorithm>
+#include <type_traits>
+
+#include "cg_device.h"
+#include "cgmi_internal.h"
+
+namespace cgmi {
+
+namespace {
+
+// One DPP move of a double (both 32-bit halves with the same lane pattern).
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double v) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xF, 0xF, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xF, 0xF, false);
+    return __hiloint2double(hi, lo);
+}
+
+__device__ __forceinline__ double readlane_f64(double v, int lane) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
+                            __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+
+// Sum over each row of 16 lanes, the same value in all of them.
+__device__ __forceinline__ double row_allsum(double v) {
+    v += dpp_f64<0xB1>(v);   // quad_perm [1,0,3,2]
+    v += dpp_f64<0x4E>(v);   // quad_perm [2,3,0,1]
+    v += dpp_f64<0x141>(v);  // row_half_mirror
+    v += dpp_f64<0x140>(v);  // row_mirror
+    return v;
+}
+
+// Sum over the wave, the same value in every lane, in a fixed order.
+__device__ __forceinline__ double wave_allsum(double v) {
+    v = row_allsum(v);
+    return (readlane_f64(v, 0) + readlane_f64(v, 16)) + (readlane_f64(v, 32) + readlane_f64(v, 48));
+}
+
+// Element i of an array of 8-byte values below 2^32 bytes: a 32-bit offset
+// from the uniform base, where an index would cost a 64-bit address per lane.
+template <class T>
+__device__ __forceinline__ T *elem(T *base, uint32_t i) {
+    typedef typename std::conditional<std::is_const<T>::value, const char, char>::type Byte;
+    return reinterpret_cast<T *>(reinterpret_cast<Byte *>(base) + (uint32_t)(i * 8u));
+}
+__device__ __forceinline__ double load_agent(const double *p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void store_agent(double *p, double v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+template <int NT>
+struct ResidentShared {
+    double red[2][NT / kWave];
+    double sum[2];
+    int ok;
+};
+
+// One word of a pair: half of the bits of a value beside a tag.
+__device__ __forceinline__ void store_pair(uint64_t *lo, uint64_t *hi, double v, uint32_t tag) {
+    const uint64_t bits = (uint64_t)__double_as_longlong(v), t = (uint64_t)tag << 32;
+    __hip_atomic_store(lo, t | (bits & 0xFFFFFFFFu), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(hi, t | bits >> 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ uint64_t load_word(const uint64_t *p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ bool tagged(uint64_t lo, uint64_t hi, uint32_t tag) {
+    return (uint32_t)(lo >> 32) == tag && (uint32_t)(hi >> 32) == tag;
+}
+__device__ __forceinline__ double pair_value(uint64_t lo, uint64_t hi) {
+    return __longlong_as_double((long long)(hi << 32 | (lo & 0xFFFFFFFFu)));
+}
+
+// Spin `spin` of a wait that began at t0: false when the launch is being
+// abandoned (looked at every 64 spins).
+__device__ __forceinline__ bool wait_on(const ResidentArgs &a, int spin, uint64_t t0) {
+    if ((spin & 63) != 63) return true;
+    if (__hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) return false;
+    if ((int64_t)(wall_clock64() - t0) <= a.timeout_ticks) return true;
+    __hip_atomic_store(a.err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return false;
+}
+
+// Sum of v over the grid, the same bits in every thread, in a fixed order.
+// `no` counts the launch's sums from 1; consecutive sums alternate between two
+// sets of words, so a set is written again only after its writer has seen
+// every workgroup's word of the sum between, hence after every workgroup has
+// read it.  Each workgroup posts its word in kResidentCopies copies and reads
+// one of them, so that a copy's lines have 1/8 of the grid for readers (one
+// copy: 9.5 us per iteration of 64^3 rows, 8: 7.7, 16: 8.2).  STORED: what any
+// thread stored with store_agent before is visible to load_agent behind the
+// sum.  False when the launch is being abandoned.
+template <int NT, bool STORED>
+__device__ __forceinline__ bool grid_sum(const ResidentArgs &a, double v, uint32_t no, ResidentShared<NT> &S,
+                                         double &out) {
+    constexpr int C = kResidentCopies, W = NT / kWave;
+    static_assert(W <= 16 && C <= kWave, "one row of lanes sums the waves");
+    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave, half = no & 1;
+    const int T = gridDim.x;
+    if (STORED) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's stores are done
+    v = wave_allsum(v);
+    if (lane == 0) S.red[half][w] = v;
+    __syncthreads();
+    if (w == 0) {
+        double s = row_allsum((lane & 15) < W ? S.red[half][lane & 15] : 0.0);
+        if (lane < C) {
+            uint64_t *const lo = a.words + ((size_t)half * C + lane) * 2 * T;
+            store_pair(lo + blockIdx.x, lo + T + blockIdx.x, s, no);
+        }
+        const uint64_t *const lo = a.words + ((size_t)half * C + blockIdx.x % C) * 2 * T, *const hi = lo + T;
+        constexpr int Q = kResidentMaxGroups / kWave;   // members per lane
+        uint64_t l[Q], h[Q];
+        int first = lane;
+        asm volatile("" : "+v"(first));   // its addresses: worked out here, not kept
+        bool ok = true;
+        const uint64_t t0 = wall_clock64();
+        for (int spin = 0;; ++spin) {
+            bool all = true;
+#pragma unroll
+            for (int q = 0; q < Q; ++q)
+                if (q * kWave < T) {
+                    const int m = min(first + q * kWave, T - 1);
+                    l[q] = load_word(elem(lo, m));
+                    h[q] = load_word(elem(hi, m));
+                }
+#pragma unroll
+            for (int q = 0; q < Q; ++q)
+                if (q * kWave < T) all &= tagged(l[q], h[q], no);
+            if (__all(all)) break;
+            if (!__all(wait_on(a, spin, t0))) {
+                ok = false;
+                break;
+            }
+        }
+        s = 0.0;
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+            if (lane + q * kWave < T) s += pair_value(l[q], h[q]);
+        s = wave_allsum(s);
+        if (lane == 0) {
+            S.sum[half] = s;
+            if (!ok) S.ok = 0;
+        }
+    }
+    __syncthreads();
+    out = S.sum[half];
+    return S.ok != 0;
+}
+
+// W: entries of a row at most.
+template <int NT, int W>
+__global__ __launch_bounds__(NT) void k_cg_resident(ResidentArgs a) {
+    __shared__ double s_p[NT];
+    __shared__ ResidentShared<NT> S;
+    if (threadIdx.x == 0) S.ok = 1;
+    if (blockIdx.x == 0 && threadIdx.x == 0) a.st->done = kDoneRunning;   // left so by an abandoned launch
+    const int n = a.n, lo = blockIdx.x * NT, i = lo + threadIdx.x;
+    const bool mine = i < n;
+    // the row's entries in CSR order; past its end the row itself with value 0
+    int col[W];
+    double v[W];
+    const int beg = mine ? a.rp[i] : 0, len = mine ? a.rp[i + 1] - beg : 0;
+#pragma unroll
+    for (int e = 0; e < W; ++e) {
+        col[e] = e < len ? a.ci[beg + e] : min(i, n - 1);
+        v[e] = e < len ? a.val[beg + e] : 0.0;
+    }
+    auto away = [&](int e) { return (uint32_t)(col[e] - lo) >= (uint32_t)NT; };   // another workgroup's
+    double x = 0.0, r = 0.0, p = 0.0, bi = 0.0;
+    if (mine) {
+        double s = 0.0;
+#pragma unroll
+        for (int e = 0; e < W; ++e) s = fma(v[e], *elem(a.x, col[e]), s);
+        x = a.x[i];
+        bi = a.b[i];
+        r = bi - s;
+        store_agent(elem(a.r, i), r);
+    }
+    uint32_t no = 1;
+    double rho, bb;
+    if (!grid_sum<NT, true>(a, r * r, no++, S, rho)) return;
+    if (!grid_sum<NT, false>(a, bi * bi, no++, S, bb)) return;
+    if (bb == 0.0) {   // b = 0: the solution is x = 0
+        if (mine) a.x[i] = 0.0;
+        if (i == 0) {
+            a.st->iter = 0;
+            a.st->done = kDoneConverged;
+            a.st->rho[0] = a.st->rr = a.st->bb = a.st->rr_true = 0.0;
+        }
+        return;
+    }
+    double pn[W];   // p of other workgroups' columns
+#pragma unroll
+    for (int e = 0; e < W; ++e) pn[e] = away(e) ? load_agent(elem(a.r, col[e])) : 0.0;
+    p = r;
+    int status = kDoneMaxit, k = 0;
+    for (;;) {
+        if (stop_test(rho, bb, a.tol)) {
+            status = kDoneConverged;
+            break;
+        }
+        if (k >= a.maxit) break;
+        s_p[threadIdx.x] = p;
+        __syncthreads();
+        double q = 0.0;
+#pragma unroll
+        for (int e = 0; e < W; ++e) q = fma(v[e], away(e) ? pn[e] : s_p[(uint32_t)(col[e] - lo) % NT], q);
+        double pq;
+        if (!grid_sum<NT, false>(a, p * q, no++, S, pq)) return;
+        if (!(pq > 0.0) || !isfinite(pq)) {
+            status = kDoneBreakdown;
+            break;
+        }
+        const double alpha = rho / pq;
+        x = fma(alpha, p, x);
+        r = fma(-alpha, q, r);
+        ++k;
+        if (mine) store_agent(elem(a.r, i), r);
+        double rr;
+        if (!grid_sum<NT, true>(a, r * r, no++, S, rr)) return;
+        const double beta = rr / rho;
+        rho = rr;
+        p = fma(beta, p, r);
+        // (columns made opaque: their addresses and masks, worked out once
+        // before the loop and kept, would not fit the registers)
+#pragma unroll
+        for (int e = 0; e < W; ++e) asm volatile("" : "+v"(col[e]));
+#pragma unroll
+        for (int e = 0; e < W; ++e)
+            if (away(e)) pn[e] = fma(beta, pn[e], load_agent(elem(a.r, col[e])));
+    }
+    // the solution, and the true residual b - A x
+    if (mine) store_agent(elem(a.x, i), x);
+    double rr_true;
+    if (!grid_sum<NT, true>(a, 0.0, no++, S, rr_true)) return;
+    double s = 0.0;
+    if (mine) {
+#pragma unroll
+        for (int e = 0; e < W; ++e) s = fma(v[e], load_agent(elem(a.x, col[e])), s);
+        s = a.b[i] - s;
+    }
+    if (!grid_sum<NT, false>(a, s * s, no++, S, rr_true)) return;
+    if (i == 0) {
+        a.st->iter = k;
+        a.st->done = status;
+        a.st->rho[0] = a.st->rr = rho;
+        a.st->bb = bb;
+        a.st->rr_true = rr_true;
+    }
+}
+
+constexpr int kNT = 1024;   // threads of a workgroup: one workgroup per compute unit
+
+const void *resident_fn(int max_row_len) {
+    return max_row_len <= 5 ? reinterpret_cast<const void *>(k_cg_resident<kNT, 5>)
+                            : reinterpret_cast<const void *>(k_cg_resident<kNT, kResidentMaxRow>);
+}
+
+}  // namespace
+
+int resident_groups(int32_t n, int32_t max_row_len, int cus) {
+    if (n <= 0 || max_row_len < 0 || max_row_len > kResidentMaxRow) return 0;
+    const int groups = (n + kNT - 1) / kNT;
+    return groups <= std::min(cus, kResidentMaxGroups) ? groups : 0;
+}
+
+hipError_t launch_cg_resident(const ResidentArgs &a, int32_t max_row_len, int cus, hipStream_t s) {
+    const int groups = resident_groups(a.n, max_row_len, cus);
+    if (!groups) return hipErrorInvalidValue;
+    ResidentArgs args = a;
+    void *params[] = {&args};
+    return hipLaunchCooperativeKernel(resident_fn(max_row_len), dim3(groups), dim3(kNT), params, 0, s);
+}
+
+}  // namespace cgmi

@@ -548,6 +548,97 @@ def test_split_gap_coded_slices(cg, rb, re):
     assert np.array_equal(out[3], out[7])
 
 
+def tridiagonal(n, step=1):
+    """1D Laplacian plus the identity, coupling rows `step` apart (step
+    coprime to n, around a ring): rows of 3 entries, kappa <= 5."""
+    r = np.arange(n, dtype=np.int64)
+    cols = np.stack([(r - step) % n, r, (r + step) % n], axis=1)
+    vals = np.tile([-1.0, 3.0, -1.0], (n, 1))
+    order = np.argsort(cols, axis=1)
+    return I.CSR(n, np.arange(n + 1, dtype=np.int32) * 3,
+                 np.take_along_axis(cols, order, 1).ravel().astype(np.int32),
+                 np.take_along_axis(vals, order, 1).ravel())
+
+
+RESIDENT = {
+    "one_row_in_the_last_workgroup": lambda: tridiagonal(4097),
+    "scattered_columns": lambda: tridiagonal(20001, 7919),
+    "rows_of_7": lambda: I.poisson3d(27),
+    "largest": lambda: I.poisson2d(512),
+    "past_the_largest": lambda: tridiagonal(262145),
+}
+
+
+@pytest.mark.parametrize("name", sorted(RESIDENT))
+def test_one_cooperative_launch_matches_oracle(cg, name):
+    """The solve with a row per thread (the default above one workgroup's
+    size): fixed work within 1e-9 of the oracle's iterates on well-conditioned
+    systems (rounding differs by a few ulps times the iterations), the same
+    bits again, with and without its own work memory; then to convergence,
+    b = 0, maxit = 0, a breakdown."""
+    A = RESIDENT[name]()
+    n = A.n
+    rng = np.random.default_rng(2)
+    xstar, x0 = rng.uniform(-1, 1, n), rng.uniform(-1, 1, n)
+    b = A.scipy() @ xstar
+    ref = oracle.cg(A, b, x0=x0, tol=0.0, maxit=20)
+    with cg.Solver(A) as s:
+        runs = [s.solve(dev(b), dev(x0), tol=0.0, maxit=20) for _ in range(2)]
+        runs.append(s.solve_noalloc(dev(b), dev(x0), tol=0.0, maxit=20))
+        for x, res in runs:
+            assert res["code"] == cg.CG_MAXIT and res["iterations"] == 20
+            assert np.array_equal(host(x), host(runs[0][0]))
+        x = host(runs[0][0])
+        assert np.linalg.norm(x - ref["x"]) <= 1e-9 * np.linalg.norm(ref["x"])
+        true = np.linalg.norm(b - oracle.spmv(A, x)) / np.linalg.norm(b)
+        assert abs(runs[0][1]["rel_res_true"] - true) <= 1e-9 * true + 1e-14
+        x1, r1 = s.solve(dev(b), tol=1e-10, maxit=5000)
+        s.set_opts(small_path=0)
+        x2, r2 = s.solve(dev(b), tol=1e-10, maxit=5000)
+        s.set_opts(small_path=1)
+        assert r1["code"] == r2["code"] == cg.CG_OK and r1["rel_res_true"] <= 1.01e-10
+        assert abs(r1["iterations"] - r2["iterations"]) <= max(2, 0.05 * r2["iterations"])
+        x, res = s.solve(dev(np.zeros(n)), dev(x0))
+        assert res["code"] == cg.CG_OK and res["iterations"] == 0 and not host(x).any()
+        x, res = s.solve(dev(b), dev(x0), maxit=0)
+        assert res["code"] == cg.CG_MAXIT and np.array_equal(host(x), x0)
+        bad = b.copy()
+        bad[n - 1] = np.nan
+        assert s.solve(dev(bad), maxit=10)[1]["code"] == cg.CG_EBREAKDOWN
+
+
+def test_one_cooperative_launch_from_two_threads(cg):
+    """Two handles, each on its own stream and thread, solve at the same time
+    and give the bits they give alone."""
+    import threading
+    systems = [I.poisson2d(450), I.poisson3d(60)]
+    bs = [A.scipy() @ np.random.default_rng(k).uniform(-1, 1, A.n) for k, A in enumerate(systems)]
+    alone, out, errors = [], [None, None], []
+    for A, b in zip(systems, bs):
+        with cg.Solver(A) as s:
+            alone.append(host(s.solve(dev(b), tol=0.0, maxit=30)[0]))
+
+    def run(k):
+        try:
+            st = torch.cuda.Stream()
+            with torch.cuda.stream(st), cg.Solver(systems[k]) as s:
+                s.set_stream(st)
+                b = dev(bs[k])
+                out[k] = [host(s.solve(b, torch.zeros_like(b), tol=0.0, maxit=30)[0]) for _ in range(10)]
+        except Exception as e:   # reported by the main thread
+            errors.append(e)
+
+    threads = [threading.Thread(target=run, args=(k,)) for k in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not errors, errors
+    for k in range(2):
+        for x in out[k]:
+            assert np.array_equal(x, alone[k])
+
+
 @pytest.mark.parametrize("small_path", [1, 0])
 def test_cg_edge_cases(cg, small_path):
     p = I.poisson2d_problem(16)
