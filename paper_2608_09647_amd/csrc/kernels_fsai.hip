@@ -17,9 +17,8 @@
 // outputs, and the weight gradients' sums over a tile's 16 rows) use the
 // 16x16x16 form, which they fill exactly.
 //
-// The backward pass stages activations and signals in wavefront-private LDS in
-// [unit][row] order so the weight-gradient products (a reduction over rows)
-// read 4 consecutive rows per lane.
+// In the backward pass the weight gradients (a reduction over rows) take their
+// operands from the same fragments, transposed by products with the identity.
 //
 // Definitions (features, factor, loss) follow the header cgmi_fsai.h.
 #include <hip/hip_runtime.h>
@@ -64,6 +63,10 @@ __device__ __forceinline__ bf16x8 cat(bf16x4 lo, bf16x4 hi) {
     return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
 }
 
+__device__ __forceinline__ bf16x4 half(bf16x8 x, int upper) {
+    return upper ? __builtin_shufflevector(x, x, 4, 5, 6, 7) : __builtin_shufflevector(x, x, 0, 1, 2, 3);
+}
+
 // Hidden unit carried by entry j of lane group q in contraction step h of a
 // 16x16x32 product over 64 units.
 __device__ __forceinline__ int unit32(int h, int q, int j) { return 32 * h + 16 * (j >> 2) + 4 * q + (j & 3); }
@@ -75,7 +78,7 @@ __device__ __forceinline__ f32x4 zero4() { return f32x4{0.f, 0.f, 0.f, 0.f}; }
 // every fragment entry below is an unconditional LDS read.
 struct ParamLds {
     uint16_t w1[kHidden][16];     // W1 [unit][feature]
-    uint16_t w2[kHidden][kHidden];
+    uint16_t w2[kHidden][kHidden + 8];
     uint16_t w3[16][kHidden];     // W3 [output][unit]
     float b1[kHidden], b2[kHidden], b3[16];
 };
@@ -88,7 +91,17 @@ __device__ __forceinline__ void stage_params(const float *__restrict__ th, Param
         const int o = i >> 6, c = i & 63;
         P.w3[o][c] = o < kOut ? bf16_bits(th[kOffW3 + o * kHidden + c]) : 0;
     }
-    for (int i = threadIdx.x; i < kHidden * kHidden; i += blockDim.x) P.w2[i >> 6][i & 63] = bf16_bits(th[kOffW2 + i]);
+    // (256 threads: sixteen loads in flight each)
+    for (int i0 = threadIdx.x; i0 < kHidden * kHidden; i0 += 16 * blockDim.x) {
+        float w[16];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) w[k] = th[kOffW2 + min(i0 + k * (int)blockDim.x, kHidden * kHidden - 1)];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            const int i = i0 + k * (int)blockDim.x;
+            if (i < kHidden * kHidden) P.w2[i >> 6][i & 63] = bf16_bits(w[k]);
+        }
+    }
     for (int i = threadIdx.x; i < kHidden; i += blockDim.x) {
         P.b1[i] = th[kOffB1 + i];
         P.b2[i] = th[kOffB2 + i];
@@ -248,7 +261,7 @@ __global__ void k_fsai_prepare(int32_t n, const int32_t *__restrict__ rp, const 
 // Forward pass over a list of 16-row tiles.  Training: outputs to out[row][8].
 // Inference: the factor's values into G (CSR of tril(A)) and G^T.
 template <bool TRAIN>
-__global__ __launch_bounds__(256) void k_fsai_forward(int32_t ntiles, const int32_t *__restrict__ tiles,
+__global__ __launch_bounds__(256, 3) void k_fsai_forward(int32_t ntiles, const int32_t *__restrict__ tiles,
                                                       int64_t nrows, const uint16_t *__restrict__ feats,
                                                       const float *__restrict__ th, float *__restrict__ out,
                                                       const int32_t *__restrict__ scol,
@@ -266,10 +279,17 @@ __global__ __launch_bounds__(256) void k_fsai_forward(int32_t ntiles, const int3
     const int r = l & 15, q = l >> 4;
     const int wave = blockIdx.x * (blockDim.x / kW) + threadIdx.x / kW;
     const int nwaves = gridDim.x * (blockDim.x / kW);
+    // a tile's row and features are loaded while the one before is computed
+    auto row_of = [&](int t) { return (tiles ? (int64_t)tiles[min(t, ntiles - 1)] : (int64_t)t * 16) + r; };
+    auto feats_of = [&](int64_t row) { return row < nrows ? load_feats(feats, row) : bf16x4{0, 0, 0, 0}; };
+    int64_t row_next = row_of(wave), row_after = row_of(wave + nwaves);
+    bf16x4 fin_next = feats_of(row_next);
     for (int t = wave; t < ntiles; t += nwaves) {
-        const int64_t row0 = tiles ? (int64_t)tiles[t] : (int64_t)t * 16;
-        const int64_t row = row0 + r;
-        const bf16x4 fin = row < nrows ? load_feats(feats, row) : bf16x4{0, 0, 0, 0};
+        const int64_t row = row_next;
+        const bf16x4 fin = fin_next;
+        row_next = row_after;
+        fin_next = feats_of(row_next);
+        row_after = row_of(t + 2 * nwaves);
         Fwd Y;
         forward_tile(W, P, fin, Y);
         if (row >= nrows) continue;
@@ -320,23 +340,36 @@ struct GRow {
 __device__ __forceinline__ GRow g_row(int64_t base, int j, const float *__restrict__ out,
                                       const int32_t *__restrict__ scol) {
     GRow g;
-    const float *o = out + (base + j) * kOutPad;
-    const float oc = o[0];
+    const float4 o = *reinterpret_cast<const float4 *>(out + (base + j) * kOutPad);   // 32-byte rows
     g.col[0] = j;
-    g.val[0] = (oc > 30.f ? oc : log1pf(expf(oc))) + (float)kEpsDiag;
+    g.val[0] = (o.x > 30.f ? o.x : log1pf(expf(o.x))) + (float)kEpsDiag;
     g.col[1] = scol[(base + j) * kSlots + kSlotW];
-    g.val[1] = g.col[1] >= 0 ? o[1] : 0.f;
+    g.val[1] = g.col[1] >= 0 ? o.y : 0.f;
     g.col[2] = scol[(base + j) * kSlots + kSlotS];
-    g.val[2] = g.col[2] >= 0 ? o[3] : 0.f;
+    g.val[2] = g.col[2] >= 0 ? o.w : 0.f;
     return g;
 }
 
-__device__ __forceinline__ float ahat(int64_t base, int row, int colj, const int32_t *__restrict__ scol,
-                                      const float *__restrict__ sval) {
+// The slots of a row of A_hat, and its entry in a column (0: none).
+struct ARow {
+    int col[kSlots];
+    float val[kSlots];
+    __device__ __forceinline__ float at(int c) const {
+        float v = 0.f;
 #pragma unroll
-    for (int s = 0; s < kSlots; ++s)
-        if (scol[(base + row) * kSlots + s] == colj) return sval[(base + row) * kSlots + s];
-    return 0.f;
+        for (int s = 0; s < kSlots; ++s) v = col[s] == c ? val[s] : v;
+        return v;
+    }
+};
+
+__device__ __forceinline__ ARow a_row(int64_t row, const int32_t *__restrict__ scol, const float *__restrict__ sval) {
+    ARow R;
+#pragma unroll
+    for (int s = 0; s < kSlots; ++s) {
+        R.col[s] = scol[row * kSlots + s];
+        R.val[s] = sval[row * kSlots + s];
+    }
+    return R;
 }
 
 // Row i of G~ A_hat has at most 15 terms (G~ entry a of row i times slot s
@@ -395,16 +428,15 @@ __global__ __launch_bounds__(256) void k_fsai_loss(int32_t nsamp, const int32_t 
         }
         // the lowest lane proposing j owns it
         bool own = j >= 0;
-        for (int q = 0; q < 3 * kLossTerms; ++q) {
-            const int jq = __shfl(j, q, 64);
-            if (q < lane && jq == j) own = false;
-        }
+#pragma unroll
+        for (int q = 0; q < 3 * kLossTerms; ++q)
+            if (q < lane && __builtin_amdgcn_readlane(j, q) == j) own = false;
         // u at j's columns (every lane takes part in the shuffles)
         float ub[3] = {0.f, 0.f, 0.f};
 #pragma unroll
         for (int q = 0; q < kLossTerms; ++q) {
-            const int cq = __shfl(tcol, q, 64);
-            const float vq = __shfl(tval, q, 64);
+            const int cq = __builtin_amdgcn_readlane(tcol, q);
+            const float vq = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(tval), q));
 #pragma unroll
             for (int b = 0; b < 3; ++b)
                 if (cq >= 0 && cq == gj.col[b]) ub[b] += vq;
@@ -420,17 +452,19 @@ __global__ __launch_bounds__(256) void k_fsai_loss(int32_t nsamp, const int32_t 
 #pragma unroll
             for (int b = 0; b < 3; ++b)
                 if (gj.col[b] >= 0) dg_add(&dg[(base + j) * 3 + b], coef * e * ub[b]);
+            // the three rows of A_hat whole, in one trip (searched slot by slot
+            // through memory, the kernel took 47 us at 8192 samples)
+            ARow ar[3];
+#pragma unroll
+            for (int s2 = 0; s2 < 3; ++s2) ar[s2] = a_row(base + max(gj.col[s2], 0), scol, sval);
 #pragma unroll
             for (int b = 0; b < 3; ++b) {
                 const int cb = gi.col[b];
                 if (cb < 0) continue;
                 float w = 0.f;
 #pragma unroll
-                for (int s2 = 0; s2 < 3; ++s2) {
-                    const int cs = gj.col[s2];
-                    if (cs < 0) continue;
-                    w += gj.val[s2] * ahat(base, cs, cb, scol, sval);
-                }
+                for (int s2 = 0; s2 < 3; ++s2)
+                    if (gj.col[s2] >= 0) w += gj.val[s2] * ar[s2].at(cb);
                 gacc[b] = coef * e * w;
             }
         }
@@ -455,19 +489,34 @@ __global__ __launch_bounds__(256) void k_fsai_loss(int32_t nsamp, const int32_t 
 // ---------------------------------------------------------------------------
 // Backward pass over a list of 16-row tiles; one partial gradient per
 // workgroup (waves added in order through LDS).
-struct alignas(16) WaveLds {   // 8-byte loads of 4 consecutive entries
-    uint16_t fT[16][16];    // [feature][row]
-    uint16_t h1T[64][16];   // [unit][row]
-    uint16_t h2T[64][16];
-    uint16_t d1T[64][16];   // dz1
-    uint16_t d2T[64][16];   // dz2
-    uint16_t d3T[16][16];   // dz3 (outputs padded to 16)
-};
+//
+// The weight gradients sum over a tile's rows, so their operands hold four
+// rows of one unit per lane, where the forward fragments hold four units of
+// one row: 16x16 blocks transposed.  A fragment read as an A operand is its
+// block transposed already, so one product with the identity returns it in the
+// other layout, exactly (each sum has one nonzero term, a bfloat16 value).
+// Through LDS the 72 two-byte writes a tile took, four to a bank, were 1.5 us
+// of its 2.7.
+__device__ __forceinline__ bf16x4 transpose16(bf16x4 x, bf16x4 ident) {
+    const f32x4 c = mfma(x, ident, zero4());
+    // the upper halves of the float32 values
+    const uint32_t lo = __builtin_amdgcn_perm(__float_as_uint(c[1]), __float_as_uint(c[0]), 0x07060302);
+    const uint32_t hi = __builtin_amdgcn_perm(__float_as_uint(c[3]), __float_as_uint(c[2]), 0x07060302);
+    return __builtin_bit_cast(bf16x4, (uint64_t)lo | (uint64_t)hi << 32);
+}
 
-__device__ __forceinline__ void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+template <int CTRL>
+__device__ __forceinline__ float dpp_f32(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
+}
+
+// Sum over each row of 16 lanes, in all of them.
+__device__ __forceinline__ float row16_allsum(float v) {
+    v += dpp_f32<0xB1>(v);   // quad_perm [1,0,3,2]
+    v += dpp_f32<0x4E>(v);   // quad_perm [2,3,0,1]
+    v += dpp_f32<0x141>(v);  // row_half_mirror
+    v += dpp_f32<0x140>(v);  // row_mirror
+    return v;
 }
 
 __global__ __launch_bounds__(256) void k_fsai_backward(int32_t ntiles, const int32_t *__restrict__ tiles,
@@ -477,12 +526,10 @@ __global__ __launch_bounds__(256) void k_fsai_backward(int32_t ntiles, const int
                                                        const int64_t *__restrict__ dg,
                                                        const int32_t *__restrict__ scol,
                                                        float *__restrict__ gpart) {
-    __shared__ WaveLds L[4];
-    __shared__ float acc[kNParams];
+    __shared__ float grad[4][kNParams];
     const int l = threadIdx.x & (kW - 1);
     const int r = l & 15, q = l >> 4;
     const int wv = threadIdx.x / kW;
-    WaveLds &S = L[wv];
     __shared__ ParamLds P;
     stage_params(th, P);
     Frags W;
@@ -518,38 +565,50 @@ __global__ __launch_bounds__(256) void k_fsai_backward(int32_t ntiles, const int
 
     const int wave = blockIdx.x * 4 + wv;
     const int nwaves = gridDim.x * 4;
+    // what a tile reads is loaded while the one before is computed, its row
+    // one tile earlier still
+    struct TileIn {
+        bf16x4 fin;
+        float oc;
+        int64_t dg[3];
+        int32_t w, s;   // columns of the W and S slots
+    };
+    auto row_of = [&](int t) { return (int64_t)tiles[min(t, ntiles - 1)] + r; };
+    auto load_in = [&](int64_t row) {
+        TileIn I;
+        I.fin = load_feats(feats, row);
+        I.oc = out[row * kOutPad];
+#pragma unroll
+        for (int b = 0; b < 3; ++b) I.dg[b] = dg[row * 3 + b];
+        I.w = scol[row * kSlots + kSlotW];
+        I.s = scol[row * kSlots + kSlotS];
+        return I;
+    };
+    bf16x4 ident;   // B operand
+#pragma unroll
+    for (int v = 0; v < 4; ++v) ident[v] = 4 * q + v == r ? (short)0x3F80 : (short)0;
+    TileIn next = load_in(row_of(wave));
+    int64_t row_next = row_of(wave + nwaves);
     for (int tt = wave; tt < ntiles; tt += nwaves) {
-        const int64_t row = (int64_t)tiles[tt] + r;
-        const bf16x4 fin = load_feats(feats, row);
+        const TileIn in = next;
+        next = load_in(row_next);
+        row_next = row_of(tt + 2 * nwaves);
         Fwd Y;
-        forward_tile(W, P, fin, Y);
-#pragma unroll
-        for (int v = 0; v < 4; ++v) S.fT[4 * q + v][r] = (uint16_t)fin[v];
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                S.h1T[16 * t + 4 * q + v][r] = (uint16_t)Y.h1[t >> 1][4 * (t & 1) + v];
-                S.h2T[16 * t + 4 * q + v][r] = (uint16_t)Y.h2[t >> 1][4 * (t & 1) + v];
-            }
+        forward_tile(W, P, in.fin, Y);
         // dz3 (outputs 4q+v of row r)
         // dL/do of row r from dL/dG~: through the softplus for C, directly for
         // the W and S slots the row has, zero for the unused E and N
         bf16x4 d3;
-        const float oc = out[row * kOutPad];
-        const float sig = 1.f / (1.f + expf(-oc));
+        const float sig = 1.f / (1.f + expf(-in.oc));
         float dgr[3];
 #pragma unroll
-        for (int b = 0; b < 3; ++b) dgr[b] = (float)((double)dg[row * 3 + b] * (1.0 / kDgScale));
-        const float dv[4] = {dgr[0] * sig, scol[row * kSlots + kSlotW] >= 0 ? dgr[1] : 0.f,
-                             0.f, scol[row * kSlots + kSlotS] >= 0 ? dgr[2] : 0.f};
+        for (int b = 0; b < 3; ++b) dgr[b] = (float)((double)in.dg[b] * (1.0 / kDgScale));
+        const float dv[4] = {dgr[0] * sig, in.w >= 0 ? dgr[1] : 0.f, 0.f, in.s >= 0 ? dgr[2] : 0.f};
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            const int o = 4 * q + v;
             const float g = q == 0 ? dv[v] : 0.f;
             gb3[v] += g;
             d3[v] = (short)bf16_bits(g);
-            S.d3T[o][r] = (uint16_t)d3[v];
         }
         // dz2 = (W3^T dz3) * (z2 > 0)
         bf16x4 d2[4];
@@ -561,10 +620,10 @@ __global__ __launch_bounds__(256) void k_fsai_backward(int32_t ntiles, const int
                 const float g = Y.z2[t][v] > 0.f ? c[v] : 0.f;
                 gb2[t][v] += g;
                 d2[t][v] = (short)bf16_bits(g);
-                S.d2T[16 * t + 4 * q + v][r] = (uint16_t)d2[t][v];
             }
         }
         // dz1 = (W2^T dz2) * (z1 > 0)
+        bf16x4 d1[4];
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
             f32x4 c = zero4();
@@ -574,66 +633,61 @@ __global__ __launch_bounds__(256) void k_fsai_backward(int32_t ntiles, const int
             for (int v = 0; v < 4; ++v) {
                 const float g = Y.z1[t][v] > 0.f ? c[v] : 0.f;
                 gb1[t][v] += g;
-                S.d1T[16 * t + 4 * q + v][r] = bf16_bits(g);
+                d1[t][v] = (short)bf16_bits(g);
             }
         }
-        wave_sync();
         // weight gradients: sums over the tile's 16 rows
+        const bf16x4 ft = transpose16(in.fin, ident), d3t = transpose16(d3, ident);
+        bf16x4 h1t[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) h1t[t] = transpose16(half(Y.h1[t >> 1], t & 1), ident);
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
-            const bf16x4 a1 = lds4(&S.d1T[16 * t + r][4 * q]);
-            gw1[t] = mfma(a1, lds4(&S.fT[r][4 * q]), gw1[t]);
-            const bf16x4 a2 = lds4(&S.d2T[16 * t + r][4 * q]);
+            gw1[t] = mfma(transpose16(d1[t], ident), ft, gw1[t]);
+            const bf16x4 a2 = transpose16(d2[t], ident);
 #pragma unroll
-            for (int s = 0; s < 4; ++s) gw2[t][s] = mfma(a2, lds4(&S.h1T[16 * s + r][4 * q]), gw2[t][s]);
-            gw3[t] = mfma(lds4(&S.d3T[r][4 * q]), lds4(&S.h2T[16 * t + r][4 * q]), gw3[t]);
+            for (int s = 0; s < 4; ++s) gw2[t][s] = mfma(a2, h1t[s], gw2[t][s]);
+            gw3[t] = mfma(d3t, transpose16(half(Y.h2[t >> 1], t & 1), ident), gw3[t]);
         }
-        wave_sync();
     }
     // bias sums: reduce over the 16 rows held by lanes r = 0..15
 #pragma unroll
     for (int t = 0; t < 4; ++t)
 #pragma unroll
-        for (int v = 0; v < 4; ++v)
+        for (int v = 0; v < 4; ++v) {
+            gb1[t][v] = row16_allsum(gb1[t][v]);
+            gb2[t][v] = row16_allsum(gb2[t][v]);
+        }
 #pragma unroll
-            for (int m = 1; m < 16; m <<= 1) {
-                gb1[t][v] += __shfl_xor(gb1[t][v], m, 64);
-                gb2[t][v] += __shfl_xor(gb2[t][v], m, 64);
-            }
+    for (int v = 0; v < 4; ++v) gb3[v] = row16_allsum(gb3[v]);
+    // each wavefront's gradient to its own part of LDS, then the four added in
+    // order: added one wavefront
+    // after the other into one copy, each add waited for its LDS read, 20 us of
+    // the kernel's 43 at 131K rows
+    float *const mine = grad[wv];
 #pragma unroll
-    for (int v = 0; v < 4; ++v)
+    for (int t = 0; t < 4; ++t)
 #pragma unroll
-        for (int m = 1; m < 16; m <<= 1) gb3[v] += __shfl_xor(gb3[v], m, 64);
-    // add the four wavefronts' gradients in order
-    for (int p = threadIdx.x; p < kNParams; p += blockDim.x) acc[p] = 0.f;
-    __syncthreads();
-    for (int w = 0; w < 4; ++w) {
-        if (wv == w) {
+        for (int v = 0; v < 4; ++v) {
+            const int u = 16 * t + 4 * q + v;  // row of the gradient tile
+            if (r < kFeat) mine[kOffW1 + u * kFeat + r] = gw1[t][v];
 #pragma unroll
-            for (int t = 0; t < 4; ++t)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int u = 16 * t + 4 * q + v;  // row of the gradient tile
-                    if (r < kFeat) acc[kOffW1 + u * kFeat + r] += gw1[t][v];
-#pragma unroll
-                    for (int s = 0; s < 4; ++s) acc[kOffW2 + u * kHidden + 16 * s + r] += gw2[t][s][v];
-                    const int o = 4 * q + v;
-                    if (o < kOut) acc[kOffW3 + o * kHidden + 16 * t + r] += gw3[t][v];
-                    if (r == 0) {
-                        acc[kOffB1 + u] += gb1[t][v];
-                        acc[kOffB2 + u] += gb2[t][v];
-                    }
-                }
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int o = 4 * q + v;
-                if (r == 0 && o < kOut) acc[kOffB3 + o] += gb3[v];
+            for (int s = 0; s < 4; ++s) mine[kOffW2 + u * kHidden + 16 * s + r] = gw2[t][s][v];
+            const int o = 4 * q + v;
+            if (o < kOut) mine[kOffW3 + o * kHidden + 16 * t + r] = gw3[t][v];
+            if (r == 0) {
+                mine[kOffB1 + u] = gb1[t][v];
+                mine[kOffB2 + u] = gb2[t][v];
             }
         }
-        __syncthreads();
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const int o = 4 * q + v;
+        if (r == 0 && o < kOut) mine[kOffB3 + o] = gb3[v];
     }
+    __syncthreads();
     for (int p = threadIdx.x; p < kNParams; p += blockDim.x)
-        gpart[(int64_t)blockIdx.x * kNParams + p] = acc[p];
+        gpart[(int64_t)blockIdx.x * kNParams + p] = ((grad[0][p] + grad[1][p]) + grad[2][p]) + grad[3][p];
 }
 
 // Sum of the workgroup gradients in a fixed order; Adam step when t_step > 0,
@@ -728,7 +782,7 @@ hipError_t fsai_forward_outputs(int32_t ntiles, const int32_t *tiles, int64_t nr
                                 const uint16_t *feats, const float *theta, float *out, int64_t *dg_zero,
                                 hipStream_t s) {
     if (ntiles <= 0) return hipSuccess;
-    const int grid = (ntiles + 3) / 4 < 1024 ? (ntiles + 3) / 4 : 1024;
+    const int grid = (ntiles + 3) / 4 < 768 ? (ntiles + 3) / 4 : 768;   // as many as are resident at once
     hipLaunchKernelGGL(k_fsai_forward<true>, dim3(grid), dim3(256), 0, s, ntiles, tiles, nrows, feats,
                        theta, out, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, dg_zero);
     return hipGetLastError();
