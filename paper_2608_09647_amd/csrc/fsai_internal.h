@@ -60,14 +60,15 @@ hipError_t fsai_forward_factor(int32_t n, const uint16_t *feats, const float *th
 
 // Loss terms and dL/dG~ (dg[row][3]: C, W, S; 64-bit fixed point in units of
 // 2^-40, accumulated with integer atomics, so the sums are reproducible) of
-// the sampled rows, one wavefront per sample; partials[block] = sum of
+// the sampled rows (rows_per_sys of each selected system, whose first rows and
+// sizes are sel_base and sel_n), one wavefront per sample; partials[block] = sum of
 // squared entries of E, fsai_loss_blocks(nsamp) of them.
 inline int32_t fsai_loss_blocks(int32_t nsamp) {
     const int32_t b = (nsamp + 3) / 4;
     return b < 1 ? 1 : b > 2048 ? 2048 : b;
 }
-hipError_t fsai_loss(int32_t nsamp, const int32_t *samp_row, const int64_t *samp_base,
-                     const int32_t *samp_n, const float *out, const int32_t *scol, const float *sval,
+hipError_t fsai_loss(int32_t nsamp, int32_t rows_per_sys, const int32_t *samp_row, const int64_t *sel_base,
+                     const int32_t *sel_n, const float *out, const int32_t *scol, const float *sval,
                      int64_t *dg, float coef, double *partials, hipStream_t s);
 
 // Parameter gradient of the listed 16-row tiles: gpart[block][kNParams].
@@ -77,9 +78,10 @@ hipError_t fsai_backward(int32_t ntiles, const int32_t *tiles, const uint16_t *f
                          hipStream_t s);
 
 // Sum of nparts gradient partials (in order) into grad_out (may be null);
-// with t_step >= 1 an Adam step on theta (m, v: moments).
-hipError_t fsai_adam(int32_t nparts, const float *gpart, float *theta, float *m, float *v,
-                     float *grad_out, int32_t t_step, float lr, hipStream_t s);
+// with t_step >= 1 an Adam step on theta (m, v: moments).  The sum of the
+// nloss loss partials goes to *loss_sum.
+hipError_t fsai_adam(int32_t nloss, const double *lpart, double *loss_sum, int32_t nparts, const float *gpart,
+                     float *theta, float *m, float *v, float *grad_out, int32_t t_step, float lr, hipStream_t s);
 
 // Copy CSR values into the slot-major sliced layout (slices of 64 rows).
 hipError_t sell_refresh(int32_t m, int32_t ntiles, const int32_t *rp, const int32_t *sell_off,

@@ -385,9 +385,10 @@ __device__ __forceinline__ ARow a_row(int64_t row, const int32_t *__restrict__ s
 // per entry).
 constexpr int kLossTerms = 3 * kSlots;
 
-__global__ __launch_bounds__(256) void k_fsai_loss(int32_t nsamp, const int32_t *__restrict__ samp_row,
-                                                   const int64_t *__restrict__ samp_base,
-                                                   const int32_t *__restrict__ samp_n,
+__global__ __launch_bounds__(256) void k_fsai_loss(int32_t nsamp, int32_t rows_per_sys,
+                                                   const int32_t *__restrict__ samp_row,
+                                                   const int64_t *__restrict__ sel_base,
+                                                   const int32_t *__restrict__ sel_n,
                                                    const float *__restrict__ out,
                                                    const int32_t *__restrict__ scol,
                                                    const float *__restrict__ sval,
@@ -397,9 +398,9 @@ __global__ __launch_bounds__(256) void k_fsai_loss(int32_t nsamp, const int32_t 
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     double loss = 0.0;
     for (int sidx = blockIdx.x * 4 + wv; sidx < nsamp; sidx += gridDim.x * 4) {
-        const int i = samp_row[sidx];
-        const int64_t base = samp_base[sidx];
-        const int n = samp_n[sidx];
+        const int i = samp_row[sidx], sel = sidx / rows_per_sys;
+        const int64_t base = sel_base[sel];
+        const int n = sel_n[sel];
         const GRow gi = g_row(base, i, out, scol);
         // term t of u (lanes 0..14; -1: absent)
         int tcol = -1;
@@ -694,13 +695,29 @@ __global__ __launch_bounds__(256) void k_fsai_backward(int32_t ntiles, const int
 // else the gradient is only written to grad_out.  A workgroup takes 64
 // parameters; wave w sums, in order, the w-th quarter of the partials of
 // its lane's parameter (16 loads in flight per lane), and wave 0 adds the
-// four quarter sums in order.
-__global__ __launch_bounds__(256) void k_fsai_adam(int32_t nparts, const float *__restrict__ gpart,
+// four quarter sums in order.  The workgroup after the last sums the loss
+// partials, in an order of its own that is the same on every run.
+constexpr int kAdamBlocks = (kNParams + 63) / 64;
+
+__global__ __launch_bounds__(256) void k_fsai_adam(int32_t nloss, const double *__restrict__ lpart,
+                                                   double *__restrict__ loss_sum, int32_t nparts,
+                                                   const float *__restrict__ gpart,
                                                    float *__restrict__ theta, float *__restrict__ m,
                                                    float *__restrict__ v, float *__restrict__ grad_out,
                                                    int32_t t_step, float lr) {
     __shared__ float part[4][64];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    if (blockIdx.x == kAdamBlocks) {
+        __shared__ double wsum[4];
+        double s = 0.0;
+        for (int i = threadIdx.x; i < nloss; i += 256) s += lpart[i];
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
+        if (lane == 0) wsum[w] = s;
+        __syncthreads();
+        if (threadIdx.x == 0) *loss_sum = ((wsum[0] + wsum[1]) + wsum[2]) + wsum[3];
+        return;
+    }
     const int p = blockIdx.x * 64 + lane;
     const int pc = p < kNParams ? p : kNParams - 1;
     const int q = (nparts + 3) / 4;
@@ -799,12 +816,12 @@ hipError_t fsai_forward_factor(int32_t n, const uint16_t *feats, const float *th
     return hipGetLastError();
 }
 
-hipError_t fsai_loss(int32_t nsamp, const int32_t *samp_row, const int64_t *samp_base,
-                     const int32_t *samp_n, const float *out, const int32_t *scol, const float *sval,
+hipError_t fsai_loss(int32_t nsamp, int32_t rows_per_sys, const int32_t *samp_row, const int64_t *sel_base,
+                     const int32_t *sel_n, const float *out, const int32_t *scol, const float *sval,
                      int64_t *dg, float coef, double *partials, hipStream_t s) {
     if (nsamp <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_fsai_loss, dim3(fsai_loss_blocks(nsamp)), dim3(256), 0, s, nsamp, samp_row,
-                       samp_base, samp_n, out, scol, sval, dg, coef, partials);
+    hipLaunchKernelGGL(k_fsai_loss, dim3(fsai_loss_blocks(nsamp)), dim3(256), 0, s, nsamp, rows_per_sys, samp_row,
+                       sel_base, sel_n, out, scol, sval, dg, coef, partials);
     return hipGetLastError();
 }
 
@@ -817,10 +834,10 @@ hipError_t fsai_backward(int32_t ntiles, const int32_t *tiles, const uint16_t *f
     return hipGetLastError();
 }
 
-hipError_t fsai_adam(int32_t nparts, const float *gpart, float *theta, float *m, float *v,
-                     float *grad_out, int32_t t_step, float lr, hipStream_t s) {
-    hipLaunchKernelGGL(k_fsai_adam, dim3((kNParams + 63) / 64), dim3(256), 0, s, nparts, gpart, theta,
-                       m, v, grad_out, t_step, lr);
+hipError_t fsai_adam(int32_t nloss, const double *lpart, double *loss_sum, int32_t nparts, const float *gpart,
+                     float *theta, float *m, float *v, float *grad_out, int32_t t_step, float lr, hipStream_t s) {
+    hipLaunchKernelGGL(k_fsai_adam, dim3(kAdamBlocks + 1), dim3(256), 0, s, nloss, lpart, loss_sum, nparts, gpart,
+                       theta, m, v, grad_out, t_step, lr);
     return hipGetLastError();
 }
 
