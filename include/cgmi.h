@@ -98,9 +98,12 @@ typedef struct cg_opts {
                               (n_spmv = 1); 0: off                               */
     int32_t small_path;    /* 1 (default): systems that fit one workgroup's LDS
                               run the whole solve in one single-workgroup
-                              kernel; larger ones of rows of at most 7 entries
-                              and at most 1024 rows per compute unit in one
-                              cooperative launch, where the tiling, grid and
+                              kernel; larger ones run it in one cooperative
+                              launch, if their rows have at most 7 entries and
+                              number at most 1024 per compute unit, or if they
+                              form a grid of 3, 5 or 7 points whose share of a
+                              compute unit fits its registers and LDS (up to
+                              about 10,000 rows), and the tiling, grid and
                               fusion options below and profile are left
                               automatic or off; 0: always several kernels  */
     int32_t spmv_grid;     /* workgroups of the SpMV kernels (0: automatic)      */

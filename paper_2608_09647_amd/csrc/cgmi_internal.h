@@ -367,6 +367,30 @@ constexpr inline size_t resident_words(int groups) { return 4 * kResidentCopies 
 int resident_groups(int32_t n, int32_t max_row_len, int cus);
 hipError_t launch_cg_resident(const ResidentArgs &a, int32_t max_row_len, int cus, hipStream_t s);
 
+// The same for a global stencil of width 3, 5 or 7, several rows per thread
+// and p in LDS.
+constexpr int kWindowEntries = 20352;     // entries of the window in LDS at most (159 KB)
+struct WindowSegment {
+    int32_t start, len;       // columns, from the workgroup's first row
+    int32_t base;             // where they begin in LDS
+};
+struct WindowArgs {
+    StenGlobal sten;
+    const double *val;        // stencil slices (konst: null)
+    const uint8_t *mask;      // slots of every row
+    int32_t groups;           // workgroups
+    int32_t rows;             // rows of each: a multiple of 64
+    int32_t nseg, entries;    // segments of the window, entries of all
+    WindowSegment seg[kSliceMaxWidth + 1];
+    int32_t disp[kSliceMaxWidth];   // column at offset e of the workgroup's row r: entry disp[e] + r
+    int32_t own;              // and r itself: entry own + r
+    int32_t head, tail;       // rows before head and from tail on are columns of other workgroups
+};
+// False: the system does not fit (width, rows, the window); else
+// fills in g but for val and mask.
+bool window_shape(int32_t n, const StenGlobal &C, int cus, WindowArgs &g);
+hipError_t launch_cg_window(const ResidentArgs &a, const WindowArgs &g, hipStream_t s);
+
 // Gather / scatter of p entries for the halo exchange.
 hipError_t launch_gather(int32_t cnt, const int32_t *idx, const double *src, double *dst,
                          hipStream_t s);

@@ -29,6 +29,7 @@
 #include <math.h>
 
 #include <algorithm>
+#include <climits>
 #include <type_traits>
 
 #include "cg_device.h"
@@ -79,6 +80,8 @@ __device__ __forceinline__ double load_agent(const double *p) {
 __device__ __forceinline__ void store_agent(double *p, double v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+
+constexpr int kNT = 1024;   // threads of a workgroup: one workgroup per compute unit
 
 template <int NT>
 struct ResidentShared {
@@ -281,7 +284,235 @@ __global__ __launch_bounds__(NT) void k_cg_resident(ResidentArgs a) {
     }
 }
 
-constexpr int kNT = 1024;   // threads of a workgroup: one workgroup per compute unit
+// The same for a global stencil (StenGlobal), several rows per thread: a
+// workgroup's M consecutive rows keep x, r and q in registers, row u NT + ...
+// of a thread in slice order, and in LDS p of every column they have: the rows
+// moved by each offset, overlapping ranges in one segment.  What lies outside
+// the workgroup's rows there are its copies of other workgroups' p.  Constant values are launch arguments, so
+// an iteration then touches memory for r alone, and of r only the rows that
+// others read; other values are streamed from the stencil slices.  Us per
+// iteration, separate kernels (whose vectors pass through memory in every one)
+// and here: 2-D diffusion 1024^2 26.6 and 12.3, 1500 x 1401 43.0 and 21.7 (84
+// MB of values, 13 us at 6.4 TB/s), 1600^2 51 and 24; Poisson 1024^2 21.4 and
+// 9.7, 1500 x 1400 33.7 and 15.9, 72^3 16.3 and 10.0, 90^3 19.4 and 14.2.
+template <int NT, int RPT, int W, bool KONST>
+__global__ __launch_bounds__(NT) void k_cg_window(ResidentArgs a, WindowArgs g) {
+    extern __shared__ double s_p[];   // [g.entries]
+    __shared__ ResidentShared<NT> S;
+    if (threadIdx.x == 0) S.ok = 1;
+    if (blockIdx.x == 0 && threadIdx.x == 0) a.st->done = kDoneRunning;   // left so by an abandoned launch
+    const int n = a.n, lo = blockIdx.x * g.rows, end = min(n, lo + g.rows);
+    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+    // the thread's row u; its first one is made opaque before every phase, or
+    // the addresses of all rows would be worked out once and kept in registers
+    int row0 = lo + w * kWave + lane;
+    auto row_of = [&](int u) { return row0 + u * NT; };
+    // whether another workgroup's rows have this one as a column
+    auto shared = [&](int i) { return i - lo < g.head || i - lo >= g.tail; };
+    auto phase = [&] { asm volatile("" : "+v"(row0)); };
+    // a row's entries (constant ones: which it has); a row past the end reads
+    // those of the last slice
+    struct Entries {
+        double v[KONST ? 1 : W];
+        uint32_t have;
+    };
+    auto entries = [&](int i) {
+        Entries E;
+        if (KONST) {
+            E.have = g.mask[min(i, n - 1)];
+        } else {
+            const double *const v = g.val + ((int64_t)min(i / kWave, (n - 1) / kWave) * W * kWave + lane);
+#pragma unroll
+            for (int e = 0; e < W; ++e) E.v[KONST ? 0 : e] = v[e * kWave];
+        }
+        return E;
+    };
+    // q of a row from the window, its products and sums rounded in turn
+    auto product = [&](int i, const Entries &E) {
+        const double *const at = s_p + (i - lo);
+        double s = 0.0;
+#pragma unroll
+        for (int e = 0; e < W; ++e)
+            s = add_rounded(s, KONST ? ((E.have >> e) & 1u ? g.sten.val[e] : 0.0) : E.v[KONST ? 0 : e], at[g.disp[e]]);
+        return s;
+    };
+    // f(u, row, q) of the thread's rows, the next row's entries on their way;
+    // first: those of row 0
+    auto for_products = [&](const Entries &first, auto f) {
+        Entries E = first;
+#pragma unroll
+        for (int u = 0; u < RPT; ++u) {
+            const Entries cur = E;
+            if (u + 1 < RPT) E = entries(row_of(u + 1));
+            if (row_of(u) < end) f(u, row_of(u), product(row_of(u), cur));
+        }
+    };
+    // sets the window's entries outside the workgroup's rows to f(old entry, v
+    // of its column), four loads of v in flight per thread
+    auto update_ends = [&](const double *v, auto f) {
+        for (int sg = 0; sg < g.nseg; ++sg) {
+            const int first = lo + g.seg[sg].start, len = g.seg[sg].len;
+            double *const at = s_p + g.seg[sg].base;
+            auto other = [&](int k, int c) {
+                return k < len && c >= 0 && c < n && (uint32_t)(c - lo) >= (uint32_t)g.rows;
+            };
+            for (int k0 = threadIdx.x; k0 < len; k0 += 4 * NT) {
+                double x4[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (other(k0 + j * NT, first + k0 + j * NT)) x4[j] = load_agent(elem(v, first + k0 + j * NT));
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (other(k0 + j * NT, first + k0 + j * NT)) at[k0 + j * NT] = f(at[k0 + j * NT], x4[j]);
+            }
+        }
+    };
+    for (int sg = 0; sg < g.nseg; ++sg)
+        for (int k = threadIdx.x; k < g.seg[sg].len; k += NT) {
+            const int c = lo + g.seg[sg].start + k;
+            s_p[g.seg[sg].base + k] = c >= 0 && c < n ? a.x[c] : 0.0;
+        }
+    __syncthreads();
+    double x[RPT], r[RPT], q[RPT];
+    double acc = 0.0, accb = 0.0;
+#pragma unroll
+    for (int u = 0; u < RPT; ++u) x[u] = r[u] = q[u] = 0.0;
+    for_products(entries(row_of(0)), [&](int u, int i, double s) {
+        const double bi = a.b[i];
+        x[u] = s_p[i - lo + g.own];
+        r[u] = bi - s;
+        acc = fma(r[u], r[u], acc);
+        accb = fma(bi, bi, accb);
+        if (shared(i)) store_agent(elem(a.r, i), r[u]);
+    });
+    uint32_t no = 1;
+    double rho, bb;
+    if (!grid_sum<NT, true>(a, acc, no++, S, rho)) return;
+    if (!grid_sum<NT, false>(a, accb, no++, S, bb)) return;
+    if (bb == 0.0) {   // b = 0: the solution is x = 0
+#pragma unroll
+        for (int u = 0; u < RPT; ++u)
+            if (row_of(u) < end) a.x[row_of(u)] = 0.0;
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            a.st->iter = 0;
+            a.st->done = kDoneConverged;
+            a.st->rho[0] = a.st->rr = a.st->bb = a.st->rr_true = 0.0;
+        }
+        return;
+    }
+    // p = r: every read of x in the window is behind a barrier
+    phase();
+#pragma unroll
+    for (int u = 0; u < RPT; ++u)
+        if (row_of(u) < end) s_p[row_of(u) - lo + g.own] = r[u];
+    update_ends(a.r, [](double, double v) { return v; });
+    int status = kDoneMaxit, k = 0;
+    Entries first = entries(row_of(0));
+    for (;;) {
+        if (stop_test(rho, bb, a.tol)) {
+            status = kDoneConverged;
+            break;
+        }
+        if (k >= a.maxit) break;
+        __syncthreads();
+        acc = 0.0;
+        phase();
+        for_products(first, [&](int u, int i, double s) {
+            q[u] = s;
+            acc = fma(s_p[i - lo + g.own], s, acc);
+        });
+        double pq;
+        if (!grid_sum<NT, false>(a, acc, no++, S, pq)) return;
+        if (!(pq > 0.0) || !isfinite(pq)) {
+            status = kDoneBreakdown;
+            break;
+        }
+        const double alpha = rho / pq;
+        acc = 0.0;
+        phase();
+#pragma unroll
+        for (int u = 0; u < RPT; ++u) {
+            const int i = row_of(u);
+            if (i < end) {
+                x[u] = fma(alpha, s_p[i - lo + g.own], x[u]);
+                r[u] = fma(-alpha, q[u], r[u]);
+                acc = fma(r[u], r[u], acc);
+                if (shared(i)) store_agent(elem(a.r, i), r[u]);
+            }
+        }
+        ++k;
+        first = entries(row_of(0));   // under way during the sum
+        double rr;
+        if (!grid_sum<NT, true>(a, acc, no++, S, rr)) return;
+        const double beta = rr / rho;
+        rho = rr;
+        update_ends(a.r, [beta](double p, double v) { return fma(beta, p, v); });
+        phase();
+#pragma unroll
+        for (int u = 0; u < RPT; ++u) {
+            const int i = row_of(u);
+            if (i < end) {
+                double &p = s_p[i - lo + g.own];
+                p = fma(beta, p, r[u]);
+            }
+        }
+    }
+    // the solution, and the true residual b - A x
+    phase();
+#pragma unroll
+    for (int u = 0; u < RPT; ++u)
+        if (row_of(u) < end) store_agent(elem(a.x, row_of(u)), x[u]);
+    double rr_true;
+    if (!grid_sum<NT, true>(a, 0.0, no++, S, rr_true)) return;
+    phase();
+#pragma unroll
+    for (int u = 0; u < RPT; ++u)
+        if (row_of(u) < end) s_p[row_of(u) - lo + g.own] = x[u];
+    update_ends(a.x, [](double, double v) { return v; });
+    __syncthreads();
+    acc = 0.0;
+    phase();
+    for_products(entries(row_of(0)), [&](int, int i, double s) {
+        const double v = a.b[i] - s;
+        acc = fma(v, v, acc);
+    });
+    if (!grid_sum<NT, false>(a, acc, no++, S, rr_true)) return;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        a.st->iter = k;
+        a.st->done = status;
+        a.st->rho[0] = a.st->rr = rho;
+        a.st->bb = bb;
+        a.st->rr_true = rr_true;
+    }
+}
+
+struct WindowFn {
+    const void *fn;
+    int threads;
+};
+
+template <int W, bool KONST>
+WindowFn window_fn_of(int rows) {
+#define CGMI_WINDOW(NT, RPT) \
+    if (rows <= NT * RPT) return {reinterpret_cast<const void *>(k_cg_window<NT, RPT, W, KONST>), NT}
+    // 1024 threads as long as the rows fit their 128 registers; 512 lost to
+    // them there (1024^2 diffusion 13.2 against 12.3 us per iteration) and won
+    // beyond (1500 x 1401: 21.7 against 25.3 with 12 rows per thread, spilled)
+    CGMI_WINDOW(1024, 2);
+    CGMI_WINDOW(1024, 4);
+    CGMI_WINDOW(1024, 6);
+    CGMI_WINDOW(1024, 8);
+    if constexpr (W <= 5) CGMI_WINDOW(512, 20);   // 7: its window does not fit LDS there
+#undef CGMI_WINDOW
+    return {nullptr, 0};
+}
+
+WindowFn window_fn(const StenGlobal &C, int rows) {
+    if (C.width == 3) return C.konst ? window_fn_of<3, true>(rows) : window_fn_of<3, false>(rows);
+    if (C.width == 5) return C.konst ? window_fn_of<5, true>(rows) : window_fn_of<5, false>(rows);
+    if (C.width == 7) return C.konst ? window_fn_of<7, true>(rows) : window_fn_of<7, false>(rows);
+    return {nullptr, 0};
+}
 
 const void *resident_fn(int max_row_len) {
     return max_row_len <= 5 ? reinterpret_cast<const void *>(k_cg_resident<kNT, 5>)
@@ -302,6 +533,63 @@ hipError_t launch_cg_resident(const ResidentArgs &a, int32_t max_row_len, int cu
     ResidentArgs args = a;
     void *params[] = {&args};
     return hipLaunchCooperativeKernel(resident_fn(max_row_len), dim3(groups), dim3(kNT), params, 0, s);
+}
+
+bool window_shape(int32_t n, const StenGlobal &C, int cus, WindowArgs &g) {
+    if (n <= 0 || C.width == 0) return false;
+    const int groups_max = std::min(cus, kResidentMaxGroups);
+    const int64_t rows = std::max<int64_t>(1024, ((int64_t)(n + groups_max - 1) / groups_max + kWave - 1) / kWave * kWave);
+    if (rows > kWindowEntries) return false;
+    g.rows = (int32_t)rows;
+    g.groups = (int32_t)((n + rows - 1) / rows);
+    g.sten = C;
+    if (!window_fn(C, g.rows).fn) return false;
+    g.head = std::max(0, C.offs[C.width - 1]);
+    g.tail = g.rows + std::min(0, C.offs[0]);
+    // the rows moved by every offset, and the rows themselves; ascending
+    int32_t moved[kSliceMaxWidth + 1];
+    int count = 0;
+    bool own = false;
+    for (int e = 0; e < C.width; ++e) {
+        if (!own && C.offs[e] >= 0) {
+            if (C.offs[e] > 0) moved[count++] = 0;
+            own = true;
+        }
+        moved[count++] = C.offs[e];
+    }
+    if (!own) moved[count++] = 0;
+    g.nseg = 0;
+    int64_t entries = 0;
+    for (int k = 0; k < count; ++k) {
+        WindowSegment *const last = g.nseg ? &g.seg[g.nseg - 1] : nullptr;
+        if (last && moved[k] <= (int64_t)last->start + last->len) {
+            entries += moved[k] + rows - ((int64_t)last->start + last->len);
+            last->len = (int32_t)(moved[k] + rows - last->start);
+        } else {
+            if (entries > kWindowEntries) return false;
+            g.seg[g.nseg++] = {moved[k], (int32_t)rows, (int32_t)entries};
+            entries += rows;
+        }
+        const WindowSegment &in = g.seg[g.nseg - 1];
+        const int32_t at = in.base + (moved[k] - in.start);
+        if (moved[k] == 0) g.own = at;
+        for (int e = 0; e < C.width; ++e)
+            if (C.offs[e] == moved[k]) g.disp[e] = at;
+    }
+    g.entries = (int32_t)std::min<int64_t>(entries, INT32_MAX);
+    return entries <= kWindowEntries;
+}
+
+hipError_t launch_cg_window(const ResidentArgs &a, const WindowArgs &g, hipStream_t s) {
+    const WindowFn k = window_fn(g.sten, g.rows);
+    if (!k.fn) return hipErrorInvalidValue;
+    const size_t lds = sizeof(double) * (size_t)g.entries;
+    const hipError_t e = hipFuncSetAttribute(k.fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    ResidentArgs args = a;
+    WindowArgs gs = g;
+    void *params[] = {&args, &gs};
+    return hipLaunchCooperativeKernel(k.fn, dim3(g.groups), dim3(k.threads), params, (unsigned)lds, s);
 }
 
 }  // namespace cgmi
