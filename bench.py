@@ -779,7 +779,7 @@ def bench_learned(args) -> int:
         s.set_opts(profile=0, precond=precond, fuse_dir=args.fuse_dir)
         times, setups = [], []
         res = None
-        spmv_us = None
+        spmv_us = pres = None
         for k in range(warm + reps):
             x = x0.clone()
             torch.cuda.synchronize()
@@ -804,7 +804,7 @@ def bench_learned(args) -> int:
                      "solve_seconds": float(np.mean(times)), "setup_seconds": float(np.mean(setups)),
                      "iterations": res["iterations"], "status": res["code"], "fell_back": res["fell_back"],
                      "rel_res_true": res["rel_res_true"], "rel_err_vs_xstar": err,
-                     "fused_dir": res["fused_dir"]}
+                     "fused_dir": (pres or res)["fused_dir"]}   # of the solve whose SpMV was timed
         if spmv_us is not None:
             out[name]["spmv_us"] = spmv_us
             out[name]["spmv_launches_timed"] = pres["n_spmv"]

@@ -101,11 +101,12 @@ typedef struct cg_opts {
                               kernel; larger ones run it in one cooperative
                               launch, if their rows have at most 7 entries and
                               number at most 1024 per compute unit, or if they
-                              form a grid of 3, 5 or 7 points whose share of a
-                              compute unit fits its registers and LDS (up to
-                              about 10,000 rows), and the tiling, grid and
-                              fusion options below and profile are left
-                              automatic or off; 0: always several kernels  */
+                              form a grid of 3, 5 or 7 points (with a factor:
+                              5) whose share of a compute unit fits its
+                              registers and LDS (up to about 10,000 rows,
+                              7,000 with a factor), where profile is off,
+                              fuse_dir automatic and spmv_kind 0 or 6;
+                              0: always several kernels                    */
     int32_t spmv_grid;     /* workgroups of the SpMV kernels (0: automatic)      */
     int32_t spmv_kind;     /* SpMV tiling: 0 automatic, 1 vector CSR row-length
                               bins (L lanes per row), 2 stream tiles (runs of

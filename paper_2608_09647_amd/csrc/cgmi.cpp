@@ -538,6 +538,53 @@ int status_of(int done) {
     }
 }
 
+// The result of a solve that ran in one launch, from the state it left.
+int one_launch_result(const DevState &s, double t_gpu, cg_result *res) {
+    const int status = status_of(s.done);
+    if (res) {
+        res->status = status;
+        res->iterations = s.iter;
+        res->converged = status == CG_OK;
+        res->rel_res_recur = s.bb > 0.0 ? std::sqrt(s.rr) / std::sqrt(s.bb) : 0.0;
+        res->rel_res_true = s.bb > 0.0 ? std::sqrt(s.rr_true) / std::sqrt(s.bb) : 0.0;
+        res->t_gpu = t_gpu;
+    }
+    return status;
+}
+
+// Whether a solve may take one cooperative launch: not where options ask for
+// parts of a multi-kernel solve (another tiling than the stencil slices the
+// launch is written for, a fusion, timed SpMVs).
+bool one_launch_wanted(const cg_handle *h, int precond) {
+    const cg_opts &o = h->opts;
+    if (!o.small_path || o.precision != CG_PREC_FP64 || o.precond != precond || h->shared_p()) return false;
+    return !o.profile && (o.spmv_kind == 0 || o.spmv_kind == 6) && o.fuse_dir == CG_FUSE_AUTO;
+}
+
+// What every one-launch solve is given; words: the exchanged sums, zeroed here.
+int one_launch_args(cg_handle *h, const double *b, double *x, double tol, int32_t maxit, int groups, double *r,
+                    double *words, DevState *state, ResidentArgs &a) {
+    a = ResidentArgs{};
+    a.n = h->n;
+    a.rp = h->A.d_rp;
+    a.ci = h->A.d_ci;
+    a.val = h->A.d_val;
+    a.b = b;
+    a.x = x;
+    a.r = r;
+    a.words = reinterpret_cast<uint64_t *>(words);
+    a.err = reinterpret_cast<int32_t *>(a.words + resident_words(groups) - 1);
+    a.st = state;
+    a.tol = tol;
+    a.maxit = maxit;
+    int rate_khz = 0;
+    if (hipDeviceGetAttribute(&rate_khz, hipDeviceAttributeWallClockRate, h->dev) != hipSuccess || rate_khz <= 0)
+        rate_khz = 100000;
+    a.timeout_ticks = (int64_t)rate_khz * 1000 * 20;   // 20 s
+    HIP_TRY(hipMemsetAsync(a.words, 0, sizeof(uint64_t) * resident_words(groups), h->stream));
+    return CG_OK;
+}
+
 }  // namespace cgmi
 
 // ---------------------------------------------------------------------------
@@ -655,29 +702,6 @@ int32_t max_row_len(cg_handle *h) {
     return h->max_row_len;
 }
 
-// The result of a solve that ran in one launch, from the state it left.
-int one_launch_result(const DevState &s, double t_gpu, cg_result *res) {
-    const int status = status_of(s.done);
-    if (res) {
-        res->status = status;
-        res->iterations = s.iter;
-        res->converged = status == CG_OK;
-        res->rel_res_recur = s.bb > 0.0 ? std::sqrt(s.rr) / std::sqrt(s.bb) : 0.0;
-        res->rel_res_true = s.bb > 0.0 ? std::sqrt(s.rr_true) / std::sqrt(s.bb) : 0.0;
-        res->t_gpu = t_gpu;
-    }
-    return status;
-}
-
-// Whether the automatic choices may take one cooperative launch: the options
-// that name a multi-kernel solve's parts leave it.
-bool one_launch_wanted(const cg_handle *h) {
-    const cg_opts &o = h->opts;
-    if (!o.small_path || o.precision != CG_PREC_FP64 || o.precond != CG_PC_NONE || h->shared_p()) return false;
-    if (o.profile || o.spmv_kind || o.spmv_grid || o.spmv_colblock || o.fuse_dir != CG_FUSE_AUTO) return false;
-    return true;
-}
-
 int solve_plain(cg_handle *h, const PlainWork &w, const double *b, double *x, double tol, int32_t maxit,
                 cg_result *res) {
     const int32_t n = h->n;
@@ -717,7 +741,7 @@ int solve_plain(cg_handle *h, const PlainWork &w, const double *b, double *x, do
     WindowArgs win{};
     int32_t groups = 0, row_len = 0;
     bool window = false;
-    if (one_launch_wanted(h)) {
+    if (one_launch_wanted(h, CG_PC_NONE)) {
         // a row per thread where all rows fit that: 64^3 Poisson 7.0 us per
         // iteration against 8.2 with the window, 512^2 diffusion 6.5 against
         // 7.4 (rows first: the longest one takes a pass over the matrix)
@@ -732,25 +756,10 @@ int solve_plain(cg_handle *h, const PlainWork &w, const double *b, double *x, do
         }
     }
     if (groups > 0) {
-        ResidentArgs a{};
-        a.n = n;
-        a.rp = h->A.d_rp;
-        a.ci = h->A.d_ci;
-        a.val = h->A.d_val;
-        a.b = b;
-        a.x = x;
-        a.r = w.r;
-        a.words = reinterpret_cast<uint64_t *>(w.q);
-        a.err = reinterpret_cast<int32_t *>(a.words + resident_words(groups) - 1);
-        a.st = w.state;
-        a.tol = tol;
-        a.maxit = maxit;
-        int rate_khz = 0;
-        if (hipDeviceGetAttribute(&rate_khz, hipDeviceAttributeWallClockRate, h->dev) != hipSuccess || rate_khz <= 0)
-            rate_khz = 100000;
-        a.timeout_ticks = (int64_t)rate_khz * 1000 * 20;   // 20 s
+        ResidentArgs a;
         const double t0 = now();
-        HIP_TRY(hipMemsetAsync(a.words, 0, sizeof(uint64_t) * resident_words(groups), st));
+        const int rc0 = one_launch_args(h, b, x, tol, maxit, groups, w.r, w.q, w.state, a);
+        if (rc0) return rc0;
         win.val = h->A.d_st_val;
         win.mask = h->A.d_st_mask;
         if ((window ? launch_cg_window(a, win, st) : launch_cg_resident(a, row_len, h->cus, st)) ==

@@ -292,6 +292,10 @@ inline bool fuse_dir_wanted(const cg_handle *h, bool pcg) {
     return h->opts.fuse_dir == CG_FUSE_ON || (h->opts.fuse_dir == CG_FUSE_AUTO && h->m <= lim);
 }
 int status_of(int done);
+bool one_launch_wanted(const cg_handle *h, int precond);
+int one_launch_result(const DevState &s, double t_gpu, cg_result *res);
+int one_launch_args(cg_handle *h, const double *b, double *x, double tol, int32_t maxit, int groups, double *r,
+                    double *words, DevState *state, ResidentArgs &a);
 // Preconditioned solve (fsai.cpp); on a breakdown it returns CG_EBREAKDOWN
 // with x untouched.
 int solve_gpu_pcg(cg_handle *h, const double *b, double *x, double tol, int32_t maxit,

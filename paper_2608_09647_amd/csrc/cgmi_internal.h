@@ -391,6 +391,22 @@ struct WindowArgs {
 bool window_shape(int32_t n, const StenGlobal &C, int cus, WindowArgs &g);
 hipError_t launch_cg_window(const ResidentArgs &a, const WindowArgs &g, hipStream_t s);
 
+// Preconditioned CG of a 5-point operator with a factor on its lower part.
+constexpr int kPcgReach = 2048;           // the largest offset at most
+struct PcgWindowArgs {
+    StenGlobal sten;          // A
+    const double *val;        // A's stencil slices (konst: null)
+    const uint8_t *mask;      // A's slots of every row
+    const double *g_val, *gt_val;     // G's and G^T's stencil slices
+    int32_t g_offs[3], gt_offs[3];
+    double *z;                // [n] exchanged as r is
+    int32_t groups, rows;     // as in WindowArgs
+    int32_t reach;            // window entries on either side of the rows
+};
+bool pcg_window_shape(int32_t n, const StenGlobal &A, const StenGlobal &G, const StenGlobal &GT, int cus,
+                      PcgWindowArgs &g);
+hipError_t launch_pcg_window(const ResidentArgs &a, const PcgWindowArgs &g, hipStream_t s);
+
 // Gather / scatter of p entries for the halo exchange.
 hipError_t launch_gather(int32_t cnt, const int32_t *idx, const double *src, double *dst,
                          hipStream_t s);

@@ -241,6 +241,29 @@ int solve_gpu_pcg(cg_handle *h, const double *b, double *x, double tol, int32_t 
                   cg_result *res) {
     const int32_t n = h->n;
     hipStream_t st = h->stream;
+    PcgWindowArgs win{};
+    if (one_launch_wanted(h, CG_PC_FSAI) && h->A.sched.kind == kTileStencil && h->G.sched.kind == kTileStencil &&
+        h->GT.sched.kind == kTileStencil && h->G.d_st_val && h->GT.d_st_val &&
+        pcg_window_shape(n, h->A.stg, h->G.stg, h->GT.stg, h->cus, win) &&
+        resident_words(win.groups) <= (size_t)n) {   // (the words take q's place)
+        win.val = h->A.d_st_val;
+        win.mask = h->A.d_st_mask;
+        win.g_val = h->G.d_st_val;
+        win.gt_val = h->GT.d_st_val;
+        win.z = h->d_z;
+        ResidentArgs a;
+        const double t0 = now();
+        int rc = one_launch_args(h, b, x, tol, maxit, win.groups, h->d_r, h->d_q, h->d_state, a);
+        if (rc) return rc;
+        if (launch_pcg_window(a, win, st) == hipSuccess) {
+            rc = gpu_state_read(h);
+            if (rc) return rc;
+            if (h->h_state->done == kDoneRunning)
+                return fail(CG_EDEVICE, "a wait of the one-launch solve timed out");
+            return one_launch_result(*h->h_state, now() - t0, res);
+        }
+        (void)hipGetLastError();   // not launchable here: the kernels below
+    }
     const int Ga = h->A.grid, Gg = h->G.grid, Gt = h->GT.grid, Gv = h->vec_grid;
     // the fused r/t kernel: one row per thread (CSR), or two 64-row slices per
     // wavefront (G in stencil slices; the grid a multiple of 8)

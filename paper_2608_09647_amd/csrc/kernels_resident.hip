@@ -30,6 +30,7 @@
 
 #include <algorithm>
 #include <climits>
+#include <cstdlib>
 #include <type_traits>
 
 #include "cg_device.h"
@@ -310,8 +311,9 @@ __global__ __launch_bounds__(NT) void k_cg_window(ResidentArgs a, WindowArgs g) 
     // whether another workgroup's rows have this one as a column
     auto shared = [&](int i) { return i - lo < g.head || i - lo >= g.tail; };
     auto phase = [&] { asm volatile("" : "+v"(row0)); };
-    // a row's entries (constant ones: which it has); a row past the end reads
-    // those of the last slice
+    // a row's entries (constant ones: which it has); loaded for every row, so
+    // that the loads in flight can be counted, but past the end all lanes read
+    // one place (the rows there are the next workgroup's)
     struct Entries {
         double v[KONST ? 1 : W];
         uint32_t have;
@@ -319,9 +321,9 @@ __global__ __launch_bounds__(NT) void k_cg_window(ResidentArgs a, WindowArgs g) 
     auto entries = [&](int i) {
         Entries E;
         if (KONST) {
-            E.have = g.mask[min(i, n - 1)];
+            E.have = g.mask[i < end ? i : 0];
         } else {
-            const double *const v = g.val + ((int64_t)min(i / kWave, (n - 1) / kWave) * W * kWave + lane);
+            const double *const v = g.val + (i < end ? (int64_t)(i / kWave) * (W * kWave) + lane : 0);
 #pragma unroll
             for (int e = 0; e < W; ++e) E.v[KONST ? 0 : e] = v[e * kWave];
         }
@@ -486,6 +488,256 @@ __global__ __launch_bounds__(NT) void k_cg_window(ResidentArgs a, WindowArgs g) 
     }
 }
 
+// Preconditioned CG, z = G^T (G r), for a 5-point A with a factor on its lower
+// part, as above with three sums per iteration: p^T q, r^T r (behind it the r
+// of other workgroups) and r^T z (their z, from which the copies of p outside
+// the workgroup's rows advance).  One window holds p, another r and, once it
+// has been used, t = G r; t of the rows above the workgroup's, which G^T needs,
+// is computed again here.  Us per iteration, three kernels and here: 1024^2
+// diffusion 43.5 and 23.7 (98 MB of values, 15 us at 6.4 TB/s), 777 x 700 31.9
+// and 18.4, 1300^2 73.6 and 32.4, 150 x 133 17.1 and 8.5.
+template <int RPT, bool KONST>
+__global__ __launch_bounds__(kNT) void k_pcg_window(ResidentArgs a, PcgWindowArgs g) {
+    constexpr int W = 5, RT = RPT + kPcgReach / kNT;   // rows of t: the reach more
+    extern __shared__ double lds[];   // two windows of g.rows + 2 g.reach
+    __shared__ ResidentShared<kNT> S;
+    if (threadIdx.x == 0) S.ok = 1;
+    if (blockIdx.x == 0 && threadIdx.x == 0) a.st->done = kDoneRunning;   // left so by an abandoned launch
+    const int n = a.n, lo = blockIdx.x * g.rows, end = min(n, lo + g.rows), t_end = min(n, lo + g.rows + g.reach);
+    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave, window = g.rows + 2 * g.reach;
+    double *const s_p = lds, *const s_r = lds + window;
+    int row0 = lo + w * kWave + lane;   // as in k_cg_window
+    auto row_of = [&](int u) { return row0 + u * kNT; };
+    auto phase = [&] { asm volatile("" : "+v"(row0)); };
+    auto shared = [&](int i) { return i - lo < g.reach || i - lo >= g.rows - g.reach; };
+    auto at = [&](double *win, int i) -> double & { return win[i - lo + g.reach]; };
+    // sets the entries of a window outside the workgroup's rows to f(old, v)
+    auto update_ends = [&](double *win, const double *v, auto f) {
+        for (int k0 = threadIdx.x; k0 < 2 * g.reach; k0 += 4 * kNT) {
+            double x4[4];
+            auto col = [&](int j) {
+                const int k = k0 + j * kNT;
+                return k < g.reach ? lo - g.reach + k : lo + g.rows + k - g.reach;
+            };
+            auto other = [&](int j) { return k0 + j * kNT < 2 * g.reach && col(j) >= 0 && col(j) < n; };
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (other(j)) x4[j] = load_agent(elem(v, col(j)));
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (other(j)) at(win, col(j)) = f(at(win, col(j)), x4[j]);
+        }
+    };
+    struct Slots {
+        double v[W];
+        uint32_t have;
+    };
+    auto slots = [&](const double *val, int width, int i, int limit) {   // as entries in k_cg_window (777 x 700: 23.2 to 18.4)
+        Slots E;
+        const double *const v = val + (i < limit ? (int64_t)(i / kWave) * (width * kWave) + lane : 0);
+#pragma unroll
+        for (int e = 0; e < W; ++e)
+            if (e < width) E.v[e] = v[e * kWave];
+        return E;
+    };
+    auto a_slots = [&](int i) {
+        if (!KONST) return slots(g.val, W, i, end);
+        Slots E;
+        E.have = g.mask[i < end ? i : 0];
+#pragma unroll
+        for (int e = 0; e < W; ++e) E.v[e] = (E.have >> e) & 1u ? g.sten.val[e] : 0.0;
+        return E;
+    };
+    auto g_slots = [&](int i) { return slots(g.g_val, 3, i, t_end); };
+    auto gt_slots = [&](int i) { return slots(g.gt_val, 3, i, end); };
+    auto dot = [&](const Slots &E, int width, const int32_t *offs, double *win, int i) {
+        double s = 0.0;
+#pragma unroll
+        for (int e = 0; e < W; ++e)
+            if (e < width) s = add_rounded(s, E.v[e], at(win, i + offs[e]));
+        return s;
+    };
+    // z = G^T (G r) of the workgroup's rows into z, r^T z into acc; r of the
+    // window's ends is read behind the sum before.  first: G's slots of row 0
+    double x[RPT], r[RPT], z[RPT];
+    double acc = 0.0;
+    auto precondition = [&](const Slots &first) {
+        update_ends(s_r, a.r, [](double, double v) { return v; });
+        phase();
+#pragma unroll
+        for (int u = 0; u < RPT; ++u)
+            if (row_of(u) < end) at(s_r, row_of(u)) = r[u];
+        __syncthreads();
+        double t[RT];
+        Slots E = first;
+        phase();
+#pragma unroll
+        for (int u = 0; u < RT; ++u) {
+            const Slots cur = E;
+            if (u + 1 < RT) E = g_slots(row_of(u + 1));
+            t[u] = row_of(u) < t_end ? dot(cur, 3, g.g_offs, s_r, row_of(u)) : 0.0;
+        }
+        E = gt_slots(row_of(0));
+        __syncthreads();
+        phase();
+#pragma unroll
+        for (int u = 0; u < RT; ++u)
+            if (row_of(u) < t_end) at(s_r, row_of(u)) = t[u];
+        __syncthreads();
+        acc = 0.0;
+        phase();
+#pragma unroll
+        for (int u = 0; u < RPT; ++u) {
+            const Slots cur = E;
+            if (u + 1 < RPT) E = gt_slots(row_of(u + 1));
+            const int i = row_of(u);
+            if (i < end) {
+                z[u] = dot(cur, 3, g.gt_offs, s_r, i);
+                acc = fma(r[u], z[u], acc);
+                if (shared(i)) store_agent(elem(g.z, i), z[u]);
+            }
+        }
+    };
+    for (int k = threadIdx.x; k < window; k += kNT) {
+        const int c = lo - g.reach + k;
+        s_p[k] = c >= 0 && c < n ? a.x[c] : 0.0;
+        s_r[k] = 0.0;
+    }
+    __syncthreads();
+    double accb = 0.0;
+#pragma unroll
+    for (int u = 0; u < RPT; ++u) {
+        const int i = row_of(u);
+        x[u] = r[u] = z[u] = 0.0;
+        if (i < end) {
+            const double bi = a.b[i];
+            x[u] = at(s_p, i);
+            r[u] = bi - dot(a_slots(i), W, g.sten.offs, s_p, i);
+            acc = fma(r[u], r[u], acc);
+            accb = fma(bi, bi, accb);
+            if (shared(i)) store_agent(elem(a.r, i), r[u]);
+        }
+    }
+    uint32_t no = 1;
+    double rr, bb, rho;
+    if (!grid_sum<kNT, true>(a, acc, no++, S, rr)) return;
+    if (!grid_sum<kNT, false>(a, accb, no++, S, bb)) return;
+    precondition(g_slots(row_of(0)));
+    if (!grid_sum<kNT, true>(a, acc, no++, S, rho)) return;
+    // p = z
+    phase();
+#pragma unroll
+    for (int u = 0; u < RPT; ++u)
+        if (row_of(u) < end) at(s_p, row_of(u)) = z[u];
+    update_ends(s_p, g.z, [](double, double v) { return v; });
+    int status = kDoneRunning, k = 0;
+    if (stop_test(rr, bb, a.tol) || bb == 0.0) status = kDoneConverged;
+    else if (a.maxit <= 0) status = kDoneMaxit;
+    Slots first = a_slots(row_of(0));
+    while (status == kDoneRunning) {
+        __syncthreads();
+        double q[RPT];
+        acc = 0.0;
+        phase();
+#pragma unroll
+        for (int u = 0; u < RPT; ++u) {
+            const Slots cur = first;
+            if (u + 1 < RPT) first = a_slots(row_of(u + 1));
+            const int i = row_of(u);
+            q[u] = 0.0;
+            if (i < end) {
+                q[u] = dot(cur, W, g.sten.offs, s_p, i);
+                acc = fma(at(s_p, i), q[u], acc);
+            }
+        }
+        double pq;
+        if (!grid_sum<kNT, false>(a, acc, no++, S, pq)) return;
+        if (!(pq > 0.0) || !isfinite(pq)) {
+            status = kDoneBreakdown;
+            break;
+        }
+        const double alpha = rho / pq;
+        acc = 0.0;
+        phase();
+#pragma unroll
+        for (int u = 0; u < RPT; ++u) {
+            const int i = row_of(u);
+            if (i < end) {
+                x[u] = fma(alpha, at(s_p, i), x[u]);
+                r[u] = fma(-alpha, q[u], r[u]);
+                acc = fma(r[u], r[u], acc);
+                if (shared(i)) store_agent(elem(a.r, i), r[u]);
+            }
+        }
+        ++k;
+        const Slots g0 = g_slots(row_of(0));   // under way during the sum
+        if (!grid_sum<kNT, true>(a, acc, no++, S, rr)) return;
+        precondition(g0);
+        first = a_slots(row_of(0));
+        double rz;
+        if (!grid_sum<kNT, true>(a, acc, no++, S, rz)) return;
+        const double beta = rz / rho;
+        rho = rz;
+        if ((!(rz > 0.0) || !isfinite(rz)) && rr != 0.0) status = kDoneBreakdown;
+        else if (stop_test(rr, bb, a.tol)) status = kDoneConverged;
+        else if (k >= a.maxit) status = kDoneMaxit;
+        if (status != kDoneRunning) break;
+        update_ends(s_p, g.z, [beta](double p, double v) { return fma(beta, p, v); });
+        phase();
+#pragma unroll
+        for (int u = 0; u < RPT; ++u)
+            if (row_of(u) < end) at(s_p, row_of(u)) = fma(beta, at(s_p, row_of(u)), z[u]);
+    }
+    // b = 0: the solution is x = 0; after a breakdown x stays as it was given
+    double rr_true = 0.0;
+    if (status != kDoneBreakdown) {
+        phase();
+#pragma unroll
+        for (int u = 0; u < RPT; ++u)
+            if (row_of(u) < end) store_agent(elem(a.x, row_of(u)), bb == 0.0 ? 0.0 : x[u]);
+        if (!grid_sum<kNT, true>(a, 0.0, no++, S, rr_true)) return;
+        phase();
+#pragma unroll
+        for (int u = 0; u < RPT; ++u)
+            if (row_of(u) < end) at(s_p, row_of(u)) = x[u];
+        update_ends(s_p, a.x, [](double, double v) { return v; });
+        __syncthreads();
+        acc = 0.0;
+        phase();
+#pragma unroll
+        for (int u = 0; u < RPT; ++u) {
+            const int i = row_of(u);
+            if (i < end) {
+                const double v = a.b[i] - dot(a_slots(i), W, g.sten.offs, s_p, i);
+                acc = fma(v, v, acc);
+            }
+        }
+        if (!grid_sum<kNT, false>(a, acc, no++, S, rr_true)) return;
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        a.st->iter = k;
+        a.st->done = status;
+        a.st->rho[0] = rho;
+        a.st->rr = rr;
+        a.st->bb = bb;
+        a.st->rr_true = rr_true;
+    }
+}
+
+const void *pcg_window_fn(int rows, bool konst) {
+#define CGMI_PCG_WINDOW(RPT)                                                            \
+    if (rows <= kNT * RPT)                                                              \
+    return konst ? reinterpret_cast<const void *>(k_pcg_window<RPT, true>)              \
+                 : reinterpret_cast<const void *>(k_pcg_window<RPT, false>)
+    CGMI_PCG_WINDOW(1);
+    CGMI_PCG_WINDOW(2);
+    CGMI_PCG_WINDOW(4);
+    CGMI_PCG_WINDOW(6);
+    CGMI_PCG_WINDOW(7);
+#undef CGMI_PCG_WINDOW
+    return nullptr;
+}
+
 struct WindowFn {
     const void *fn;
     int threads;
@@ -590,6 +842,40 @@ hipError_t launch_cg_window(const ResidentArgs &a, const WindowArgs &g, hipStrea
     WindowArgs gs = g;
     void *params[] = {&args, &gs};
     return hipLaunchCooperativeKernel(k.fn, dim3(g.groups), dim3(k.threads), params, (unsigned)lds, s);
+}
+
+bool pcg_window_shape(int32_t n, const StenGlobal &A, const StenGlobal &G, const StenGlobal &GT, int cus,
+                      PcgWindowArgs &g) {
+    if (n <= 0 || A.width != 5 || G.width != 3 || GT.width != 3 || G.konst || GT.konst) return false;
+    int32_t reach = 0;
+    for (int e = 0; e < 5; ++e) reach = std::max(reach, std::abs(A.offs[e]));
+    for (int e = 0; e < 3; ++e) {
+        if (G.offs[e] > 0 || GT.offs[e] != -G.offs[2 - e]) return false;
+        reach = std::max(reach, -G.offs[e]);
+    }
+    if (reach > kPcgReach) return false;
+    const int groups_max = std::min(cus, kResidentMaxGroups);
+    const int64_t rows = std::max<int64_t>(kNT, ((int64_t)(n + groups_max - 1) / groups_max + kWave - 1) / kWave * kWave);
+    if (2 * (rows + 2 * reach) > kWindowEntries || !pcg_window_fn((int)rows, A.konst != 0)) return false;
+    g.sten = A;
+    std::copy(G.offs, G.offs + 3, g.g_offs);
+    std::copy(GT.offs, GT.offs + 3, g.gt_offs);
+    g.rows = (int32_t)rows;
+    g.reach = reach;
+    g.groups = (int32_t)((n + rows - 1) / rows);
+    return true;
+}
+
+hipError_t launch_pcg_window(const ResidentArgs &a, const PcgWindowArgs &g, hipStream_t s) {
+    const void *fn = pcg_window_fn(g.rows, g.sten.konst != 0);
+    if (!fn) return hipErrorInvalidValue;
+    const size_t lds = 2 * sizeof(double) * ((size_t)g.rows + 2 * (size_t)g.reach);
+    const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    ResidentArgs args = a;
+    PcgWindowArgs gs = g;
+    void *params[] = {&args, &gs};
+    return hipLaunchCooperativeKernel(fn, dim3(g.groups), dim3(kNT), params, (unsigned)lds, s);
 }
 
 }  // namespace cgmi

@@ -334,6 +334,49 @@ def test_pcg_fused_direction_update_is_bitwise(cg, maxit, tol):
     assert r0["n_spmv"] == r1["n_spmv"] == (min(maxit, r1["iterations"]) + 2) // 3
 
 
+@pytest.mark.parametrize("nx,ny,values", [
+    (33, 31, "field"),        # one workgroup, its last rows missing
+    (64, 32, "field"),        # two full ones
+    (300, 290, "field"),      # a row per thread, 85 workgroups
+    (2048, 131, "field"),     # two rows, the longest reach
+    (2049, 130, "field"),     # past it: separate kernels
+    (700, 777, "field"),      # four rows, some of them missing
+    (640, 700, "const"),
+    (1180, 1100, "field"),    # six
+    (1300, 1300, "field"),    # seven
+])
+def test_pcg_one_cooperative_launch_matches_separate_kernels(cg, nx, ny, values):
+    """Preconditioned CG in one launch against the separate kernels (held to
+    the oracle by the tests around): fixed work within 1e-9 (rounding differs
+    in the sums alone), the same iterations within max(2, 5%), the same bits
+    from a second run, and the ends of a solve."""
+    A = I.poisson2d(nx, ny) if values == "const" else field(nx, ny, 61)
+    n = A.n
+    rng = np.random.default_rng(7)
+    b, x0 = A.scipy() @ rng.uniform(-1, 1, n), rng.uniform(-1, 1, n)
+    with cg.Solver(A) as s:
+        s.fsai_classic()
+        s.set_opts(precond=cg.PC_FSAI)
+        out = {}
+        for small in (1, 0):
+            s.set_opts(small_path=small)
+            x, res = s.solve(dev(b), dev(x0), tol=0.0, maxit=12)
+            assert res["code"] == cg.CG_MAXIT and res["iterations"] == 12 and res["fell_back"] == 0
+            _, conv = s.solve(dev(b), tol=1e-8, maxit=5000)
+            assert conv["code"] == cg.CG_OK and conv["rel_res_true"] <= 1.01e-8
+            out[small] = host(x), res, conv["iterations"]
+        assert np.linalg.norm(out[1][0] - out[0][0]) <= 1e-9 * np.linalg.norm(out[0][0])
+        assert abs(out[1][1]["rel_res_true"] - out[0][1]["rel_res_true"]) <= 1e-9 * out[0][1]["rel_res_true"]
+        assert abs(out[1][2] - out[0][2]) <= max(2, 0.05 * out[0][2])
+        s.set_opts(small_path=1)
+        x, _ = s.solve(dev(b), dev(x0), tol=0.0, maxit=12)
+        assert np.array_equal(host(x), out[1][0])
+        x, res = s.solve(dev(np.zeros(n)), dev(x0))
+        assert res["code"] == cg.CG_OK and res["iterations"] == 0 and not host(x).any()
+        x, res = s.solve(dev(b), dev(x0), maxit=0)
+        assert res["code"] == cg.CG_MAXIT and np.array_equal(host(x), x0)
+
+
 def test_pcg_breakdown_falls_back_to_plain_cg(cg):
     p = I.poisson2d_problem(24, seed=1)
     G = sp.identity(p.A.n, format="lil")
