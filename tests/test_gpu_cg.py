@@ -1245,6 +1245,30 @@ def test_global_stencil_forms(cg, n, offs, values):
     assert np.array_equal(out[1][0], out[2][0]) and out[1][1] == out[2][1]
 
 
+def spread_offsets(width, n):
+    half = [1 + 3 * k for k in range(width // 2)]
+    return tuple([-o for o in half[::-1] if o < n] + [0] + [o for o in half if o < n])
+
+
+@pytest.mark.parametrize("n,width", [
+    (1, 1), (511, 3), (512, 7), (400, 19), (513, 5), (1024, 7), (1000, 19), (1025, 7), (2048, 11), (2049, 5),
+    (4095, 5), (4096, 7), (3001, 9), (600, 41)])
+def test_one_workgroup_solve_at_its_edges(cg, n, width):
+    """The single-workgroup solve at the edges of its rows per thread and row
+    lengths held in registers: fixed work within 1e-9 of the oracle's
+    iterates (diagonally dominant systems), the same bits again."""
+    A = banded(n, spread_offsets(width, n), "random")
+    rng = np.random.default_rng(3)
+    b, x0 = A.scipy() @ rng.uniform(-1, 1, n), rng.uniform(-1, 1, n)
+    its = 1 if n == 1 else 12
+    ref = oracle.cg(A, b, x0=x0, tol=0.0, maxit=its)
+    with cg.Solver(A) as s:
+        runs = [s.solve(dev(b), dev(x0), tol=0.0, maxit=its) for _ in range(2)]
+    assert runs[0][1]["iterations"] == its
+    assert np.array_equal(host(runs[0][0]), host(runs[1][0]))
+    assert np.linalg.norm(host(runs[0][0]) - ref["x"]) <= 1e-9 * np.linalg.norm(ref["x"])
+
+
 def scattered(n, per_row, long_rows, seed=5):
     """Random columns over the whole vector, about per_row entries a row, a few
     rows of 1,500 entries, some empty rows (not symmetric: products only)."""
