@@ -178,7 +178,9 @@ typedef struct cg_opts {
                               preconditioned solves of at most 2,097,152 GPU
                               rows and plain ones of at most 262,144 (where
                               the launch and pass it saves outweigh the extra
-                              gathers), separate above.                        */
+                              gathers), separate above.  The automatic choice
+                              may run kernels that sum in another order (see
+                              small_path), ON and OFF agree bit for bit.       */
 } cg_opts;
 
 enum { CG_VECTORS_DEVICE = 0, CG_VECTORS_HOST = 1 };  /* cg_opts.vectors   */

@@ -25,7 +25,7 @@ LIB = os.path.join(PKG, "libcgmi.so")
 ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 
 HIP_SOURCES = ["kernels_cg.hip", "kernels_small.hip", "kernels_fsai.hip", "kernels_batch.hip", "kernels_util.hip",
-               "scratch.hip", "kernels_staged.hip", "kernels_resident.hip"]
+               "scratch.hip", "kernels_staged.hip", "kernels_resident.hip", "kernels_march.hip"]
 HOST_SOURCES = ["cgmi.cpp", "devmatrix.cpp", "fsai.cpp", "batch.cpp", "mmio.cpp", "staged.cpp"]
 
 HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

@@ -779,6 +779,10 @@ int solve_plain(cg_handle *h, const PlainWork &w, const double *b, double *x, do
     // x updated every other iteration from two p buffers (not with p in
     // shared host memory, whose one buffer the other side reads)
     const bool two_buf = w.p2 != nullptr;
+    CsrDev Ad = h->A.dev();
+    // (the sums of the walk are in its own order, and those of CG_FUSE_ON and
+    // CG_FUSE_OFF agree bit for bit)
+    Ad.march = h->opts.fuse_dir == CG_FUSE_AUTO ? 1 : 0;
     const bool fused = two_buf && fuse_dir_wanted(h, false) &&
                        spmv_dir_applies(h->A.dev(), h->A.sched, h->A.grid, w.p, w.r, w.p2, w.x, w.q);
     const double t0 = now();
@@ -808,7 +812,7 @@ int solve_plain(cg_handle *h, const PlainWork &w, const double *b, double *x, do
                 const int32_t kk = k + j;
                 if (sampled(kk)) HIP_TRY(hipEventRecord(ev[2 * j], st));
                 double *p_k = two_buf ? pbuf[kk & 1] : w.p;
-                HIP_TRY(launch_spmv(h->A.dev(), h->A.sched, Gs, p_k, w.q, p_k, nullptr, nullptr,
+                HIP_TRY(launch_spmv(Ad, h->A.sched, Gs, p_k, w.q, p_k, nullptr, nullptr,
                                     w.part_pq, setup_rr, setup_bb, w.state, kSpmvDot, kk == 0, st));
                 if (sampled(kk)) HIP_TRY(hipEventRecord(ev[2 * j + 1], st));
                 if (maxit == 0) break;
@@ -1505,7 +1509,9 @@ static int spmv_impl(cg_handle *h, const double *x, double *y) {
             HIP_TRY(hipMemsetAsync(y, 0, sizeof(double) * n, h->stream));
             return CG_OK;
         }
-        HIP_TRY(launch_spmv(h->A.dev(), h->A.sched, h->A.grid, x, y, nullptr, nullptr, nullptr, nullptr,
+        CsrDev Ad = h->A.dev();
+        Ad.march = 2;
+        HIP_TRY(launch_spmv(Ad, h->A.sched, h->A.grid, x, y, nullptr, nullptr, nullptr, nullptr,
                             no_partials(), no_partials(), nullptr, kSpmvPlain, 0, h->stream));
         return CG_OK;
     }

@@ -188,6 +188,7 @@ struct CsrDev {
     const uint8_t *st_fast;   //   its fast tiles, one byte per 128 rows
     const StagedDev<double> *st64;  // staged column segments (host memory; launch side only)
     const StagedDev<float> *st32;
+    int32_t march;            // launch side: 1 = products may walk the planes, also with the dot, 2 = without it
 };
 
 // Per-block operands of the column-blocked tiling (kept on the host by the
@@ -339,6 +340,16 @@ int small_path_max_rows();
 hipError_t launch_cg_small(int32_t n, const int32_t *rp, const int32_t *ci, const double *val,
                            const double *b, double *x, double tol, int32_t maxit, DevState *st,
                            int32_t max_row_len, hipStream_t s);
+
+// Products of a constant 7-point operator walked plane by plane
+// (kernels_march.hip): all columns in [0, m), p_own p itself or null; modes
+// kSpmvPlain and kSpmvDot without the test of iteration 0; one partial per
+// workgroup of the grid.
+constexpr int kMarchLine = 512;            // the second largest offset at most
+constexpr int32_t kMarchRows = 6 << 20;    // rows at least (see march_applies)
+bool march_applies(int32_t m, const StenGlobal &C, const double *p, const double *p_own);
+hipError_t launch_spmv_march(int32_t m, const StenGlobal &C, const uint8_t *mask, int grid, const double *p, double *q,
+                             double *out, const DevState *st, int mode, hipStream_t s);
 
 // Whole solve in one cooperative launch with a row per thread
 // (kernels_resident.hip).  Limits: a workgroup of 1024 threads per compute

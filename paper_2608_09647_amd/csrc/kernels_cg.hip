@@ -2003,6 +2003,9 @@ hipError_t launch_spmv(const CsrDev &A, const Schedule &S, int grid, const doubl
     if (A.m == 0) return hipSuccess;
     if (A.st64)
         return launch_spmv_staged(*A.st64, grid, p, q, p_own, b, p_dst, out_partials, in0, in1, st, mode, k0_check, s);
+    if (A.march && S.kind == kTileStencil && (mode == kSpmvPlain || (mode == kSpmvDot && !k0_check && A.march == 1)) &&
+        march_applies(A.m, A.stg, p, p_own))
+        return launch_spmv_march(A.m, A.stg, A.st_mask, grid, p, q, out_partials, st, mode, s);
     SpmvArgs<double> a{p, q, p_own, b, p_dst};
     if (S.kind == kTileColBlocked) {
         if (!A.cb || mode < kSpmvPlain || mode > kSpmvResidual) return hipErrorInvalidValue;

@@ -1245,6 +1245,32 @@ def test_global_stencil_forms(cg, n, offs, values):
     assert np.array_equal(out[1][0], out[2][0]) and out[1][1] == out[2][1]
 
 
+@pytest.mark.parametrize("n,offs", [
+    (6_291_456, (-8192, -512, -1, 0, 1, 512, 8192)),       # the smallest plane, whole tiles
+    (6_300_002, (-10_000, -77, -3, 0, 3, 77, 10_000)),     # no whole number of tiles, the last plane cut
+    (6_291_459, (-10_000, -100, -1, 0, 1, 100, 10_000)),   # odd: the other kernels
+    (6_400_000, (-1_600_000, -400, -1, 0, 1, 400, 1_600_000))])   # few planes
+def test_products_walked_by_planes(cg, n, offs):
+    """Constant 7-point operators above the caches: the product bit for bit
+    the oracle's (aligned and 8 bytes off), a solve within 1e-12 of the one
+    with separate kernels asked for (the p^T q sums differ in order alone)."""
+    A = banded(n, offs, "const")
+    x = np.random.default_rng(41).uniform(-1, 1, n)
+    ref = oracle.spmv(A, x)
+    with cg.Solver(A) as s:
+        s.set_opts(small_path=0)
+        assert np.array_equal(host(s.spmv(dev(x))), ref)
+        off = torch.zeros(n + 1, dtype=torch.float64, device="cuda")[1:]
+        assert np.array_equal(host(s.spmv(dev(x), off)), ref)
+        out = {}
+        for fuse in (cg.FUSE_AUTO, cg.FUSE_OFF):
+            s.set_opts(fuse_dir=fuse)
+            xs, res = s.solve(dev(ref), tol=0.0, maxit=5)
+            assert res["iterations"] == 5
+            out[fuse] = host(xs)
+    assert np.linalg.norm(out[0] - out[2]) <= 1e-12 * np.linalg.norm(out[2])
+
+
 def spread_offsets(width, n):
     half = [1 + 3 * k for k in range(width // 2)]
     return tuple([-o for o in half[::-1] if o < n] + [0] + [o for o in half if o < n])
