@@ -97,18 +97,18 @@ int lanes_variant(const cg_batch *b, const cg_batch_sched &s) {
 size_t part_words(int grid) { return (size_t)grid * kBatchSlots * 2 * kBatchLanes + ((size_t)grid + 2) / 2; }
 
 // Threads per workgroup: 1024, one workgroup per compute unit, so that teams
-// have few members to wait for and few caches to write back (24 diffusion
-// systems of side 32-256, 16 right-hand sides, us per iteration: 181 against
-// 203 with 256 threads; 3 systems of side <= 64: 22 against 36).  256 where
-// many tiny systems each leave most of 1024 threads idle (2000 systems of
-// 16-100 rows: 87 against 166; 1000 of 100-1600 rows the same, 411 and 410),
-// and where the phases are long against the team waits, which several
-// workgroups per unit then overlap with each other's work (60 systems of side
-// <= 512, 29K rows per unit: 2292 against 2424; 24 such systems, 8.7K rows per
-// unit: 715 against 708).
+// have few members to wait for and few caches to write back, and a workgroup
+// the unit's LDS for its vectors (24 diffusion systems of side 32-256, 16
+// right-hand sides, us per iteration: 161 against 203 with 256 threads; 3
+// systems of side <= 64: 23 against 36).  256 where light systems share
+// workgroups, which leave most of 1024 threads idle (2000 systems of 16-100
+// rows: 88 against 166; 1000 of 100-1600 rows 411 against 454), and where the
+// phases are long against the team waits, which several workgroups per unit
+// then overlap with each other's work (60 systems of side <= 512, 29K rows per
+// unit: 2292 against 2424; 24 such systems, 8.7K rows per unit: 715 against
+// 705).
 int batch_threads(const cg_batch *b) {
-    if (b->nsys > b->cus && b->n_total < 512 * (int64_t)b->nsys) return 256;
-    return b->n_total <= 16384 * (int64_t)b->cus ? 1024 : 256;
+    return b->nsys <= b->cus && b->n_total <= 16384 * (int64_t)b->cus ? 1024 : 256;
 }
 
 // Workgroups per system, with w_k = n_k^exponent as a system's cost: the

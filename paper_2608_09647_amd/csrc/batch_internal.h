@@ -36,10 +36,17 @@ struct BatchArgs {
     BatchOutDev *out;           // [nsys * nrhs]
     int32_t *episodes;          // [nsys] barriers passed (statistics)
     int32_t nrhs;
+    int32_t lane_bits;          // log2 of the lanes per row: enough for nrhs (set by the launch)
+    int32_t keep;               // float64 values of LDS for vectors kept there (set by the launch)
     int32_t maxit;
     double tol;
     int64_t timeout_ticks;      // wall-clock ticks a team wait may take
 };
+
+// Float64 values of LDS a workgroup keeps parts of its vectors in: what one of
+// 1024 threads leaves of a compute unit's 160 KB; with several workgroups per
+// unit, whose batches are far larger, none.
+constexpr inline int batch_keep(int threads) { return threads == 1024 ? 18432 : 0; }
 
 // Occupancy of the persistent kernel (workgroups per compute unit) for a
 // variant: threads per workgroup (256, 1024), rows a thread advances per step (1, 2), right-hand sides per lane

@@ -2,10 +2,11 @@
 //
 // Each pair (system k, right-hand side j) runs the CG recurrence of
 // Algorithm 1 with its own scalars.  A team of workgroups owns the rows of
-// system k for the whole launch; lane j of every 16-lane row group handles
-// right-hand side j, so the 16 values of one row of a vector form one
-// contiguous 128-byte line and a gathered p_c of all right-hand sides is one
-// line per column c.
+// system k for the whole launch; a row takes as many lanes (a power of two) as
+// its right-hand sides need, so the values of one row of a vector are
+// contiguous (16 right-hand sides: a 128-byte line, which a gathered p_c of
+// all of them is too) and few lanes idle (always 16 lanes: 511K rows with one
+// right-hand side 135 us per iteration, now 30; with 5, 138 and 76).
 //
 // A workgroup works through a list of items, each a (system, rank in its
 // team) pair, one after the other: heavy systems get teams of their own,
@@ -30,10 +31,12 @@
 // leave every cache as it is.  With a cache write-back and invalidation by
 // every wave at all three, and 256 threads to a workgroup, an iteration of 24
 // diffusion systems of side 32-256 with 16 right-hand sides took 607 us, 330 of
-// them in the barriers; so, and with 1024 threads, it takes 181 us.  Waits are
+// them in the barriers; so, and with 1024 threads, it took 181 us.  Waits are
 // bounded by a wall-clock limit; on expiry the error flag ends every team.
 #include <hip/hip_runtime.h>
 #include <math.h>
+
+#include <type_traits>
 
 #include "batch_internal.h"
 
@@ -42,6 +45,7 @@ namespace cgmi {
 namespace {
 
 constexpr int kL = kBatchLanes;
+constexpr int kStripSteps = 4;   // steps a line has at least where phase A goes by strips
 enum { kSlotPQ = 0, kSlotRR = 1, kSlotBB = 2, kSlotTrue = 3 };
 enum { kStOk = 0, kStMaxit = 1, kStBreakdown = -4 };
 
@@ -57,21 +61,34 @@ struct Shared {
     int ok;
 };
 
+// The value of the lane N further on in its row of 16.
+template <int N>
+__device__ __forceinline__ double row_rotate(double v) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x120 + N, 0xF, 0xF, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x120 + N, 0xF, 0xF, false);
+    return __hiloint2double(hi, lo);
+}
+
 // Sum over the workgroup for each right-hand side: a lane holds V consecutive
 // right-hand sides j0 .. j0+V-1 (acc[v] for j0 + v); lanes with the same j0
-// are 16/V apart.  The sums are returned to threads 0 .. 15.
+// are `lanes` apart.  The sums are returned to threads 0 .. 15.
 template <int NT, int V>
-__device__ __forceinline__ double wg_partial(const double (&acc)[V], Shared<NT> &S) {
-    constexpr int LPR = kL / V;
+__device__ __forceinline__ double wg_partial(const double (&acc)[V], int lanes, Shared<NT> &S) {
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     double v[V];
 #pragma unroll
     for (int q = 0; q < V; ++q) {
         v[q] = acc[q];
-#pragma unroll
-        for (int o = LPR; o < 64; o <<= 1) v[q] += __shfl_xor(v[q], o, 64);
+        v[q] += __shfl_xor(v[q], 32, 64);
+        v[q] += __shfl_xor(v[q], 16, 64);
+        // within the rows of 16 lanes: what has the period 2 o already, a
+        // rotation by o pairs like an exchange
+        if (lanes <= 8) v[q] += row_rotate<8>(v[q]);
+        if (lanes <= 4) v[q] += row_rotate<4>(v[q]);
+        if (lanes <= 2) v[q] += row_rotate<2>(v[q]);
+        if (lanes <= 1) v[q] += row_rotate<1>(v[q]);
     }
-    if (lane < LPR)
+    if (lane < lanes)
 #pragma unroll
         for (int q = 0; q < V; ++q) S.red[wv][lane * V + q] = v[q];
     __syncthreads();
@@ -231,6 +248,23 @@ __device__ __forceinline__ void stv(double *__restrict__ p, int64_t idx, const d
     }
 }
 
+// What a workgroup keeps in LDS of the vectors that no other workgroup reads
+// (511K rows with 16 right-hand sides, 2000 rows of which 1152 fit: 181 to 161
+// us per iteration): r of its first nr rows, q of its first nq and x of its first nx (nx <= nq <=
+// nr; r is touched three times an iteration, the others twice).  All three are
+// read and written by the same thread of a row, but q, which phase A writes.
+template <bool ON>
+struct Keep {
+    double *r, *q, *x;
+    int nr, nq, nx;
+    template <int V>
+    __device__ __forceinline__ void put(double *kept, int rows, double *__restrict__ v, int64_t local, int64_t idx,
+                                        int nrhs, int j0, const double (&s)[V]) const {
+        if (ON && local < rows) stv<V>(kept, (int)local * nrhs + j0, s);
+        else stv<V>(v, idx, s);
+    }
+};
+
 // sum_k val[k] * v[col[k] * nr + j0 + q] for one row and the lane's V
 // right-hand sides, in CSR order, each product and sum rounded separately (as
 // the oracle's SpMV).  Rows of up to kShort entries load all their columns
@@ -295,8 +329,8 @@ __device__ __forceinline__ void row_cw(const BatchArgs &a, int k0, int len, int 
 // the one after are loading), so a row costs about one memory round trip
 // instead of three.  Sums as row_dot: CSR order, each product and sum
 // rounded; rows longer than kPipe go entry by entry in the same order.
-template <int V>
-__device__ __forceinline__ void spmv_rows_pipelined(const BatchArgs &a, int64_t lo, int64_t hi, int RS,
+template <int V, class K_>
+__device__ __forceinline__ void spmv_rows_pipelined(const BatchArgs &a, const K_ &K, int64_t lo, int64_t hi, int RS,
                                                     int rsub, int nr, int j0, const bool (&on)[V],
                                                     double (&acc)[V]) {
 #pragma clang fp contract(off)
@@ -343,7 +377,7 @@ __device__ __forceinline__ void spmv_rows_pipelined(const BatchArgs &a, int64_t 
                 for (int q = 0; q < V; ++q) sv[q] += wk * g[q];
             }
         }
-        stv<V>(a.Q, idx, sv);
+        K.template put<V>(K.q, K.nq, a.Q, row - lo, idx, nr, j0, sv);
 #pragma unroll
         for (int q = 0; q < V; ++q)
             if (on[q]) acc[q] = fma(po[q], sv[q], acc[q]);
@@ -370,8 +404,8 @@ __device__ __forceinline__ void spmv_rows_pipelined(const BatchArgs &a, int64_t 
 // and 16 right-hand sides, more than an XCD's L2 holds for all its
 // workgroups).  Rows are summed as in spmv_rows_pipelined, three in flight;
 // only the order of the rows in the thread's partial p^T q changes.
-template <int V>
-__device__ __forceinline__ void spmv_rows_strips(const BatchArgs &a, int64_t off, int64_t lo, int64_t hi, int D,
+template <int V, class K_>
+__device__ __forceinline__ void spmv_rows_strips(const BatchArgs &a, const K_ &K, int64_t off, int64_t lo, int64_t hi, int D,
                                                  int RS, int rsub, int nr, int j0, const bool (&on)[V],
                                                  double (&acc)[V]) {
 #pragma clang fp contract(off)
@@ -437,7 +471,7 @@ __device__ __forceinline__ void spmv_rows_strips(const BatchArgs &a, int64_t off
             }
         }
         if (row >= 0) {
-            stv<V>(a.Q, idx, sv);
+            K.template put<V>(K.q, K.nq, a.Q, row - lo, idx, nr, j0, sv);
 #pragma unroll
             for (int q = 0; q < V; ++q)
                 if (on[q]) acc[q] = fma(po[q], sv[q], acc[q]);
@@ -456,6 +490,8 @@ __device__ __forceinline__ void spmv_rows_strips(const BatchArgs &a, int64_t off
     }
 }
 
+extern __shared__ double s_keep[];   // [a.keep]
+
 // U: rows a thread advances per step in the setup and the vector phases B
 // and C (phase A keeps three rows in flight by itself); V: right-hand sides
 // per lane (2 needs an even nrhs and 16-byte aligned vectors).
@@ -464,15 +500,45 @@ __device__ __forceinline__ void spmv_rows_strips(const BatchArgs &a, int64_t off
 // is being abandoned (a team wait gave up).
 template <int NT, int U, int V>
 __device__ __forceinline__ bool batch_solve_one(const BatchArgs &a, int sys, int rank, Shared<NT> &S) {
-    constexpr int LPR = kL / V;          // lanes per row
-    constexpr int RS = NT / LPR;         // rows per workgroup step
+    const int lanes = 1 << a.lane_bits;  // lanes per row
+    const int RS = NT >> a.lane_bits;    // rows per workgroup step
     const int T = a.team_size[sys], first = a.team_first[sys];
     const int64_t off = a.row_off[sys], n = a.row_off[sys + 1] - off;
     const int64_t lo = off + n * rank / T, hi = off + n * (rank + 1) / T;
     const int nr = a.nrhs;
-    const int j0 = (threadIdx.x % LPR) * V, rsub = threadIdx.x / LPR;
+    const int j0 = (threadIdx.x & (lanes - 1)) * V, rsub = threadIdx.x >> a.lane_bits;
     const bool lane_on = j0 < nr;
     int episode = 1;
+    constexpr bool kept = NT == 1024;   // else none is (batch_keep)
+    Keep<kept> K{};
+    if (kept) {
+        // whole steps, or all rows
+        const int rows = (int)min(hi - lo, (int64_t)(1 << 30)), most = a.keep / nr;
+        auto part = [&](int room) { return room >= rows ? rows : max(room, 0) / RS * RS; };
+        K.nr = part(most);
+        K.nq = min(part(most - K.nr), K.nr);
+        K.nx = min(part(most - K.nr - K.nq), K.nq);
+        K.r = s_keep;
+        K.q = K.r + (int64_t)K.nr * nr;
+        K.x = K.q + (int64_t)K.nq * nr;
+    }
+    // f(kept in LDS: r, second) over the thread's rows, U a step, in order:
+    // those with r and the second vector (q or x) there, with r alone, neither
+    auto for_rows = [&](int second, auto f) {
+        auto run = [&](int from, int to, auto kept_r, auto kept_s) {
+            for (int64_t r0 = lo + from; r0 < lo + to; r0 += RS * U)
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int64_t row = r0 + u * RS + rsub;
+                    if (row < lo + to) f(row, kept_r, kept_s);
+                }
+        };
+        if (kept) {
+            run(0, second, std::true_type{}, std::true_type{});
+            run(second, K.nr, std::true_type{}, std::false_type{});
+        }
+        run(K.nr, (int)(hi - lo), std::false_type{}, std::false_type{});
+    };
 
     // setup: r = b - A x, p = r; partial r^T r and b^T b
     {
@@ -495,15 +561,20 @@ __device__ __forceinline__ bool batch_solve_one(const BatchArgs &a, int sys, int
                             arr[q] = fma(rv[q], rv[q], arr[q]);
                             abb[q] = fma(bv[q], bv[q], abb[q]);
                         }
-                        stv<V>(a.R, idx, rv);
+                        K.template put<V>(K.r, K.nr, a.R, row - lo, idx, nr, j0, rv);
                         stv<V>(a.P, idx, rv);
+                        if (kept && row - lo < K.nx) {
+                            double xv[V];
+                            ldv<V>(a.X, idx, xv);
+                            stv<V>(K.x, (row - lo) * nr + j0, xv);
+                        }
                     }
                 }
-        const double rr = wg_partial<NT, V>(arr, S);
+        const double rr = wg_partial<NT, V>(arr, lanes, S);
         if (!team_sync<NT>(a, first, T, episode, S)) return false;
         if (!team_sum<NT>(a, first, T, kSlotRR, episode, rr, S)) return false;
         if (threadIdx.x < kL) S.rr_last[threadIdx.x] = S.sum[threadIdx.x];
-        const double bb = wg_partial<NT, V>(abb, S);
+        const double bb = wg_partial<NT, V>(abb, lanes, S);
         if (!team_sum<NT>(a, first, T, kSlotBB, episode, bb, S)) return false;
     }
     if (threadIdx.x < kL) {
@@ -544,13 +615,15 @@ __device__ __forceinline__ bool batch_solve_one(const BatchArgs &a, int sys, int
 #pragma unroll
             for (int q = 0; q < V; ++q) acc[q] = 0.0;
             if (any_on && lane_on) {
+                // (strips only where a step is a small part of a line: the
+                // last strip's lanes past the line idle)
                 const int D = a.strip[sys];
-                if (D > 0)
-                    spmv_rows_strips<V>(a, off, lo, hi, D, RS, rsub, nr, j0, on, acc);
+                if (D >= kStripSteps * RS)
+                    spmv_rows_strips<V>(a, K, off, lo, hi, D, RS, rsub, nr, j0, on, acc);
                 else
-                    spmv_rows_pipelined<V>(a, lo, hi, RS, rsub, nr, j0, on, acc);
+                    spmv_rows_pipelined<V>(a, K, lo, hi, RS, rsub, nr, j0, on, acc);
             }
-            const double pq = wg_partial<NT, V>(acc, S);
+            const double pq = wg_partial<NT, V>(acc, lanes, S);
             if (!team_sum<NT>(a, first, T, kSlotPQ, ++episode, pq, S)) return false;
         }
         if (threadIdx.x < kL) {
@@ -583,26 +656,25 @@ __device__ __forceinline__ bool batch_solve_one(const BatchArgs &a, int sys, int
                 acc[q] = 0.0;
             }
             if (any_on)
-                for (int64_t r0 = lo; r0 < hi; r0 += RS * U)
+                for_rows(K.nq, [&](int64_t row, auto kept_r, auto kept_q) {
+                    const int64_t idx = row * nr + j0;
+                    const int at = (int)(row - lo) * nr + j0;
+                    double qv[V], rv[V];
+                    if constexpr (decltype(kept_q)::value) ldv<V>(K.q, at, qv);
+                    else ldv<V>(a.Q, idx, qv);
+                    if constexpr (decltype(kept_r)::value) ldv<V>(K.r, at, rv);
+                    else ldv<V>(a.R, idx, rv);
 #pragma unroll
-                    for (int u = 0; u < U; ++u) {
-                        const int64_t row = r0 + u * RS + rsub;
-                        if (row < hi) {
-                            const int64_t idx = row * nr + j0;
-                            double qv[V], rv[V];
-                            ldv<V>(a.Q, idx, qv);
-                            ldv<V>(a.R, idx, rv);
-#pragma unroll
-                            for (int q = 0; q < V; ++q) {
-                                if (on[q]) {
-                                    rv[q] = fma(-alpha[q], qv[q], rv[q]);
-                                    acc[q] = fma(rv[q], rv[q], acc[q]);
-                                }
-                            }
-                            stv<V>(a.R, idx, rv);
+                    for (int q = 0; q < V; ++q) {
+                        if (on[q]) {
+                            rv[q] = fma(-alpha[q], qv[q], rv[q]);
+                            acc[q] = fma(rv[q], rv[q], acc[q]);
                         }
                     }
-            const double rr = wg_partial<NT, V>(acc, S);
+                    if constexpr (decltype(kept_r)::value) stv<V>(K.r, at, rv);
+                    else stv<V>(a.R, idx, rv);
+                });
+            const double rr = wg_partial<NT, V>(acc, lanes, S);
             if (!team_sum<NT>(a, first, T, kSlotRR, ++episode, rr, S)) return false;
         }
         if (threadIdx.x < kL) {
@@ -650,31 +722,38 @@ __device__ __forceinline__ bool batch_solve_one(const BatchArgs &a, int sys, int
                 beta[q] = S.beta[j0 + q];
             }
             if (any_up)
-                for (int64_t r0 = lo; r0 < hi; r0 += RS * U)
-#pragma unroll
-                    for (int u = 0; u < U; ++u) {
-                        const int64_t row = r0 + u * RS + rsub;
-                        if (row < hi) {
-                            const int64_t idx = row * nr + j0;
-                            double pv[V], xv[V], rv[V];
-                            ldv<V>(a.P, idx, pv);
-                            ldv<V>(a.X, idx, xv);
-                            if (any_on) ldv<V>(a.R, idx, rv);
-#pragma unroll
-                            for (int q = 0; q < V; ++q) {
-                                if (up[q]) xv[q] = fma(alpha[q], pv[q], xv[q]);
-                                if (on[q]) pv[q] = fma(beta[q], pv[q], rv[q]);
-                            }
-                            stv<V>(a.X, idx, xv);
-                            if (any_on) stv<V>(a.P, idx, pv);
-                        }
+                for_rows(K.nx, [&](int64_t row, auto kept_r, auto kept_x) {
+                    const int64_t idx = row * nr + j0;
+                    const int at = (int)(row - lo) * nr + j0;
+                    double pv[V], xv[V], rv[V];
+                    ldv<V>(a.P, idx, pv);
+                    if constexpr (decltype(kept_x)::value) ldv<V>(K.x, at, xv);
+                    else ldv<V>(a.X, idx, xv);
+                    if (any_on) {
+                        if constexpr (decltype(kept_r)::value) ldv<V>(K.r, at, rv);
+                        else ldv<V>(a.R, idx, rv);
                     }
+#pragma unroll
+                    for (int q = 0; q < V; ++q) {
+                        if (up[q]) xv[q] = fma(alpha[q], pv[q], xv[q]);
+                        if (on[q]) pv[q] = fma(beta[q], pv[q], rv[q]);
+                    }
+                    if constexpr (decltype(kept_x)::value) stv<V>(K.x, at, xv);
+                    else stv<V>(a.X, idx, xv);
+                    if (any_on) stv<V>(a.P, idx, pv);
+                });
         }
         if (!S.any) break;       // the x updates above reach the team at the next barrier
         if (!team_sync<NT>(a, first, T, ++episode, S)) return false;
     }
 
-    // b = 0: the solution is x = 0
+    // the x kept in LDS; b = 0: the solution is x = 0
+    if (kept && lane_on)
+        for (int64_t row = lo + rsub; row < lo + K.nx; row += RS) {
+            double xv[V];
+            ldv<V>(K.x, (row - lo) * nr + j0, xv);
+            stv<V>(a.X, row * nr + j0, xv);
+        }
     if (lane_on)
         for (int64_t row = lo + rsub; row < hi; row += RS)
 #pragma unroll
@@ -698,7 +777,7 @@ __device__ __forceinline__ bool batch_solve_one(const BatchArgs &a, int sys, int
                     acc[q] = fma(rv, rv, acc[q]);
                 }
             }
-        const double tr = wg_partial<NT, V>(acc, S);
+        const double tr = wg_partial<NT, V>(acc, lanes, S);
         if (!team_sum<NT>(a, first, T, kSlotTrue, ++episode, tr, S)) return false;
     }
     if (rank == 0) {
@@ -755,7 +834,9 @@ const void *kernel_of(int threads, int rows_per_thread, int rhs_per_lane) {
 int batch_blocks_per_cu(int threads, int rows_per_thread, int rhs_per_lane) {
     int nb = 0;
     const void *fn = kernel_of(threads, rows_per_thread, rhs_per_lane);
-    return fn && hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fn, threads, 0) == hipSuccess ? nb : 0;
+    const int lds = batch_keep(threads) * (int)sizeof(double);
+    if (!fn || (lds && hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess)) return 0;
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fn, threads, lds) == hipSuccess ? nb : 0;
 }
 
 hipError_t launch_batch_cg(const BatchArgs &a, int grid, int threads, int rows_per_thread, int rhs_per_lane,
@@ -765,10 +846,18 @@ hipError_t launch_batch_cg(const BatchArgs &a, int grid, int threads, int rows_p
     void *params[] = {&args};
     const void *fn = kernel_of(threads, rows_per_thread, rhs_per_lane);
     if (!fn) return hipErrorInvalidValue;
-    if (cooperative) return hipLaunchCooperativeKernel(fn, dim3(grid), dim3(threads), params, 0, s);
+    args.keep = batch_keep(threads);
+    args.lane_bits = 0;
+    while ((rhs_per_lane << args.lane_bits) < a.nrhs) ++args.lane_bits;
+    const unsigned lds = (unsigned)(args.keep * sizeof(double));
+    if (lds) {
+        const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+    }
+    if (cooperative) return hipLaunchCooperativeKernel(fn, dim3(grid), dim3(threads), params, lds, s);
     // ordinary launch of a grid the caller has checked to be resident (the
     // team waits give up after their time limit if it were not)
-    return hipLaunchKernel(fn, dim3(grid), dim3(threads), params, 0, s);
+    return hipLaunchKernel(fn, dim3(grid), dim3(threads), params, lds, s);
 }
 
 }  // namespace cgmi

@@ -218,7 +218,17 @@ def test_fixed_work_matches_oracle_iterates(cg):
     ([(130, 131)], 3),                          # one team of all workgroups, over 64 members
     ([(72, 71), (9, 7)], 16),                   # 64 members or so beside a workgroup of its own
     ([(5 + k % 7, 9) for k in range(300)], 2),  # more systems than compute units, all tiny
-    ([(400, 129), (128, 300)], 5),              # rows and vectors past what stays on chip
+    ([(400, 129), (128, 300)], 5),
+    ([(300, 300)], 16),                         # r, q and x of all rows fit LDS
+    ([(500, 500)], 12),                         # r of all rows, q of some
+    ([(600, 600)], 8),
+    ([(600, 600), (9, 9)], 16),                 # r of some
+    ([(40, 33), (20, 11)], 1),                  # every number of lanes per row
+    ([(40, 33), (20, 11)], 2),
+    ([(40, 33), (20, 11)], 4),
+    ([(40, 33), (20, 11)], 7),
+    ([(40, 33), (20, 11)], 10),
+    ([(40, 33), (20, 11)], 15),
 ])
 def test_team_sizes_match_oracle_iterates(cg, shapes, nrhs):
     """Fixed work on Poisson systems, from teams of one workgroup to one team
