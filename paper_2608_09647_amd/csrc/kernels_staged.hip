@@ -28,6 +28,8 @@
 // depend on timing.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "cg_device.h"
 #include "staged_internal.h"
 
@@ -269,11 +271,24 @@ hipError_t launch_sums(const StagedDev<T> &D, const T *p, const DevState *st, hi
 #define CGMI_STAGED(CH, K)                                                                                    \
     hipLaunchKernelGGL((k_staged_sums<T, CH, K>), dim3(D.nblocks * D.ngroups), dim3(kST), lds, s, D, p, D.off, \
                        D.idx, D.val, st)
-    const bool few = D.ahead <= 3;
-    if (chunks <= 3 && few) CGMI_STAGED(3, 3);
-    else if (chunks <= 3) CGMI_STAGED(3, kStagedAhead);
-    else if (few) CGMI_STAGED(4, 3);
-    else CGMI_STAGED(4, kStagedAhead);
+    // as many steps ahead as a list has at the most on average: a step costs
+    // its instructions also where the list has ended (900K rows of 49 entries,
+    // 2.6 steps a list: 211 us with 6, 190 with 3, 198 with 2; 700K of 41 158
+    // and 133 with 6 and 3)
+    const int K = std::min(std::max(D.ahead, 2), kStagedAhead);
+    if (chunks <= 3) {
+        if (K == 2) CGMI_STAGED(3, 2);
+        else if (K == 3) CGMI_STAGED(3, 3);
+        else if (K == 4) CGMI_STAGED(3, 4);
+        else if (K == 5) CGMI_STAGED(3, 5);
+        else CGMI_STAGED(3, kStagedAhead);
+    } else {
+        if (K == 2) CGMI_STAGED(4, 2);
+        else if (K == 3) CGMI_STAGED(4, 3);
+        else if (K == 4) CGMI_STAGED(4, 4);
+        else if (K == 5) CGMI_STAGED(4, 5);
+        else CGMI_STAGED(4, kStagedAhead);
+    }
 #undef CGMI_STAGED
     return hipGetLastError();
 }
@@ -291,9 +306,15 @@ hipError_t launch_mode(const StagedDev<T> &D, int grid, const SpmvArgs<T> &a, do
 template <class T>
 hipError_t allow_lds() {
     hipError_t e = hipSuccess;
-    for (const void *fn : {reinterpret_cast<const void *>(k_staged_sums<T, 3, 3>),
+    for (const void *fn : {reinterpret_cast<const void *>(k_staged_sums<T, 3, 2>),
+                           reinterpret_cast<const void *>(k_staged_sums<T, 4, 2>),
+                           reinterpret_cast<const void *>(k_staged_sums<T, 3, 3>),
+                           reinterpret_cast<const void *>(k_staged_sums<T, 3, 4>),
+                           reinterpret_cast<const void *>(k_staged_sums<T, 3, 5>),
                            reinterpret_cast<const void *>(k_staged_sums<T, 3, kStagedAhead>),
                            reinterpret_cast<const void *>(k_staged_sums<T, 4, 3>),
+                           reinterpret_cast<const void *>(k_staged_sums<T, 4, 4>),
+                           reinterpret_cast<const void *>(k_staged_sums<T, 4, 5>),
                            reinterpret_cast<const void *>(k_staged_sums<T, 4, kStagedAhead>)})
         if (e == hipSuccess) e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kStagedLds);
     return e;

@@ -242,7 +242,7 @@ void staged_build(DevMatrix &M, int cus, StagedMem<T> &S) {
         S.dev.seg_cols = seg;
         S.dev.max_slots = max_slots;
         S.dev.ncols = ncols;
-        S.dev.ahead = (int32_t)(n / ((int64_t)nb * lists) / kWaveSize) + 2;
+        S.dev.ahead = (int32_t)(n / ((int64_t)nb * lists) / kWaveSize) + 1;
         S.state = 1;
     } catch (...) {
         give_up();

@@ -40,7 +40,7 @@ struct StagedDev {
     int32_t nseg, seg_cols;       // segments, columns per segment
     int32_t max_slots;            // slots of the longest block
     int32_t ncols;                // columns the vector is known to have
-    int32_t ahead;                // steps of a list that the average one has, and one more
+    int32_t ahead;                // steps of the average list, the last one begun counted
     const int32_t *row0;          // [nblocks * kStagedWaves + 1] first row of every wave
     const int32_t *nslots;        // [nblocks] slots of every block
     const int32_t *off;           // [nblocks * kStagedWaves * nseg + 1] first entry of every wave's list per segment
