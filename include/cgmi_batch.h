@@ -7,7 +7,7 @@
  * (system k, right-hand side j) -- its own alpha, beta, stop test and
  * iteration count -- with all pairs advancing inside a single kernel launch.
  * A heavy system is given a team of workgroups that owns a contiguous share
- * of its rows for the whole solve; a team synchronises through counters in
+ * of its rows for the whole solve; a team synchronises through words in
  * device memory between the phases of an iteration (q = A p with p^T q;
  * x/r update with r^T r; p update) and stops when all of its right-hand sides
  * have converged, broken down or reached maxit.  Light systems share
@@ -43,7 +43,10 @@ typedef struct cg_batch cg_batch;
 
 /* Schedule of the persistent launch (the autotuner's search space). */
 typedef struct cg_batch_sched {
-    int32_t blocks_per_cu;  /* workgroups per compute unit (capped by occupancy) */
+    int32_t blocks_per_cu;  /* workgroups per compute unit (capped by occupancy:
+                               one of 1024 threads for batches of at most one
+                               system and 16384 rows per unit, else several of
+                               256) */
     int32_t rows_per_thread;/* rows a thread advances per step of the vector
                                phases: 1 or 2 */
     double team_exponent;   /* team size of system k proportional to n_k^team_exponent */

@@ -792,17 +792,18 @@ int dm_ensure_f32(DevMatrix &M) {
 
 // Whether staged column segments beat the kernels that gather from the L2 for
 // values of `elem` bytes, by what both take on matrices of random columns
-// (200K-2M rows of 15-81 entries): the staged sums 18 us, 1/14 us per MB of
-// segments and 1/350 us per 1000 entries; the gathers 1/140 us per 1000
+// (200K-2M rows of 15-81 entries): the staged sums 10 us, 1/14.5 us per MB of
+// segments and 1/430 us per 1000 entries; the gathers 1/140 us per 1000
 // entries, 1/120 where the vector exceeds an L2.  Measured at the two sides of
-// the line (float64): 1M rows of 15 entries 120 us staged against 122 us, of
-// 21 entries 142 against 170 us; 1.5M rows of 17 entries 299 against 244 us.
-// Under 196608 rows, where a wave's lists come to a step or two, little is
-// won: 150K rows of 51 entries 51 against 52 us (float32 50 against 48), 70K
-// rows of 81 entries 39 against 40 us.
+// the line (staged and gathered): float64 1M rows of 15 entries 110 and 121 us,
+// of 21 entries 123 and 170; 1.5M rows of 17 entries 267 and 244, of 25 entries
+// 295 and 310; float32 1M of 15 75 and 105, 1.5M of 17 142 and 175.  Under
+// 196608 rows, where a wave's lists come to a step or two, little is won: 150K
+// rows of 51 entries 51 against 52 us (float32 51 against 48), 100K rows of 81
+// 44 against 52 (47 against 47).
 static bool staged_pays(const DevMatrix &M, int32_t ncols, int cus, size_t elem) {
     const StagedShape S = staged_shape(M.m, cus);
-    const double staged = (double)S.nblocks * ncols * (double)elem / 14e12 + (double)M.nnz / 350e9 + 18e-6;
+    const double staged = (double)S.nblocks * ncols * (double)elem / 14.5e12 + (double)M.nnz / 430e9 + 10e-6;
     const double gathers = (double)M.nnz / ((double)ncols * (double)elem > (4 << 20) ? 120e9 : 140e9);
     return M.m >= 196608 && staged < 0.95 * gathers;
 }
