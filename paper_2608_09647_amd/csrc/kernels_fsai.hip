@@ -329,8 +329,9 @@ __global__ __launch_bounds__(256, 3) void k_fsai_forward(int32_t ntiles, const i
 constexpr double kDgScale = 1099511627776.0;   // 2^40
 
 __device__ __forceinline__ void dg_add(int64_t *p, float x) {
-    atomicAdd(reinterpret_cast<unsigned long long *>(p),
-              (unsigned long long)__double2ll_rn((double)x * kDgScale));
+    const long long v = __double2ll_rn((double)x * kDgScale);
+    // (a column outside supp(u) contributes nothing, and an atomic costs a trip)
+    if (v) atomicAdd(reinterpret_cast<unsigned long long *>(p), (unsigned long long)v);
 }
 struct GRow {
     int col[3];      // C, W, S columns (-1 absent)
@@ -385,7 +386,11 @@ __device__ __forceinline__ ARow a_row(int64_t row, const int32_t *__restrict__ s
 // per entry).
 constexpr int kLossTerms = 3 * kSlots;
 
-__global__ __launch_bounds__(256) void k_fsai_loss(int32_t nsamp, int32_t rows_per_sys,
+// 8 wavefronts per SIMD (12 bytes of spills): 8192 samples then run at once, a
+// chain of six trips to memory each (26.7 to 22.6 us without the atomics that
+// add nothing, to 19.6 with this).
+
+__global__ __launch_bounds__(256, 8) void k_fsai_loss(int32_t nsamp, int32_t rows_per_sys,
                                                    const int32_t *__restrict__ samp_row,
                                                    const int64_t *__restrict__ sel_base,
                                                    const int32_t *__restrict__ sel_n,
