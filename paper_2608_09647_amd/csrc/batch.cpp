@@ -23,6 +23,7 @@ struct cg_batch {
     hipStream_t stream = nullptr;
     int32_t nsys = 0, nrhs = 0;
     int64_t n_total = 0, nnz_total = 0;
+    int32_t row_max = 0;            // entries of the longest row
     std::vector<int64_t> row_off;   // nsys + 1
     int cus = 256;
     cg_batch_sched sched{};
@@ -99,7 +100,8 @@ size_t part_words(int grid) { return (size_t)grid * kBatchSlots * 2 * kBatchLane
 // Threads per workgroup: 1024, one workgroup per compute unit, so that teams
 // have few members to wait for and few caches to write back, and a workgroup
 // the unit's LDS for its vectors (24 diffusion systems of side 32-256, 16
-// right-hand sides, us per iteration: 161 against 203 with 256 threads; 3
+// right-hand sides, us per iteration: 161 against 203 with 256 threads, both with
+// 6 entries per row in flight; 3
 // systems of side <= 64: 23 against 36).  256 where light systems share
 // workgroups, which leave most of 1024 threads idle (2000 systems of 16-100
 // rows: 88 against 166; 1000 of 100-1600 rows 411 against 454), and where the
@@ -121,7 +123,7 @@ int batch_threads(const cg_batch *b) {
 // every one is heavier than L and has a team of its own.
 int assign_teams(cg_batch *b, const cg_batch_sched &s) {
     b->threads = batch_threads(b);
-    const int occ = batch_blocks_per_cu(b->threads, s.rows_per_thread, lanes_variant(b, s));
+    const int occ = batch_blocks_per_cu({b->threads, s.rows_per_thread, lanes_variant(b, s), b->row_max});
     if (occ <= 0) return fail(CG_EDEVICE, "occupancy query of the batched kernel failed");
     int grid = std::min(s.blocks_per_cu, occ) * b->cus;
     grid = std::max(1, std::min(grid, b->grid_cap));
@@ -291,7 +293,10 @@ extern "C" int cg_batch_create(int32_t nsys, const int32_t *n, const int64_t *nn
     int64_t r = 0, z = 0;
     for (int32_t k = 0; k < nsys; ++k) {
         b->row_off[k] = r;
-        for (int32_t i = 0; i < n[k]; ++i) rp[r + i] = (int32_t)(z + row_ptr[k][i]);
+        for (int32_t i = 0; i < n[k]; ++i) {
+            rp[r + i] = (int32_t)(z + row_ptr[k][i]);
+            b->row_max = std::max(b->row_max, row_ptr[k][i + 1] - row_ptr[k][i]);
+        }
         for (int64_t e = 0; e < nnz[k]; ++e) {
             ci[z + e] = (int32_t)(r + col[k][e]);
             va[z + e] = val[k][e];
@@ -303,7 +308,7 @@ extern "C" int cg_batch_create(int32_t nsys, const int32_t *n, const int64_t *nn
     rp[r] = (int32_t)z;
     int occ = 0;
     for (int u = 1; u <= 2; ++u)
-        for (int v = 1; v <= 2; ++v) occ = std::max(occ, batch_blocks_per_cu(batch_threads(b), u, v));
+        for (int v = 1; v <= 2; ++v) occ = std::max(occ, batch_blocks_per_cu({batch_threads(b), u, v, b->row_max}));
     if (occ <= 0) return bail(fail(CG_EDEVICE, "occupancy query of the batched kernel failed"));
     b->grid_cap = occ * b->cus;
     const size_t vec = (size_t)rows * nrhs;
@@ -429,7 +434,7 @@ extern "C" int cg_batch_solve(cg_batch *b, const double *B, double *X, double to
     if (V == 2 && ((reinterpret_cast<uintptr_t>(B) | reinterpret_cast<uintptr_t>(X)) & 15)) {
         // unaligned vectors: one right-hand side per lane, if that variant
         // keeps the grid resident
-        if (batch_blocks_per_cu(b->threads, b->sched.rows_per_thread, 1) * b->cus < b->grid) {
+        if (batch_blocks_per_cu({b->threads, b->sched.rows_per_thread, 1, b->row_max}) * b->cus < b->grid) {
             (void)hipEventDestroy(e0);
             (void)hipEventDestroy(e1);
             return fail(CG_EINVAL, "B and X must be 16-byte aligned for this schedule");
@@ -438,7 +443,7 @@ extern "C" int cg_batch_solve(cg_batch *b, const double *B, double *X, double to
     }
     // the grid is within the kernel's occupancy (assign_teams), so every
     // workgroup is resident at once in either launch form
-    const hipError_t le = launch_batch_cg(a, b->grid, b->threads, b->sched.rows_per_thread, V,
+    const hipError_t le = launch_batch_cg(a, b->grid, {b->threads, b->sched.rows_per_thread, V, b->row_max},
                                           b->sched.launch == CG_BATCH_LAUNCH_COOPERATIVE, st);
     if (le != hipSuccess) {
         (void)hipEventDestroy(e0);

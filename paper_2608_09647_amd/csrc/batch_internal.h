@@ -48,13 +48,17 @@ struct BatchArgs {
 // unit, whose batches are far larger, none.
 constexpr inline int batch_keep(int threads) { return threads == 1024 ? 18432 : 0; }
 
-// Occupancy of the persistent kernel (workgroups per compute unit) for a
-// variant: threads per workgroup (256, 1024), rows a thread advances per step (1, 2), right-hand sides per lane
-// (1; 2 needs an even nrhs and 16-byte aligned vectors).
-int batch_blocks_per_cu(int threads, int rows_per_thread, int rhs_per_lane);
+// A variant of the persistent kernel.
+struct BatchVariant {
+    int threads;           // per workgroup: 256 or 1024
+    int rows_per_thread;   // rows a thread advances per step: 1 or 2
+    int rhs_per_lane;      // right-hand sides per lane: 1; 2 needs an even nrhs and 16-byte aligned vectors
+    int row_max;           // entries of the longest row
+};
+// Occupancy (workgroups per compute unit).
+int batch_blocks_per_cu(const BatchVariant &k);
 // Launch of the persistent kernel over `grid` workgroups: cooperative, or
 // ordinary (cooperative = 0) for a grid already checked to be resident.
-hipError_t launch_batch_cg(const BatchArgs &a, int grid, int threads, int rows_per_thread, int rhs_per_lane,
-                           int cooperative, hipStream_t s);
+hipError_t launch_batch_cg(const BatchArgs &a, int grid, const BatchVariant &k, int cooperative, hipStream_t s);
 
 }  // namespace cgmi

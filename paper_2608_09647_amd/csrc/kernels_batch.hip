@@ -309,9 +309,11 @@ __device__ __forceinline__ void row_dot(const BatchArgs &a, int64_t row, const d
 }
 
 // Columns and values of a row of at most kPipe entries (clamped: entries
-// past the row repeat its first, an empty row reads entry 0).
-constexpr int kPipe = 6;
-
+// past the row repeat its first, an empty row reads entry 0).  kPipe is 5 for a
+// batch of rows of at most 5 entries, else 6: every entry more is two loads and
+// a gather per row, needed or not (24 diffusion systems, 16 right-hand sides:
+// 148 us per iteration with 5, 161 with 6).
+template <int kPipe>
 __device__ __forceinline__ void row_cw(const BatchArgs &a, int k0, int len, int (&c)[kPipe],
                                        double (&w)[kPipe]) {
     const int base = len > 0 ? k0 : 0;
@@ -329,7 +331,7 @@ __device__ __forceinline__ void row_cw(const BatchArgs &a, int k0, int len, int 
 // the one after are loading), so a row costs about one memory round trip
 // instead of three.  Sums as row_dot: CSR order, each product and sum
 // rounded; rows longer than kPipe go entry by entry in the same order.
-template <int V, class K_>
+template <int V, int kPipe, class K_>
 __device__ __forceinline__ void spmv_rows_pipelined(const BatchArgs &a, const K_ &K, int64_t lo, int64_t hi, int RS,
                                                     int rsub, int nr, int j0, const bool (&on)[V],
                                                     double (&acc)[V]) {
@@ -339,7 +341,7 @@ __device__ __forceinline__ void spmv_rows_pipelined(const BatchArgs &a, const K_
     int k0c = a.rp[row], lenc = a.rp[row + 1] - k0c;
     int cc[kPipe];
     double wc[kPipe];
-    row_cw(a, k0c, lenc, cc, wc);
+    row_cw<kPipe>(a, k0c, lenc, cc, wc);
     int k0n = 0, k1n = 0;
     if (row + RS < hi) {
         k0n = a.rp[row + RS];
@@ -353,7 +355,7 @@ __device__ __forceinline__ void spmv_rows_pipelined(const BatchArgs &a, const K_
         ldv<V>(a.P, idx, po);
         int cn[kPipe];
         double wn[kPipe];
-        row_cw(a, k0n, k1n - k0n, cn, wn);
+        row_cw<kPipe>(a, k0n, k1n - k0n, cn, wn);
         int k0nn = 0, k1nn = 0;
         if (row + 2 * RS < hi) {
             k0nn = a.rp[row + 2 * RS];
@@ -404,7 +406,7 @@ __device__ __forceinline__ void spmv_rows_pipelined(const BatchArgs &a, const K_
 // and 16 right-hand sides, more than an XCD's L2 holds for all its
 // workgroups).  Rows are summed as in spmv_rows_pipelined, three in flight;
 // only the order of the rows in the thread's partial p^T q changes.
-template <int V, class K_>
+template <int V, int kPipe, class K_>
 __device__ __forceinline__ void spmv_rows_strips(const BatchArgs &a, const K_ &K, int64_t off, int64_t lo, int64_t hi, int D,
                                                  int RS, int rsub, int nr, int j0, const bool (&on)[V],
                                                  double (&acc)[V]) {
@@ -430,7 +432,7 @@ __device__ __forceinline__ void spmv_rows_strips(const BatchArgs &a, const K_ &K
     }
     int cc[kPipe];
     double wc[kPipe];
-    row_cw(a, k0c, lenc, cc, wc);
+    row_cw<kPipe>(a, k0c, lenc, cc, wc);
     int64_t rown = row_at(1);
     int k0n = 0, k1n = 0;
     if (rown >= 0) {
@@ -445,7 +447,7 @@ __device__ __forceinline__ void spmv_rows_strips(const BatchArgs &a, const K_ &K
         ldv<V>(a.P, idx, po);
         int cn[kPipe];
         double wn[kPipe];
-        row_cw(a, k0n, k1n - k0n, cn, wn);
+        row_cw<kPipe>(a, k0n, k1n - k0n, cn, wn);
         const int64_t rownn = row_at(t + 2);
         int k0nn = 0, k1nn = 0;
         if (rownn >= 0) {
@@ -498,7 +500,7 @@ extern __shared__ double s_keep[];   // [a.keep]
 // One system's solve by this workgroup as member `rank` of its team (the
 // whole solve when the team is the workgroup alone).  False when the launch
 // is being abandoned (a team wait gave up).
-template <int NT, int U, int V>
+template <int NT, int U, int V, int E>
 __device__ __forceinline__ bool batch_solve_one(const BatchArgs &a, int sys, int rank, Shared<NT> &S) {
     const int lanes = 1 << a.lane_bits;  // lanes per row
     const int RS = NT >> a.lane_bits;    // rows per workgroup step
@@ -619,9 +621,9 @@ __device__ __forceinline__ bool batch_solve_one(const BatchArgs &a, int sys, int
                 // last strip's lanes past the line idle)
                 const int D = a.strip[sys];
                 if (D >= kStripSteps * RS)
-                    spmv_rows_strips<V>(a, K, off, lo, hi, D, RS, rsub, nr, j0, on, acc);
+                    spmv_rows_strips<V, E>(a, K, off, lo, hi, D, RS, rsub, nr, j0, on, acc);
                 else
-                    spmv_rows_pipelined<V>(a, K, lo, hi, RS, rsub, nr, j0, on, acc);
+                    spmv_rows_pipelined<V, E>(a, K, lo, hi, RS, rsub, nr, j0, on, acc);
             }
             const double pq = wg_partial<NT, V>(acc, lanes, S);
             if (!team_sum<NT>(a, first, T, kSlotPQ, ++episode, pq, S)) return false;
@@ -800,7 +802,7 @@ __device__ __forceinline__ bool batch_solve_one(const BatchArgs &a, int sys, int
 // team of several workgroups has one, a workgroup hosting small systems
 // (teams of one) several, so their rows share workgroups instead of each
 // taking one.
-template <int NT, int U, int V>
+template <int NT, int U, int V, int E>
 __global__ __launch_bounds__(NT) void k_batch_cg(BatchArgs a) {
     __shared__ Shared<NT> S;
     if (threadIdx.x == 0) S.ok = 1;
@@ -809,14 +811,16 @@ __global__ __launch_bounds__(NT) void k_batch_cg(BatchArgs a) {
     for (int it = i0; it < i1; ++it) {
         const int sys = __builtin_amdgcn_readfirstlane(a.item_sys[it]);
         const int rank = __builtin_amdgcn_readfirstlane(a.item_rank[it]);
-        if (!batch_solve_one<NT, U, V>(a, sys, rank, S)) return;
+        if (!batch_solve_one<NT, U, V, E>(a, sys, rank, S)) return;
         __syncthreads();   // S is set up afresh by the next system
     }
 }
 
-const void *kernel_of(int threads, int rows_per_thread, int rhs_per_lane) {
-#define CGMI_BATCH(NT, U, V)                                             \
-    if (threads == NT && rows_per_thread == U && rhs_per_lane == V) return reinterpret_cast<const void *>(k_batch_cg<NT, U, V>)
+const void *kernel_of(const BatchVariant &k) {
+#define CGMI_BATCH(NT, U, V)                                                                   \
+    if (k.threads == NT && k.rows_per_thread == U && k.rhs_per_lane == V)                      \
+    return k.row_max <= 5 ? reinterpret_cast<const void *>(k_batch_cg<NT, U, V, 5>)            \
+                          : reinterpret_cast<const void *>(k_batch_cg<NT, U, V, 6>)
     CGMI_BATCH(256, 1, 1);
     CGMI_BATCH(256, 1, 2);
     CGMI_BATCH(256, 2, 1);
@@ -831,24 +835,24 @@ const void *kernel_of(int threads, int rows_per_thread, int rhs_per_lane) {
 
 }  // namespace
 
-int batch_blocks_per_cu(int threads, int rows_per_thread, int rhs_per_lane) {
+int batch_blocks_per_cu(const BatchVariant &k) {
     int nb = 0;
-    const void *fn = kernel_of(threads, rows_per_thread, rhs_per_lane);
-    const int lds = batch_keep(threads) * (int)sizeof(double);
+    const void *fn = kernel_of(k);
+    const int threads = k.threads, lds = batch_keep(threads) * (int)sizeof(double);
     if (!fn || (lds && hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess)) return 0;
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fn, threads, lds) == hipSuccess ? nb : 0;
 }
 
-hipError_t launch_batch_cg(const BatchArgs &a, int grid, int threads, int rows_per_thread, int rhs_per_lane,
-                          int cooperative, hipStream_t s) {
+hipError_t launch_batch_cg(const BatchArgs &a, int grid, const BatchVariant &k, int cooperative, hipStream_t s) {
     if (grid <= 0) return hipSuccess;
     BatchArgs args = a;
     void *params[] = {&args};
-    const void *fn = kernel_of(threads, rows_per_thread, rhs_per_lane);
+    const void *fn = kernel_of(k);
+    const int threads = k.threads;
     if (!fn) return hipErrorInvalidValue;
     args.keep = batch_keep(threads);
     args.lane_bits = 0;
-    while ((rhs_per_lane << args.lane_bits) < a.nrhs) ++args.lane_bits;
+    while ((k.rhs_per_lane << args.lane_bits) < a.nrhs) ++args.lane_bits;
     const unsigned lds = (unsigned)(args.keep * sizeof(double));
     if (lds) {
         const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
