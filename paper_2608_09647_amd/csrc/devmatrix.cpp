@@ -792,18 +792,21 @@ int dm_ensure_f32(DevMatrix &M) {
 
 // Whether staged column segments beat the kernels that gather from the L2 for
 // values of `elem` bytes, by what both take on matrices of random columns
-// (200K-2M rows of 15-81 entries): the staged sums 10 us, 1/14.5 us per MB of
-// segments and 1/430 us per 1000 entries; the gathers 1/140 us per 1000
-// entries, 1/120 where the vector exceeds an L2.  Measured at the two sides of
-// the line (staged and gathered): float64 1M rows of 15 entries 110 and 121 us,
-// of 21 entries 123 and 170; 1.5M rows of 17 entries 267 and 244, of 25 entries
-// 295 and 310; float32 1M of 15 75 and 105, 1.5M of 17 142 and 175.  Under
-// 196608 rows, where a wave's lists come to a step or two, little is won: 150K
-// rows of 51 entries 51 against 52 us (float32 51 against 48), 100K rows of 81
-// 44 against 52 (47 against 47).
+// (200K-2M rows of 15-81 entries): the staged sums 10 us (28 with four groups
+// or more, whose sums pass through memory), 1/14.5 us per MB of segments and
+// 1/430 us per 1000 entries; the gathers 1/140 us per 1000 entries, 1/120 where
+// the vector exceeds an L2.  Measured at the two sides of the line (staged and
+// gathered): float64 1M rows of 15 entries 110 and 121 us, of 21 entries 123 and
+// 170; 1.5M rows of 17 entries 267 and 244, of 25 entries 295 and 310; 200K rows
+// of 19 entries 36 and 34, of 29 entries 44 and 42; 300K rows of 41 entries 60
+// and 83; float32 1M of 15 75 and 105, 1.5M of 17 142 and 175.  Under 196608
+// rows, where a wave's lists come to a step or two, little is won: 150K rows of
+// 51 entries 51 against 52 us (float32 51 against 48), 100K rows of 81 44 against
+// 52 (47 against 47).
 static bool staged_pays(const DevMatrix &M, int32_t ncols, int cus, size_t elem) {
     const StagedShape S = staged_shape(M.m, cus);
-    const double staged = (double)S.nblocks * ncols * (double)elem / 14.5e12 + (double)M.nnz / 430e9 + 10e-6;
+    const double staged = (double)S.nblocks * ncols * (double)elem / 14.5e12 + (double)M.nnz / 430e9 +
+                          (S.ngroups >= 4 ? 28e-6 : 10e-6);
     const double gathers = (double)M.nnz / ((double)ncols * (double)elem > (4 << 20) ? 120e9 : 140e9);
     return M.m >= 196608 && staged < 0.95 * gathers;
 }
