@@ -449,7 +449,7 @@ def bench_mixed(args) -> int:
                                 None, None)
     err = float(np.linalg.norm(xs["mixed"] - xs["fp64"]) / np.linalg.norm(xs["fp64"]))
     sp = out["fp64"]["seconds"] / out["mixed"]["seconds"]
-    # the mixed solve's dominant kernel is its float32 SpMV (staged segments)
+    # the mixed solve's dominant kernel is its float32 SpMV (column blocks)
     us32 = profiled_spmv_us(prob, {"precision": 1})
     us64 = profiled_spmv_us(prob, {})
     n, nnz = prob.A.n, prob.A.nnz
@@ -475,10 +475,10 @@ def bench_mixed(args) -> int:
                                                          "values from a 2 MB vector / SpMV time"},
                  roofline=roofline_hbm(spmv_algorithmic_bytes_f32(n, nnz), us32 * 1e-6,
                                        measured_traffic("spmv_random_spd_2m_f32", 5),
-                                       kernel="k_staged_sums<float> + k_staged_end (staged column segments)",
+                                       kernel="float32 column-blocked SpMV (start, 8 passes, finish)",
                                        note="CSR-algorithmic bytes (8 nnz + 4 (n+1) + 8 n) per SpMV; its "
-                                            "uniformly random columns are gathered from segments "
-                                            "of the vector staged in LDS"),
+                                            "uniformly random columns make it bound by L2 gathers: see "
+                                            "spmv_frac_of_gather_ceiling"),
                  traffic_fp64_spmv=measured_traffic("spmv_random_spd_2m_f64", 5))
     line["dtype"] = "f32+f64"
     line["rel_error_vs_xstar"] = {k: float(np.linalg.norm(xs[k] - prob.xstar) / np.linalg.norm(prob.xstar))

@@ -110,9 +110,8 @@ hipError_t dmalloc(T **p, size_t count) {
 
 // Staged column segments of a block (staged.cpp): 0 not built, 1 built, -1
 // the block does not take them.
-template <class T>
 struct StagedMem {
-    StagedDev<T> dev{};
+    StagedDev dev{};
     int8_t state = 0;
 };
 
@@ -147,9 +146,8 @@ struct DevMatrix {
     StenGlobal stg{};                 //   global stencil (konst: no slot values are stored)
     uint8_t *d_st_fast = nullptr;     //   its fast tiles
     bool konst_allowed = false;       //   the owner's kernels take constant values
-    StagedMem<double> st64;           // staged column segments (state 1: the products run on them)
-    StagedMem<float> st32;
-    bool use_st64 = false, use_st32 = false;   // for the current options
+    StagedMem st64;           // staged column segments (state 1: the products run on them)
+    bool use_st64 = false;            // for the current options
     std::vector<DevMatrix> blocks;    // column-blocked layout: one CSR per column block
     ColBlocks *cb = nullptr;          //   and their launch operands
     int32_t block_cols = 0;           //   columns per block
@@ -161,7 +159,7 @@ struct DevMatrix {
                       d_sell_idx, d_sell_dict, pad_col_base, cb,
                       d_st_off, d_st_offs, d_st_mask, d_st_val, d_sell_len, d_tile_row,
                       use_gap ? d_sell_lenx : nullptr, use_gap ? d_sell_gap : nullptr, stg, d_st_fast,
-                      use_st64 ? &st64.dev : nullptr, use_st32 ? &st32.dev : nullptr};
+                      use_st64 ? &st64.dev : nullptr};
     }
 };
 
@@ -187,13 +185,11 @@ struct StagedShape {
     int32_t nblocks, ngroups;
 };
 StagedShape staged_shape(int32_t m, int cus);
-// Builds the staged column segments of M with values of type T (S.state 1),
-// or leaves S.state -1 where they do not apply: rows over kHugeRow entries, a
-// vector of few segments, too much padding.  Rows are summed in float64.
-template <class T>
-void staged_build(DevMatrix &M, int cus, StagedMem<T> &S);
-template <class T>
-void staged_free(StagedMem<T> &S);
+// Builds the staged column segments of M (S.state 1), or leaves S.state -1
+// where they do not apply: rows over kHugeRow entries, a vector of few segments,
+// too much padding.
+void staged_build(DevMatrix &M, int cus, StagedMem &S);
+void staged_free(StagedMem &S);
 void dm_free(DevMatrix &M);
 
 }  // namespace cgmi

@@ -156,11 +156,10 @@ CGMI_HD constexpr inline int rows_per_wave_tile(int lanes) {
     return (kWaveSize / lanes) * rows_per_group(lanes);
 }
 
-// Matrix operand of the SpMV kernels: `m` rows with rebased row pointers;
-// columns index the full length-n vector.
-template <class T>
 struct StagedDev;   // staged_internal.h
 
+// Matrix operand of the SpMV kernels: `m` rows with rebased row pointers;
+// columns index the full length-n vector.
 struct CsrDev {
     int32_t m;
     const int32_t *rp;
@@ -186,8 +185,7 @@ struct CsrDev {
     const uint16_t *sell_gap; //   slot-major 16-bit column codes
     StenGlobal stg;           // global stencil (konst: st_off, st_offs and st_val do not exist)
     const uint8_t *st_fast;   //   its fast tiles, one byte per 128 rows
-    const StagedDev<double> *st64;  // staged column segments (host memory; launch side only)
-    const StagedDev<float> *st32;
+    const StagedDev *st64;  // staged column segments (host memory; launch side only)
     int32_t march;            // launch side: 1 = products may walk the planes, also with the dot, 2 = without it
 };
 

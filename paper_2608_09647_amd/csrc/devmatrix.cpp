@@ -790,24 +790,21 @@ int dm_ensure_f32(DevMatrix &M) {
     return CG_OK;
 }
 
-// Whether staged column segments beat the kernels that gather from the L2 for
-// values of `elem` bytes, by what both take on matrices of random columns
-// (200K-2M rows of 15-81 entries): the staged sums 10 us (28 with four groups
-// or more, whose sums pass through memory), 1/14.5 us per MB of segments and
-// 1/430 us per 1000 entries; the gathers 1/140 us per 1000 entries, 1/120 where
-// the vector exceeds an L2.  Measured at the two sides of the line (staged and
-// gathered): float64 1M rows of 15 entries 110 and 121 us, of 21 entries 123 and
+// Whether staged column segments beat the kernels that gather from the L2, by
+// what both take on matrices of random columns (200K-2M rows of 15-81 entries):
+// the staged sums 10 us (28 with four groups or more, whose sums pass through
+// memory), 1/14.5 us per MB of segments and 1/430 us per 1000 entries; the
+// gathers 1/140 us per 1000 entries, 1/120 where the vector exceeds an L2.  Measured at the two sides of the line (staged and
+// gathered): 1M rows of 15 entries 110 and 121 us, of 21 entries 123 and
 // 170; 1.5M rows of 17 entries 267 and 244, of 25 entries 295 and 310; 200K rows
 // of 19 entries 36 and 34, of 29 entries 44 and 42; 300K rows of 41 entries 60
-// and 83; float32 1M of 15 75 and 105, 1.5M of 17 142 and 175.  Under 196608
-// rows, where a wave's lists come to a step or two, little is won: 150K rows of
-// 51 entries 51 against 52 us (float32 51 against 48), 100K rows of 81 44 against
-// 52 (47 against 47).
-static bool staged_pays(const DevMatrix &M, int32_t ncols, int cus, size_t elem) {
+// and 83.  Under 196608 rows, where a wave's lists come to a step or two, little
+// is won: 150K rows of 51 entries 51 against 52 us, 100K rows of 81 44 against 52.
+static bool staged_pays(const DevMatrix &M, int32_t ncols, int cus) {
     const StagedShape S = staged_shape(M.m, cus);
-    const double staged = (double)S.nblocks * ncols * (double)elem / 14.5e12 + (double)M.nnz / 430e9 +
+    const double staged = (double)S.nblocks * ncols * sizeof(double) / 14.5e12 + (double)M.nnz / 430e9 +
                           (S.ngroups >= 4 ? 28e-6 : 10e-6);
-    const double gathers = (double)M.nnz / ((double)ncols * (double)elem > (4 << 20) ? 120e9 : 140e9);
+    const double gathers = (double)M.nnz / ((double)ncols * sizeof(double) > (4 << 20) ? 120e9 : 140e9);
     return M.m >= 196608 && staged < 0.95 * gathers;
 }
 
@@ -825,23 +822,23 @@ int dm_schedule(DevMatrix &M, int kind_opt, int grid_opt, int cus, int grid_cap,
     const int auto_grid = ((waves_needed / (kBlock / kWaveSize) + 8) / 8) * 8;
     const int grid = std::max(8, std::min(grid_opt > 0 ? grid_opt : std::min(cus * 8, auto_grid), grid_cap) / 8 * 8);
     // staged column segments in place of vector bins chosen automatically and
-    // of column blocks of the default width; float32 products beside them, not
-    // instead of the float64 ones (the residual of mixed precision)
-    M.use_st64 = M.use_st32 = false;
-    if (((M.sched.kind == kTileColBlocked && (kind_opt == 0 || kind_opt == 5) && block_cols <= 0) ||
+    // of column blocks of the default width.  Not in mixed precision: a float32
+    // inner solve follows the rounding of its products, and other sums, as exact
+    // as they are, move the solution it stops at within its tolerance (1e-9 at
+    // 700K rows and 1e-11), which is kept as it was
+    M.use_st64 = false;
+    if (!need_f32 &&
+        ((M.sched.kind == kTileColBlocked && (kind_opt == 0 || kind_opt == 5) && block_cols <= 0) ||
          (M.sched.kind == kTileVector && kind_opt == 0)) && !M.h_val.empty()) {
         int32_t ncols = 0;
 #pragma omp parallel for reduction(max : ncols) schedule(static)
         for (int32_t i = 0; i < M.m; ++i)
             if (M.h_rp[i + 1] > M.h_rp[i]) ncols = std::max(ncols, M.h_ci[M.h_rp[i + 1] - 1] + 1);
-        const bool w64 = staged_pays(M, ncols, cus, sizeof(double));
-        const bool w32 = need_f32 && staged_pays(M, ncols, cus, sizeof(float));
-        if (w64 && M.st64.state == 0) staged_build<double>(M, cus, M.st64);
-        if (w32 && M.st32.state == 0) staged_build<float>(M, cus, M.st32);
-        M.use_st64 = w64 && M.st64.state > 0;
-        M.use_st32 = w32 && M.st32.state > 0;
+        const bool pays = staged_pays(M, ncols, cus);
+        if (pays && M.st64.state == 0) staged_build(M, cus, M.st64);
+        M.use_st64 = pays && M.st64.state > 0;
     }
-    if (M.sched.kind == kTileColBlocked && !(M.use_st64 && (M.use_st32 || !need_f32))) {
+    if (M.sched.kind == kTileColBlocked && !M.use_st64) {
         const int32_t bc = block_cols > 0 ? block_cols : kColBlockCols;
         if (M.cb && M.block_cols == bc && need_f32)
             for (int b = 0; b < M.cb->nb; ++b) {
@@ -929,8 +926,7 @@ void dm_free(DevMatrix &M) {
     (void)hipFree(M.d_val32);
     free_sliced(M);
     staged_free(M.st64);
-    staged_free(M.st32);
-    M.use_st64 = M.use_st32 = false;
+    M.use_st64 = false;
     M.d_rp = M.d_ci = M.d_rows = nullptr;
     M.d_val = nullptr;
     M.d_val32 = nullptr;

@@ -2038,7 +2038,6 @@ hipError_t launch_spmv_f32(const CsrDev &A, const Schedule &S, int grid, const f
                            hipStream_t s) {
     if (A.m == 0) return hipSuccess;
     if (S.kind == kTileStencil) return hipErrorInvalidValue;   // no float32 variant
-    if (A.st32) return launch_spmv_staged_f32(*A.st32, grid, p, q, p_own, out_partials, st, mode, s);
     SpmvArgs<float> a{p, q, p_own, nullptr, nullptr};
     const Partials none{nullptr, 0};
     if (S.kind == kTileColBlocked) {

@@ -40,9 +40,8 @@ namespace {
 constexpr int kSW = kStagedWaves;
 constexpr int kST = kSW * kWave;
 
-// s + v x in float64, the product rounded first (exact for float32 operands).
-template <class T>
-__device__ __forceinline__ double staged_add(double s, T v, T x) {
+// s + v x, the product rounded first.
+__device__ __forceinline__ double staged_add(double s, double v, double x) {
 #pragma clang fp contract(off)
     return s + (double)v * (double)x;
 }
@@ -53,10 +52,7 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-template <class T>
-struct Piece;
-template <> struct Piece<double> { typedef double type __attribute__((ext_vector_type(2))); };
-template <> struct Piece<float> { typedef float type __attribute__((ext_vector_type(4))); };
+typedef double Piece __attribute__((ext_vector_type(2)));
 
 // The thread's 16-byte pieces of segment `seg` of p (the last segment again
 // past the end).  As many loads are issued whichever segment it is, so that
@@ -64,11 +60,11 @@ template <> struct Piece<float> { typedef float type __attribute__((ext_vector_t
 // loads leaves these in flight.  The last segment's pieces are clamped to the
 // vector's last whole one; what lies past it is stored by segment_store from
 // `tail`.
-template <class T, int CH>
-__device__ __forceinline__ void segment_load(const StagedDev<T> &D, const T *__restrict__ p, int seg,
-                                             typename Piece<T>::type (&r)[CH]) {
-    constexpr int E = 16 / sizeof(T);
-    const T *const base = p + (int64_t)min(seg, D.nseg - 1) * D.seg_cols;   // uniform
+template <int CH>
+__device__ __forceinline__ void segment_load(const StagedDev &D, const double *__restrict__ p, int seg,
+                                             Piece (&r)[CH]) {
+    constexpr int E = 16 / sizeof(double);
+    const double *const base = p + (int64_t)min(seg, D.nseg - 1) * D.seg_cols;   // uniform
     if (seg < D.nseg - 1 && D.seg_cols == CH * kST * E) {
 #pragma unroll
         for (int u = 0; u < CH; ++u) __builtin_memcpy(&r[u], base + u * kST * E + (uint32_t)threadIdx.x * E, 16);
@@ -80,12 +76,11 @@ __device__ __forceinline__ void segment_load(const StagedDev<T> &D, const T *__r
     }
 }
 
-template <class T, int CH>
-__device__ __forceinline__ void segment_store(const StagedDev<T> &D, int seg, T *buf,
-                                              const typename Piece<T>::type (&r)[CH], T tail) {
-    constexpr int E = 16 / sizeof(T);
-    typedef typename Piece<T>::type P;
-    P *const at = reinterpret_cast<P *>(buf) + threadIdx.x;
+template <int CH>
+__device__ __forceinline__ void segment_store(const StagedDev &D, int seg, double *buf,
+                                              const Piece (&r)[CH], double tail) {
+    constexpr int E = 16 / sizeof(double);
+    Piece *const at = reinterpret_cast<Piece *>(buf) + threadIdx.x;
     const int pieces = D.seg_cols / E;
     if (pieces == CH * kST) {
 #pragma unroll
@@ -104,17 +99,17 @@ __device__ __forceinline__ void segment_store(const StagedDev<T> &D, int seg, T 
 
 // The first K steps of a list, [beg, end) of the entry arrays (which are
 // padded so that these loads stay inside them).
-template <class T, int K>
+template <int K>
 struct Steps {
     int beg, end;
     uint32_t ix[K];
-    T v[K];
-    __device__ __forceinline__ void load(const uint32_t *__restrict__ idx, const T *__restrict__ val, int2 list) {
+    double v[K];
+    __device__ __forceinline__ void load(const uint32_t *__restrict__ idx, const double *__restrict__ val, int2 list) {
         const uint32_t lane = threadIdx.x & (kWave - 1);
         beg = list.x;
         end = list.y;
         const uint32_t *const ip = idx + beg;   // uniform
-        const T *const vp = val + beg;
+        const double *const vp = val + beg;
 #pragma unroll
         for (int k = 0; k < K; ++k) {
             ix[k] = ip[k * kWave + lane];
@@ -124,52 +119,51 @@ struct Steps {
 };
 
 // One step: the lanes that are on add v x to their slots, turn by turn.
-template <class T>
-__device__ __forceinline__ void staged_turns(bool on, uint32_t ix, T v, T x, double *y) {
+__device__ __forceinline__ void staged_turns(bool on, uint32_t ix, double v, double x, double *y) {
     const int turn = on ? (int)staged_turn(ix) : -1;
     for (int t = 0;; ++t) {
         if (turn == t) {
             double &s = y[staged_slot(ix)];
-            s = staged_add<T>(s, v, x);
+            s = staged_add(s, v, x);
         }
         wave_sync();   // another lane may read this sum in the next turn or step
         if (!__any(turn > t)) break;
     }
 }
 
-template <class T, int K>
-__device__ __forceinline__ void staged_compute(const uint32_t *__restrict__ idx, const T *__restrict__ val,
-                                               const Steps<T, K> &S, const T *buf, double *y) {
+template <int K>
+__device__ __forceinline__ void staged_compute(const uint32_t *__restrict__ idx, const double *__restrict__ val,
+                                               const Steps<K> &S, const double *buf, double *y) {
     const int lane = threadIdx.x & (kWave - 1);
     const int cnt = S.end - S.beg;
-    T x[K];
+    double x[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) x[k] = buf[staged_col(S.ix[k])];   // past the list: another's column
 #pragma unroll
     for (int k = 0; k < K; ++k)
-        if (k * kWave < cnt) staged_turns<T>(k * kWave + lane < cnt, S.ix[k], S.v[k], x[k], y);
+        if (k * kWave < cnt) staged_turns(k * kWave + lane < cnt, S.ix[k], S.v[k], x[k], y);
     for (int i = K * kWave; i < cnt; i += kWave) {
         const uint32_t ix = idx[S.beg + i + lane];   // past the last list: the arrays' padding
-        const T v = val[S.beg + i + lane];
-        staged_turns<T>(i + lane < cnt, ix, v, buf[staged_col(ix)], y);
+        const double v = val[S.beg + i + lane];
+        staged_turns(i + lane < cnt, ix, v, buf[staged_col(ix)], y);
     }
 }
 
 // The sums of block blockIdx.x / ngroups over segment group blockIdx.x %
 // ngroups, into D.part.
-template <class T, int CH, int K>
-__global__ __launch_bounds__(kST) void k_staged_sums(StagedDev<T> D, const T *__restrict__ p,
+template <int CH, int K>
+__global__ __launch_bounds__(kST) void k_staged_sums(StagedDev D, const double *__restrict__ p,
                                                      const int32_t *__restrict__ off,
-                                                     const uint32_t *__restrict__ idx, const T *__restrict__ val,
+                                                     const uint32_t *__restrict__ idx, const double *__restrict__ val,
                                                      const DevState *__restrict__ st) {
     extern __shared__ char lds_raw[];
     if (st && st->done) return;
-    T *const buf0 = reinterpret_cast<T *>(lds_raw), *const buf1 = buf0 + D.seg_cols;
+    double *const buf0 = reinterpret_cast<double *>(lds_raw), *const buf1 = buf0 + D.seg_cols;
     double *const y = reinterpret_cast<double *>(buf1 + D.seg_cols);
     const int b = blockIdx.x / D.ngroups, g = blockIdx.x - b * D.ngroups;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x & (kWave - 1);
     for (int i = threadIdx.x, n = D.nslots[b]; i <= n; i += kST) y[i] = 0.0;   // and the dummy
-    constexpr int E = 16 / sizeof(T);
+    constexpr int E = 16 / sizeof(double);
     const int first = (int)((int64_t)D.nseg * g / D.ngroups), last = (int)((int64_t)D.nseg * (g + 1) / D.ngroups);
     const int list0 = (b * kSW + w) * D.nseg;
     // bounds of the wave's lists: 64 segments' in two registers, one segment
@@ -187,24 +181,24 @@ __global__ __launch_bounds__(kST) void k_staged_sums(StagedDev<T> D, const T *__
     };
     renew(first);
     const int tail_col = D.ncols / E * E + (int)threadIdx.x;
-    const T tail = tail_col < D.ncols ? p[tail_col] : T(0);
-    typename Piece<T>::type P[CH];
-    Steps<T, K> E0, E1;
-    segment_load<T, CH>(D, p, first, P);
-    segment_store<T, CH>(D, first, buf0, P, tail);
+    const double tail = tail_col < D.ncols ? p[tail_col] : 0.0;
+    Piece P[CH];
+    Steps<K> E0, E1;
+    segment_load<CH>(D, p, first, P);
+    segment_store<CH>(D, first, buf0, P, tail);
     E0.load(idx, val, bounds(first));
-    segment_load<T, CH>(D, p, first + 1, P);
+    segment_load<CH>(D, p, first + 1, P);
     int2 next = bounds(first + 1);
     __syncthreads();
     // segment s: the next list's entries are issued, this one's used, then
     // segment s + 1 goes from registers to the other buffer, which every wave
     // has finished reading at the barrier before, and s + 2 is issued
-    auto step = [&](int s, const Steps<T, K> &cur, Steps<T, K> &nxt, const T *now, T *other) {
+    auto step = [&](int s, const Steps<K> &cur, Steps<K> &nxt, const double *now, double *other) {
         nxt.load(idx, val, next);
         next = bounds(s + 2);
-        staged_compute<T, K>(idx, val, cur, now, y);
-        if (s + 1 < last) segment_store<T, CH>(D, s + 1, other, P, tail);
-        segment_load<T, CH>(D, p, s + 2, P);
+        staged_compute<K>(idx, val, cur, now, y);
+        if (s + 1 < last) segment_store<CH>(D, s + 1, other, P, tail);
+        segment_load<CH>(D, p, s + 2, P);
         __syncthreads();
     };
     for (int s = first; s < last; s += 2) {
@@ -224,9 +218,9 @@ __global__ __launch_bounds__(kST) void k_staged_sums(StagedDev<T> D, const T *__
 
 // The end of every mode of k_spmv on the groups' sums; one partial per
 // workgroup.
-template <int MODE, class T>
+template <int MODE>
 __global__ __launch_bounds__(kBlock) void k_staged_end(int32_t m, int32_t ngroups, const double *__restrict__ part,
-                                                       SpmvArgs<T> a, double *__restrict__ out, Partials in0,
+                                                       SpmvArgs<double> a, double *__restrict__ out, Partials in0,
                                                        Partials in1, DevState *__restrict__ st, int flags) {
     __shared__ double sh[kWavesPerBlock];
     __shared__ double bc;
@@ -251,7 +245,7 @@ __global__ __launch_bounds__(kBlock) void k_staged_end(int32_t m, int32_t ngroup
     for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < m; i += (int64_t)gridDim.x * kBlock) {
         double s = part[i];
         for (int g = 1; g < ngroups; ++g) s += part[(int64_t)g * m + i];
-        emit_row<MODE, T>(a, (int)i, (T)s, acc0, acc1);
+        emit_row<MODE, double>(a, (int)i, s, acc0, acc1);
     }
     if (MODE == kSpmvPlain) return;
     const double s0 = block_sum<kBlock>(acc0, sh);
@@ -263,13 +257,12 @@ __global__ __launch_bounds__(kBlock) void k_staged_end(int32_t m, int32_t ngroup
     }
 }
 
-template <class T>
-hipError_t launch_sums(const StagedDev<T> &D, const T *p, const DevState *st, hipStream_t s) {
-    const size_t lds = staged_lds(D.seg_cols, sizeof(T), D.max_slots);
-    const int chunks = (int)((D.seg_cols * sizeof(T) / 16 + kST - 1) / kST);
+hipError_t launch_sums(const StagedDev &D, const double *p, const DevState *st, hipStream_t s) {
+    const size_t lds = staged_lds(D.seg_cols, D.max_slots);
+    const int chunks = (int)((D.seg_cols * sizeof(double) / 16 + kST - 1) / kST);
     if (lds > kStagedLds || chunks > kStagedChunks) return hipErrorInvalidValue;
 #define CGMI_STAGED(CH, K)                                                                                    \
-    hipLaunchKernelGGL((k_staged_sums<T, CH, K>), dim3(D.nblocks * D.ngroups), dim3(kST), lds, s, D, p, D.off, \
+    hipLaunchKernelGGL((k_staged_sums<CH, K>), dim3(D.nblocks * D.ngroups), dim3(kST), lds, s, D, p, D.off, \
                        D.idx, D.val, st)
     // as many steps ahead as a list has at the most on average: a step costs
     // its instructions also where the list has ended (900K rows of 49 entries,
@@ -293,29 +286,28 @@ hipError_t launch_sums(const StagedDev<T> &D, const T *p, const DevState *st, hi
     return hipGetLastError();
 }
 
-template <int MODE, class T>
-hipError_t launch_mode(const StagedDev<T> &D, int grid, const SpmvArgs<T> &a, double *out, Partials in0,
+template <int MODE>
+hipError_t launch_mode(const StagedDev &D, int grid, const SpmvArgs<double> &a, double *out, Partials in0,
                        Partials in1, DevState *st, int flags, hipStream_t s) {
-    const hipError_t e = launch_sums<T>(D, a.p, st, s);
+    const hipError_t e = launch_sums(D, a.p, st, s);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_staged_end<MODE, T>), dim3(grid), dim3(kBlock), 0, s, D.m, D.ngroups, D.part, a, out, in0,
+    hipLaunchKernelGGL((k_staged_end<MODE>), dim3(grid), dim3(kBlock), 0, s, D.m, D.ngroups, D.part, a, out, in0,
                        in1, st, flags);
     return hipGetLastError();
 }
 
-template <class T>
 hipError_t allow_lds() {
     hipError_t e = hipSuccess;
-    for (const void *fn : {reinterpret_cast<const void *>(k_staged_sums<T, 3, 2>),
-                           reinterpret_cast<const void *>(k_staged_sums<T, 4, 2>),
-                           reinterpret_cast<const void *>(k_staged_sums<T, 3, 3>),
-                           reinterpret_cast<const void *>(k_staged_sums<T, 3, 4>),
-                           reinterpret_cast<const void *>(k_staged_sums<T, 3, 5>),
-                           reinterpret_cast<const void *>(k_staged_sums<T, 3, kStagedAhead>),
-                           reinterpret_cast<const void *>(k_staged_sums<T, 4, 3>),
-                           reinterpret_cast<const void *>(k_staged_sums<T, 4, 4>),
-                           reinterpret_cast<const void *>(k_staged_sums<T, 4, 5>),
-                           reinterpret_cast<const void *>(k_staged_sums<T, 4, kStagedAhead>)})
+    for (const void *fn : {reinterpret_cast<const void *>(k_staged_sums<3, 2>),
+                           reinterpret_cast<const void *>(k_staged_sums<4, 2>),
+                           reinterpret_cast<const void *>(k_staged_sums<3, 3>),
+                           reinterpret_cast<const void *>(k_staged_sums<3, 4>),
+                           reinterpret_cast<const void *>(k_staged_sums<3, 5>),
+                           reinterpret_cast<const void *>(k_staged_sums<3, kStagedAhead>),
+                           reinterpret_cast<const void *>(k_staged_sums<4, 3>),
+                           reinterpret_cast<const void *>(k_staged_sums<4, 4>),
+                           reinterpret_cast<const void *>(k_staged_sums<4, 5>),
+                           reinterpret_cast<const void *>(k_staged_sums<4, kStagedAhead>)})
         if (e == hipSuccess) e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kStagedLds);
     return e;
 }
@@ -323,31 +315,20 @@ hipError_t allow_lds() {
 }  // namespace
 
 hipError_t staged_setup() {
-    const hipError_t e = allow_lds<double>();
-    return e == hipSuccess ? allow_lds<float>() : e;
+    return allow_lds();
 }
 
-hipError_t launch_spmv_staged(const StagedDev<double> &D, int grid, const double *p, double *q, const double *p_own,
+hipError_t launch_spmv_staged(const StagedDev &D, int grid, const double *p, double *q, const double *p_own,
                               const double *b, double *p_dst, double *out, Partials in0, Partials in1,
                               DevState *st, int mode, int k0_check, hipStream_t s) {
     const SpmvArgs<double> a{p, q, p_own, b, p_dst};
     const int flags = st ? kFlagCheckDone | (mode == kSpmvDot && k0_check ? kFlagFirstIter : 0) : 0;
     switch (mode) {
-        case kSpmvPlain: return launch_mode<kSpmvPlain, double>(D, grid, a, out, in0, in1, st, flags, s);
-        case kSpmvDot: return launch_mode<kSpmvDot, double>(D, grid, a, out, in0, in1, st, flags, s);
-        case kSpmvResidual: return launch_mode<kSpmvResidual, double>(D, grid, a, out, in0, in1, nullptr, 0, s);
+        case kSpmvPlain: return launch_mode<kSpmvPlain>(D, grid, a, out, in0, in1, st, flags, s);
+        case kSpmvDot: return launch_mode<kSpmvDot>(D, grid, a, out, in0, in1, st, flags, s);
+        case kSpmvResidual: return launch_mode<kSpmvResidual>(D, grid, a, out, in0, in1, nullptr, 0, s);
         default: return hipErrorInvalidValue;
     }
-}
-
-hipError_t launch_spmv_staged_f32(const StagedDev<float> &D, int grid, const float *p, float *q, const float *p_own,
-                                  double *out, DevState *st, int mode, hipStream_t s) {
-    const SpmvArgs<float> a{p, q, p_own, nullptr, nullptr};
-    const Partials none{nullptr, 0};
-    const int flags = st ? kFlagCheckDone : 0;
-    if (mode == kSpmvPlain) return launch_mode<kSpmvPlain, float>(D, grid, a, out, none, none, st, flags, s);
-    if (mode == kSpmvDot) return launch_mode<kSpmvDot, float>(D, grid, a, out, none, none, st, flags, s);
-    return hipErrorInvalidValue;
 }
 
 }  // namespace cgmi

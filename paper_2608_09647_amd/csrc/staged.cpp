@@ -17,12 +17,11 @@ struct Entry {
 };
 
 // The entries of a block as they go to the device.
-template <class T>
 struct BlockOut {
     HostVec<uint32_t> idx;
-    HostVec<T> val;
+    HostVec<double> val;
     size_t n = 0;
-    void push(uint32_t i, T v) {
+    void push(uint32_t i, double v) {
         if (n == idx.size()) {
             idx.resize(n + n / 4 + 1024);
             val.resize(idx.size());
@@ -37,8 +36,7 @@ struct BlockOut {
 // ninth entry in a step starts a new step (the old one is padded with entries
 // of the dummy slot).  seen[slot]: the step of the slot's last entry and its
 // turn there; `step` numbers the steps of all lists that share `seen`.
-template <class T>
-void append_list(const Entry *in, size_t n, const double *val, uint32_t dummy, BlockOut<T> &out,
+void append_list(const Entry *in, size_t n, const double *val, uint32_t dummy, BlockOut &out,
                  std::vector<std::pair<uint32_t, uint32_t>> &seen, uint32_t &step) {
     const size_t first = out.n;
     ++step;
@@ -47,12 +45,12 @@ void append_list(const Entry *in, size_t n, const double *val, uint32_t dummy, B
         std::pair<uint32_t, uint32_t> &s = seen[staged_slot(in[i].idx)];
         uint32_t turn = s.first == step ? s.second + 1 : 0;
         if (turn == kStagedTurns) {
-            while ((out.n - first) % kWaveSize) out.push(staged_word(0, 0, dummy), T(0));
+            while ((out.n - first) % kWaveSize) out.push(staged_word(0, 0, dummy), 0.0);
             ++step;
             turn = 0;
         }
         s = {step, turn};
-        out.push(in[i].idx | turn << kStagedColBits, (T)val[in[i].k]);
+        out.push(in[i].idx | turn << kStagedColBits, val[in[i].k]);
     }
 }
 
@@ -64,30 +62,28 @@ StagedShape staged_shape(int32_t m, int cus) {
     return {std::max<int32_t>((cus + groups - 1) / groups, (m + kStagedRows - 1) / kStagedRows), groups};
 }
 
-template <class T>
-void staged_free(StagedMem<T> &S) {
+void staged_free(StagedMem &S) {
     (void)hipFree(const_cast<int32_t *>(S.dev.row0));
     (void)hipFree(const_cast<int32_t *>(S.dev.off));
     (void)hipFree(const_cast<uint32_t *>(S.dev.idx));
-    (void)hipFree(const_cast<T *>(S.dev.val));
+    (void)hipFree(const_cast<double *>(S.dev.val));
     (void)hipFree(const_cast<int32_t *>(S.dev.nslots));
     (void)hipFree(const_cast<uint32_t *>(S.dev.slots));
     (void)hipFree(S.dev.part);
-    S.dev = StagedDev<T>{};
+    S.dev = StagedDev{};
     S.state = 0;
 }
 
 // state 1 on success; -1 where the matrix does not fit the layout or memory
 // runs out (the products stay with the gathering kernels).
-template <class T>
-void staged_build(DevMatrix &M, int cus, StagedMem<T> &S) {
+void staged_build(DevMatrix &M, int cus, StagedMem &S) {
     auto give_up = [&] {
         staged_free(S);
         S.state = -1;
     };
     give_up();
     const int32_t m = M.m;
-    const int32_t max_seg = (int32_t)(16u * kStagedWaves * kWaveSize * kStagedChunks / sizeof(T));
+    const int32_t max_seg = (int32_t)(16u * kStagedWaves * kWaveSize * kStagedChunks / sizeof(double));
     int32_t ncols = 0, longest = 0;
 #pragma omp parallel for reduction(max : ncols, longest) schedule(static)
     for (int32_t i = 0; i < m; ++i) {
@@ -137,7 +133,7 @@ void staged_build(DevMatrix &M, int cus, StagedMem<T> &S) {
             if (r < m) return;   // the cap left rows over
         }
         int32_t seg = (int32_t)std::min<size_t>(max_seg, (kStagedLds - sizeof(double) * ((size_t)max_slots + 1)) /
-                                                             (2 * sizeof(T)));
+                                                             (2 * sizeof(double)));
         seg = seg / 256 * 256;
         const int32_t nseg = (ncols + seg - 1) / seg;
         seg = std::min(seg, ((ncols + nseg - 1) / nseg + 255) / 256 * 256);
@@ -147,7 +143,7 @@ void staged_build(DevMatrix &M, int cus, StagedMem<T> &S) {
         if (room >= INT32_MAX - kStagedSlack) return;
         int32_t *d_row0 = nullptr, *d_off = nullptr, *d_nslots = nullptr;
         uint32_t *d_idx = nullptr, *d_slots = nullptr;
-        T *d_val = nullptr;
+        double *d_val = nullptr;
         hipError_t e = staged_setup();
         if (e == hipSuccess) e = dmalloc(&d_row0, row0.size());
         S.dev.row0 = d_row0;
@@ -164,7 +160,7 @@ void staged_build(DevMatrix &M, int cus, StagedMem<T> &S) {
         if (e == hipSuccess) e = dmalloc(&S.dev.part, (size_t)groups * m);
         // a few blocks at a time: built by all threads, then uploaded
         const int32_t batch = 2 * omp_get_max_threads();
-        std::vector<BlockOut<T>> out((size_t)std::min(batch, nb));
+        std::vector<BlockOut> out((size_t)std::min(batch, nb));
         std::atomic<bool> ok{true};
         int64_t n = 0;
         for (int32_t b0 = 0; b0 < nb && e == hipSuccess; b0 += batch) {
@@ -198,11 +194,11 @@ void staged_build(DevMatrix &M, int cus, StagedMem<T> &S) {
                                     if (++t == c) t = 0;
                                 }
                             }
-                        BlockOut<T> &o = out[(size_t)(b - b0)];
+                        BlockOut &o = out[(size_t)(b - b0)];
                         o.n = 0;
                         for (int32_t l = 0; l < lists; ++l) {   // cnt[l] is the end of list l by now
                             const int32_t beg = l ? cnt[(size_t)l - 1] : 0;
-                            append_list<T>(raw.data() + beg, (size_t)(cnt[(size_t)l] - beg), M.h_val.data(), dummy, o,
+                            append_list(raw.data() + beg, (size_t)(cnt[(size_t)l] - beg), M.h_val.data(), dummy, o,
                                            seen, step);
                             off[(size_t)b * lists + l + 1] = (int32_t)o.n;
                         }
@@ -213,12 +209,12 @@ void staged_build(DevMatrix &M, int cus, StagedMem<T> &S) {
             }
             if (!ok.load()) return give_up();
             for (int32_t b = b0; b < b1 && e == hipSuccess; ++b) {
-                const BlockOut<T> &o = out[(size_t)(b - b0)];
+                const BlockOut &o = out[(size_t)(b - b0)];
                 if (n + (int64_t)o.n > room) return give_up();
                 for (int32_t l = 0; l < lists; ++l) off[(size_t)b * lists + l + 1] += (int32_t)n;
                 if (o.n) e = hipMemcpy(d_idx + n, o.idx.data(), sizeof(uint32_t) * o.n, hipMemcpyHostToDevice);
                 if (o.n && e == hipSuccess)
-                    e = hipMemcpy(d_val + n, o.val.data(), sizeof(T) * o.n, hipMemcpyHostToDevice);
+                    e = hipMemcpy(d_val + n, o.val.data(), sizeof(double) * o.n, hipMemcpyHostToDevice);
                 n += (int64_t)o.n;
             }
         }
@@ -230,7 +226,7 @@ void staged_build(DevMatrix &M, int cus, StagedMem<T> &S) {
             e = hipMemcpy(d_slots, slot_of.data(), sizeof(uint32_t) * slot_of.size(), hipMemcpyHostToDevice);
         // entry 0 of the padding: column 0, turn 0, slot 0, never on
         if (e == hipSuccess) e = hipMemset(d_idx + n, 0, sizeof(uint32_t) * kStagedSlack);
-        if (e == hipSuccess) e = hipMemset(d_val + n, 0, sizeof(T) * kStagedSlack);
+        if (e == hipSuccess) e = hipMemset(d_val + n, 0, sizeof(double) * kStagedSlack);
         if (e != hipSuccess) {
             (void)hipGetLastError();
             return give_up();
@@ -248,10 +244,5 @@ void staged_build(DevMatrix &M, int cus, StagedMem<T> &S) {
         give_up();
     }
 }
-
-template void staged_free<double>(StagedMem<double> &);
-template void staged_free<float>(StagedMem<float> &);
-template void staged_build<double>(DevMatrix &, int, StagedMem<double> &);
-template void staged_build<float>(DevMatrix &, int, StagedMem<float> &);
 
 }  // namespace cgmi

@@ -29,11 +29,10 @@ CGMI_HD constexpr inline uint32_t staged_turn(uint32_t w) { return w >> kStagedC
 CGMI_HD constexpr inline uint32_t staged_slot(uint32_t w) { return w >> (kStagedColBits + kStagedTurnBits); }
 
 // LDS of a workgroup: two segments, and the block's slots with the dummy.
-CGMI_HD constexpr inline size_t staged_lds(int seg_cols, size_t elem, int max_slots) {
-    return 2 * elem * (size_t)seg_cols + sizeof(double) * ((size_t)max_slots + 1);
+CGMI_HD constexpr inline size_t staged_lds(int seg_cols, int max_slots) {
+    return sizeof(double) * (2 * (size_t)seg_cols + (size_t)max_slots + 1);
 }
 
-template <class T>
 struct StagedDev {
     int32_t m;
     int32_t nblocks, ngroups;     // row blocks, groups of segments (a workgroup takes one of each)
@@ -45,19 +44,17 @@ struct StagedDev {
     const int32_t *nslots;        // [nblocks] slots of every block
     const int32_t *off;           // [nblocks * kStagedWaves * nseg + 1] first entry of every wave's list per segment
     const uint32_t *idx;          // staged_word of every entry
-    const T *val;
+    const double *val;
     const uint32_t *slots;        // per row: its first slot in the block | its slots << 16; null: one each, in order
     double *part;                 // [ngroups * m] the groups' sums of every row
 };
 
 // Lets the kernels use kStagedLds bytes of LDS on the current device.
 hipError_t staged_setup();
-// The modes of launch_spmv / launch_spmv_f32; grid: workgroups of the second
-// kernel, and the partials in out (twice that in the residual mode).
-hipError_t launch_spmv_staged(const StagedDev<double> &D, int grid, const double *p, double *q, const double *p_own,
+// The modes of launch_spmv; grid: workgroups of the second kernel, and the
+// partials in out (twice that in the residual mode).
+hipError_t launch_spmv_staged(const StagedDev &D, int grid, const double *p, double *q, const double *p_own,
                               const double *b, double *p_dst, double *out, Partials in0, Partials in1,
                               DevState *st, int mode, int k0_check, hipStream_t s);
-hipError_t launch_spmv_staged_f32(const StagedDev<float> &D, int grid, const float *p, float *q, const float *p_own,
-                                  double *out, DevState *st, int mode, hipStream_t s);
 
 }  // namespace cgmi

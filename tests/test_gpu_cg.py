@@ -1316,8 +1316,8 @@ def scattered(n, per_row, long_rows, seed=5):
 def test_staged_segments_match_oracle(cg, n, per_row, long_rows):
     """Rows of many scattered columns (products on staged column segments:
     8, 8 and 4 groups of segments on 256 compute units,
-    rows over several slots, empty rows, an odd last column): float64 and
-    float32 products, a block of rows that starts inside the matrix, and
+    rows over several slots, empty rows, an odd last column): float64
+    products, also after float32 ones of the general kernels, a block of rows that starts inside the matrix, and
     integer values, whose sums are exact in any order."""
     A = scattered(n, per_row, long_rows)
     x = np.random.default_rng(7).uniform(-1, 1, n)
@@ -1332,13 +1332,16 @@ def test_staged_segments_match_oracle(cg, n, per_row, long_rows):
         xo.copy_(dev(x))
         shifted = host(s.spmv(xo, off))
         s.set_opts(precision=cg.PREC_MIXED)
-        y32 = host(s.spmv_f32(torch.from_numpy(x.astype(np.float32)).cuda())).astype(np.float64)
+        x32 = x.astype(np.float32)
+        y32 = host(s.spmv_f32(torch.from_numpy(x32).cuda())).astype(np.float64)
+        s.set_opts(precision=cg.PREC_FP64)
+        back = host(s.spmv(dev(x)))
     assert spmv_err(A, x, y, ref) <= 1e-12
-    assert np.array_equal(y, again) and np.array_equal(y, shifted)
-    # float32 operands summed in float64, one rounding to float32 at the end:
-    # half an ulp of the result, and half an ulp of each rounded operand
-    absA = sp.csr_matrix((np.abs(A.val), A.col, A.row_ptr), shape=(n, n))
-    assert np.all(np.abs(y32 - ref) <= 3.0 * 2.0 ** -24 * (absA @ np.abs(x)) * (1 + 1e-6) + 1e-30)
+    assert np.array_equal(y, again) and np.array_equal(y, shifted) and np.array_equal(y, back)
+    # float32 sums of a row, in another order than the oracle's
+    absA = sp.csr_matrix((np.abs(A.val.astype(np.float32)), A.col, A.row_ptr), shape=(n, n))
+    bound = 2 * np.diff(A.row_ptr).max() * 2.0 ** -24 * (absA @ np.abs(x32).astype(np.float64))
+    assert np.all(np.abs(y32 - oracle.spmv_f32(A, x32)) <= bound + 1e-30)
     B = I.CSR(n, A.row_ptr, A.col, np.random.default_rng(9).integers(-8, 9, A.nnz).astype(np.float64))
     xi = np.random.default_rng(8).integers(-8, 9, n).astype(np.float64)
     refi = oracle.spmv(B, xi)
@@ -1351,7 +1354,8 @@ def test_staged_segments_match_oracle(cg, n, per_row, long_rows):
 
 
 def test_staged_segments_solve(cg):
-    """CG and mixed precision on staged column segments against the oracle."""
+    """CG where float64 products run on staged column segments, and mixed
+    precision on the same matrix, against the oracle."""
     A = I.random_spd_lognormal(200_000, 7, mean_degree=20.0)
     b = I.rhs_of(A, I.uniform_vector(A.n, [31, 1]))
     ref = oracle.cg(A, b, tol=1e-10, maxit=5000)
