@@ -64,15 +64,16 @@ template <int CH>
 __device__ __forceinline__ void segment_load(const StagedDev &D, const double *__restrict__ p, int seg,
                                              Piece (&r)[CH]) {
     constexpr int E = 16 / sizeof(double);
-    const double *const base = p + (int64_t)min(seg, D.nseg - 1) * D.seg_cols;   // uniform
+    const int s = min(seg, D.nseg - 1);
+    const double *const base = p + (int64_t)s * D.seg_cols;   // uniform
     if (seg < D.nseg - 1 && D.seg_cols == CH * kST * E) {
 #pragma unroll
         for (int u = 0; u < CH; ++u) __builtin_memcpy(&r[u], base + u * kST * E + (uint32_t)threadIdx.x * E, 16);
     } else {
-        const int last = min(D.ncols - min(seg, D.nseg - 1) * D.seg_cols, D.seg_cols + E) / E * E - E;
+        const int last = staged_last_pair(D.ncols - s * D.seg_cols, D.seg_cols);
+        const double *const from = base + staged_pair_base(last);
 #pragma unroll
-        for (int u = 0; u < CH; ++u)
-            __builtin_memcpy(&r[u], base + (uint32_t)min((u * kST + (int)threadIdx.x) * E, last), 16);
+        for (int u = 0; u < CH; ++u) __builtin_memcpy(&r[u], from + staged_pair((u * kST + (int)threadIdx.x) * E, last), 16);
     }
 }
 

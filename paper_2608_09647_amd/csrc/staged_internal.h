@@ -33,6 +33,20 @@ CGMI_HD constexpr inline size_t staged_lds(int seg_cols, int max_slots) {
     return sizeof(double) * (2 * (size_t)seg_cols + (size_t)max_slots + 1);
 }
 
+// A segment is loaded by 16-byte pairs of columns, pair k of the segment at
+// its column k, clamped to the last pair of columns the vector has there (or
+// the two behind a whole segment).  `left`: the columns from the segment's
+// first to the vector's end.  With one column left the last pair begins before
+// the segment, at -2 (a layout has two segments or more): the base moves there
+// and the offsets stay unsigned.
+CGMI_HD constexpr inline int32_t staged_last_pair(int32_t left, int32_t seg_cols) {
+    return (left < seg_cols + 2 ? left : seg_cols + 2) / 2 * 2 - 2;
+}
+CGMI_HD constexpr inline int32_t staged_pair_base(int32_t last) { return last < 0 ? last : 0; }
+CGMI_HD constexpr inline uint32_t staged_pair(int32_t k, int32_t last) {
+    return (uint32_t)((k < last ? k : last) - staged_pair_base(last));
+}
+
 struct StagedDev {
     int32_t m;
     int32_t nblocks, ngroups;     // row blocks, groups of segments (a workgroup takes one of each)

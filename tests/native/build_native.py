@@ -36,6 +36,29 @@ def build(sanitize: str | None = None, verbose: bool = False) -> list:
     return out
 
 
+HOST_SOURCES = ["cgmi.cpp", "devmatrix.cpp", "staged.cpp", "fsai.cpp"]
+
+
+def build_host_checks(verbose: bool = False) -> str:
+    """tests/native/bin/host_checks: the library's host sources with the HIP
+    calls of host_checks.cpp (g++; needs no GPU and not libcgmi.so).  Kernel
+    launches that no check reaches stay unresolved."""
+    os.makedirs(BIN, exist_ok=True)
+    flags = ["-O1", "-g", "-std=c++17", "-fopenmp", "-fno-pie", "-D__HIP_PLATFORM_AMD__", f"-I{ROCM}/include", "-w"]
+    srcs = [os.path.join(PKG, "csrc", s) for s in HOST_SOURCES] + [os.path.join(HERE, "host_checks.cpp")]
+    objs = [os.path.join(BIN, os.path.basename(s).replace(".cpp", ".hc.o")) for s in srcs]
+    cmds = [["g++", *flags, "-c", s, "-o", o] for s, o in zip(srcs, objs)]
+    if verbose:
+        print("\n".join(" ".join(c) for c in cmds), flush=True)
+    procs = [subprocess.Popen(c) for c in cmds]
+    if any([p.wait() for p in procs]):
+        raise RuntimeError("host_checks: a compile step failed")
+    exe = os.path.join(BIN, "host_checks")
+    subprocess.run(["g++", "-fopenmp", *objs, "-o", exe, "-no-pie", "-Wl,--unresolved-symbols=ignore-all"],
+                   check=True)
+    return exe
+
+
 if __name__ == "__main__":
     san = sys.argv[2] if len(sys.argv) > 2 and sys.argv[1] == "--sanitize" else None
     print(build(san, verbose=True))

@@ -1,0 +1,34 @@
+"""The library's host code on the CPU (tests/native/host_checks.cpp): HIP calls
+on host memory, no GPU."""
+import importlib.util
+import os
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+@pytest.fixture(scope="module")
+def host_checks():
+    spec = importlib.util.spec_from_file_location("build_native", os.path.join(HERE, "native", "build_native.py"))
+    mod = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(mod)
+    exe = mod.build_host_checks()
+
+    def run(*args):
+        r = subprocess.run([exe, *map(str, args)], capture_output=True, text=True, timeout=120)
+        assert r.returncode == 0 and r.stdout.endswith("ok\n"), (args, r.stdout, r.stderr)
+        return r.stdout
+
+    return run
+
+
+@pytest.mark.parametrize("rows,cols,last", [
+    (299_521, 299_521, 1), (299_522, 299_522, 2), (299_523, 299_523, 3), (299_519, 299_519, 7679),
+    (299_520, 299_520, 7680), (262_144, 45_000, 5576)])
+def test_staged_segments_stay_in_their_buffers(host_checks, rows, cols, last):
+    """Staged column segments whose last one has one column, two, three, all
+    but one and all, and columns past the last used one: every index of the
+    product inside its buffer, the sums exact."""
+    assert f"{last} in the last" in host_checks("staged", rows, cols, 40 if cols > 45_000 else 24)
