@@ -6,8 +6,10 @@
 //
 //     host_checks staged ROWS COLS PER_ROW
 //         the staged column segments of a matrix of ROWS rows, PER_ROW random
-//         entries each, all columns below COLS: every index the product's
-//         kernel forms lies in its buffer, and the sums are the rows' own
+//         entries each (every fifth row twice as many, one row 1500), all
+//         columns below COLS: every index the product's kernel forms lies in
+//         its buffer, and the sums are the rows' own.  Says whether the
+//         schedule runs its products on them
 #include <hip/hip_runtime_api.h>
 
 #include <cmath>
@@ -64,8 +66,10 @@ namespace {
         }                                                    \
     } while (0)
 
-// PER_ROW entries a row, one in each of as many equal ranges of the columns,
-// integer values (their sums are exact in any order); the last column is used.
+// per_row entries a row, in every fifth row twice as many, in one 1500 (which
+// keeps the schedule from stream tiles), one in each of as many equal ranges of
+// the columns, integer values (their sums are exact in any order); the last
+// column is used.
 struct Matrix {
     std::vector<int32_t> rp, ci;
     std::vector<double> val;
@@ -73,11 +77,11 @@ struct Matrix {
 Matrix random_rows(int32_t rows, int32_t cols, int32_t per_row) {
     Matrix A;
     std::mt19937 rng(7);
-    const int32_t width = cols / per_row;
-    REQUIRE(width > 0, "%d columns for %d entries a row", cols, per_row);
     A.rp.assign(1, 0);
     for (int32_t i = 0; i < rows; ++i) {
-        for (int32_t j = 0; j < per_row; ++j) {
+        const int32_t len = i == rows / 2 ? 1500 : i % 5 ? per_row : 2 * per_row, width = cols / len;
+        REQUIRE(width > 0, "%d columns for %d entries a row", cols, len);
+        for (int32_t j = 0; j < len; ++j) {
             A.ci.push_back(j * width + (int32_t)(rng() % (uint32_t)width));
             A.val.push_back((double)(int32_t)(rng() % 17u) - 8.0);
         }
@@ -152,15 +156,16 @@ std::vector<double> staged_product(const StagedDev &S, const std::vector<double>
     return q;
 }
 
-// "none": the layout does not take the matrix.
 void check_staged(int32_t rows, int32_t cols, int32_t per_row) {
     const int cus = 256;
     const Matrix A = random_rows(rows, cols, per_row);
     DevMatrix M;
     REQUIRE(dm_upload(M, rows, A.rp.data(), A.ci.data(), A.val.data(), 0) == CG_OK, "upload");
-    staged_build(M, cus, M.st64);
+    REQUIRE(dm_schedule(M, 0, 0, cus, 16 * cus, false) == CG_OK, "schedule");
+    std::printf("%s ", M.use_st64 ? "taken" : "not taken");
+    if (M.st64.state == 0) staged_build(M, cus, M.st64);
     if (M.st64.state < 0) {
-        std::printf("none\n");
+        std::printf("not built\n");
         dm_free(M);
         return;
     }

@@ -1370,20 +1370,23 @@ def test_staged_segments_solve(cg):
 
 
 def prefix_rows(n, cols, per_row, seed=13):
-    """per_row entries in every row, one in each of as many equal ranges of the
-    first cols columns, the last of them used; integer values."""
+    """per_row entries in every row, in every fifth one twice as many and in one
+    1,500 (no stream tiles), one in each of as many equal ranges of the first
+    cols columns, the last of them used; integer values."""
     rng = np.random.default_rng(seed)
-    width = cols // per_row
-    c = np.arange(per_row) * width + rng.integers(0, width, (n, per_row))
-    c[-1, -1] = cols - 1
-    rp = np.arange(n + 1, dtype=np.int64) * per_row
-    return I.CSR(n, rp.astype(np.int32), c.ravel().astype(np.int32),
-                 rng.integers(-8, 9, n * per_row).astype(np.float64))
+    ln = np.where(np.arange(n) % 5, per_row, 2 * per_row)
+    ln[n // 2] = 1500
+    rp = np.zeros(n + 1, dtype=np.int64)
+    np.cumsum(ln, out=rp[1:])
+    width = np.repeat(cols // ln, ln)
+    c = (np.arange(rp[-1]) - np.repeat(rp[:-1], ln)) * width + (rng.random(rp[-1]) * width).astype(np.int64)
+    c[-1] = cols - 1
+    return I.CSR(n, rp.astype(np.int32), c.astype(np.int32), rng.integers(-8, 9, rp[-1]).astype(np.float64))
 
 
 @pytest.mark.parametrize("n,cols,per_row", [
-    (299_521, 299_521, 40), (299_522, 299_522, 40), (299_519, 299_519, 40),   # 1, 2 and all columns but one
-    (262_144, 52_993, 28)])                                                     # a prefix of the columns
+    (299_521, 299_521, 33), (299_522, 299_522, 33), (299_519, 299_519, 33),   # 1, 2 and all columns but one
+    (262_144, 52_993, 24)])                                                     # a prefix of the columns
 def test_staged_segments_at_the_end_of_the_vector(cg, n, cols, per_row):
     """Products on staged column segments whose last segment has one column,
     two or all but one, and with columns that no row uses: exact sums of
@@ -1391,4 +1394,5 @@ def test_staged_segments_at_the_end_of_the_vector(cg, n, cols, per_row):
     A = prefix_rows(n, cols, per_row)
     x = np.random.default_rng(15).integers(-8, 9, n).astype(np.float64)
     with cg.Solver(A) as s:
+        assert used_kind(s, n) == 1
         assert np.array_equal(host(s.spmv(dev(x))), oracle.spmv(A, x))
