@@ -186,8 +186,8 @@ struct StagedShape {
 };
 StagedShape staged_shape(int32_t m, int cus);
 // Builds the staged column segments of M (S.state 1), or leaves S.state -1
-// where they do not apply: rows over kHugeRow entries, a vector of few segments,
-// too much padding.
+// where they do not apply: rows over kHugeRow entries, a vector of few segments
+// (fewer than groups), too much padding.
 void staged_build(DevMatrix &M, int cus, StagedMem &S);
 void staged_free(StagedMem &S);
 void dm_free(DevMatrix &M);

@@ -137,6 +137,7 @@ void staged_build(DevMatrix &M, int cus, StagedMem &S) {
         seg = seg / 256 * 256;
         const int32_t nseg = (ncols + seg - 1) / seg;
         seg = std::min(seg, ((ncols + nseg - 1) / nseg + 255) / 256 * 256);
+        if (nseg < groups) return;   // a group would have no segment, its first list none to begin at
         const int32_t lists = nseg * kStagedWaves;   // per block
         std::vector<int32_t> off((size_t)nb * lists + 1, 0);
         const int64_t room = M.nnz + M.nnz / 8;   // more padding than that does not pay

@@ -33,3 +33,9 @@ def test_staged_segments_stay_in_their_buffers(host_checks, rows, cols, last):
     product inside its buffer, the sums exact."""
     out = host_checks("staged", rows, cols, 33 if cols > 53_000 else 24)
     assert out.startswith("taken") and f"{last} in the last" in out
+
+
+@pytest.mark.parametrize("rows,cols,per_row", [(262_144, 33_000, 12), (196_608, 16_384, 4), (196_608, 40_000, 20)])
+def test_staged_segments_need_one_per_group(host_checks, rows, cols, per_row):
+    """Fewer segments than groups: no layout is built."""
+    assert "not built" in host_checks("staged", rows, cols, per_row)
