@@ -229,7 +229,11 @@ int cg_create(int32_t n, int64_t nnz, const int32_t *row_ptr, const int32_t *col
 void cg_destroy(cg_handle *h);
 
 /* Order the handle's work on this HIP stream (a hipStream_t; NULL = null
- * stream).  The library also creates private streams for p exchange. */
+ * stream).  The library also creates private streams for p exchange.  Work
+ * given to the new stream waits for products that cg_spmv left on an earlier
+ * one where both use the same work memory of the handle; a captured product is
+ * not waited for and waits for nothing, so a graph holding it has to be ordered
+ * with the handle's other work by whoever launches it. */
 int cg_set_stream(cg_handle *h, void *hip_stream);
 
 void cg_default_opts(cg_opts *o);

@@ -161,8 +161,47 @@ static void free_device(cg_handle *h) {
     if (h->h_p) hipHostFree(h->h_p);
     if (h->h_pack_d2h) hipHostFree(h->h_pack_d2h);
     if (h->h_pack_h2d) hipHostFree(h->h_pack_h2d);
+    if (h->ev_staged) hipEventDestroy(h->ev_staged);
     if (h->s_d2h) hipStreamDestroy(h->s_d2h);
     if (h->s_h2d) hipStreamDestroy(h->s_h2d);
+}
+
+// Products on staged column segments pass their sums through one array of the
+// handle, and cg_spmv returns with its product queued: what is queued on
+// another stream (cg_set_stream) has to wait for it.  The first such change of
+// stream waits for the device; from then on an event is recorded behind every
+// product, with the product and not with the change, by when its stream may be
+// gone.  (An event from the start cost every product 2 us, 168 to 170 at 900K
+// rows of 49 entries, in programs that keep to one stream.)  Under capture
+// nothing is recorded or waited for: a graph runs when it is launched, which is
+// the caller's to order.
+static bool capturing(hipStream_t s) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();   // the null stream beside a capture
+    return true;
+}
+
+// Before the handle's stream is given work that may use the staged sums.
+static int staged_wait(cg_handle *h) {
+    if (!h->staged_pending || h->staged_stream == h->stream || capturing(h->stream)) return CG_OK;
+    if (h->ev_staged) {
+        HIP_TRY(hipStreamWaitEvent(h->stream, h->ev_staged, 0));
+    } else {
+        HIP_TRY(hipDeviceSynchronize());
+        HIP_TRY(hipEventCreateWithFlags(&h->ev_staged, hipEventDisableTiming));
+    }
+    h->staged_pending = false;
+    return CG_OK;
+}
+
+// After a product has been queued and left.
+static int staged_queued(cg_handle *h) {
+    if (!h->A.use_st64 || capturing(h->stream)) return CG_OK;
+    if (h->ev_staged) HIP_TRY(hipEventRecord(h->ev_staged, h->stream));
+    h->staged_stream = h->stream;
+    h->staged_pending = true;
+    return CG_OK;
 }
 
 extern "C" void cg_default_opts(cg_opts *o) {
@@ -1320,6 +1359,7 @@ extern "C" int cg_solve_noalloc(cg_handle *h, const double *b, double *x, double
     size_t have = 0;
     HIP_TRY(hipSetDevice(h->dev));
     HIP_TRY(scratch_region(h->dev, &base, &have));
+    if (const int rc0 = staged_wait(h)) return rc0;
     if (need > have) {
         const size_t per_vec = ((have - 4 * part - 256) / 5) & ~size_t(255);
         return fail(CG_EINVAL, "n = %d needs %zu bytes of scratch; the static scratch holds %zu (at most %zu rows)",
@@ -1403,7 +1443,8 @@ static int solve_impl(cg_handle *h, const double *b, double *x, double tol, int3
     }
     if (!h->nodev) HIP_TRY(hipSetDevice(h->dev));
     const double t0 = now();
-    int rc;
+    int rc = staged_wait(h);
+    if (rc) return rc;
     // mapped / managed modes: the solve's p is the shared allocation
     struct PSwap {
         cg_handle *h;
@@ -1504,6 +1545,7 @@ extern "C" int cg_spmv(cg_handle *h, const double *x, double *y) {
 static int spmv_impl(cg_handle *h, const double *x, double *y) {
     HIP_TRY(hipSetDevice(h->dev));
     const int32_t n = h->n, rb = h->rb, re = h->re, m = h->m;
+    if (const int rc = staged_wait(h)) return rc;
     if (h->gpu_only()) {
         if (h->nnz == 0) {
             HIP_TRY(hipMemsetAsync(y, 0, sizeof(double) * n, h->stream));
@@ -1513,7 +1555,7 @@ static int spmv_impl(cg_handle *h, const double *x, double *y) {
         Ad.march = 2;
         HIP_TRY(launch_spmv(Ad, h->A.sched, h->A.grid, x, y, nullptr, nullptr, nullptr, nullptr,
                             no_partials(), no_partials(), nullptr, kSpmvPlain, 0, h->stream));
-        return CG_OK;
+        return staged_queued(h);
     }
     // split: GPU rows on the device, host rows from a host copy of x
     double *hx = h->h_x.data(), *hq = h->h_q.data();

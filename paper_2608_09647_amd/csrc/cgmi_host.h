@@ -204,6 +204,12 @@ struct cg_handle {
     cg_opts opts{};
     hipStream_t stream = nullptr;   // caller's stream (or null stream)
     hipStream_t s_d2h = nullptr, s_h2d = nullptr;
+    // the last product cg_spmv queued that uses A's staged sums: the stream it is
+    // on and, once the handle has changed streams with one queued, the event
+    // behind it
+    hipEvent_t ev_staged = nullptr;
+    hipStream_t staged_stream = nullptr;
+    bool staged_pending = false;
     int cus = 256;
 
     // host copy of the matrix (the host complement uses its rows)

@@ -10,6 +10,9 @@
 //         columns below COLS: every index the product's kernel forms lies in
 //         its buffer, and the sums are the rows' own.  Says whether the
 //         schedule runs its products on them
+//     host_checks streams
+//         products and a solve through one handle on several streams: where
+//         they share the staged sums, each runs after the one before
 #include <hip/hip_runtime_api.h>
 
 #include <cmath>
@@ -41,13 +44,86 @@ hipError_t hipMemset(void *d, int v, size_t n) {
     std::memset(d, v, n);
     return hipSuccess;
 }
+hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind k, hipStream_t) { return hipMemcpy(d, s, n, k); }
+hipError_t hipMemsetAsync(void *d, int v, size_t n, hipStream_t) { return hipMemset(d, v, n); }
+hipError_t hipHostMalloc(void **p, size_t n, unsigned) { return hipMalloc(p, n); }
+hipError_t hipHostFree(void *p) { return hipFree(p); }
+hipError_t hipGetDeviceCount(int *n) { return *n = 1, hipSuccess; }
+hipError_t hipGetDevice(int *d) { return *d = 0, hipSuccess; }
+hipError_t hipSetDevice(int) { return hipSuccess; }
 hipError_t hipGetLastError() { return hipSuccess; }
 const char *hipGetErrorString(hipError_t) { return "error"; }
 }
 
+// Streams and events by what is known to have ended before the next command
+// on a stream: the number of the last product.
+struct ihipStream_t {
+    bool capture = false;
+    int after = 0;
+};
+struct ihipEvent_t {
+    int after = 0;
+};
+static int g_products = 0, g_ended = 0, g_waits = 0;
+static std::string g_fault;
+
+extern "C" {
+hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) { return *e = new ihipEvent_t(), hipSuccess; }
+hipError_t hipEventDestroy(hipEvent_t e) {
+    delete e;
+    return hipSuccess;
+}
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
+    if (s->capture) g_fault = "an event recorded under capture";
+    e->after = s->after;
+    return hipSuccess;
+}
+hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned) {
+    if (s->capture) g_fault = "a wait under capture";
+    s->after = std::max(s->after, e->after);
+    ++g_waits;
+    return hipSuccess;
+}
+hipError_t hipDeviceSynchronize() {
+    g_ended = g_products;
+    ++g_waits;
+    return hipSuccess;
+}
+hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus *status) {
+    *status = s->capture ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+    return hipSuccess;
+}
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+}
+
 namespace cgmi {
 hipError_t staged_setup() { return hipSuccess; }
+hipError_t scratch_setup() { return hipSuccess; }
+int device_cu_count() { return 256; }
+int small_path_max_rows() { return 4096; }
+int resident_groups(int32_t, int32_t, int) { return 0; }
+// Ends a solve at once: the state copied back says so (all memory is the host's).
+hipError_t launch_spmv(const CsrDev &A, const Schedule &, int, const double *, double *, const double *, const double *,
+                       double *, double *, Partials, Partials, DevState *st, int, int, hipStream_t s) {
+    if (A.st64 && !s->capture) {
+        if (std::max(s->after, g_ended) < g_products) g_fault = "a product beside one that is not known to have ended";
+        s->after = ++g_products;
+    }
+    if (st) st->done = kDoneConverged;
+    return hipSuccess;
 }
+hipError_t launch_update_r(int32_t, int, double *, const double *, double *, Partials, DevState *, int, hipStream_t) {
+    return hipSuccess;
+}
+hipError_t launch_update_pxb(int32_t, int, double *, const double *, const double *, double *, Partials, DevState *, int,
+                             hipStream_t) {
+    return hipSuccess;
+}
+bool spmv_dir_applies(const CsrDev &, const Schedule &, int, const void *, const void *, const void *, const void *,
+                      const void *) {
+    return false;
+}
+}  // namespace cgmi
 
 // ---------------------------------------------------------------------------
 
@@ -186,12 +262,41 @@ void check_staged(int32_t rows, int32_t cols, int32_t per_row) {
     dm_free(M);
 }
 
+void check_streams() {
+    const int32_t n = 299521;
+    const Matrix A = random_rows(n, n, 33);
+    cg_handle *h = nullptr;
+    REQUIRE(cg_create(n, (int64_t)A.ci.size(), A.rp.data(), A.ci.data(), A.val.data(), 0, n, &h) == CG_OK, "create");
+    REQUIRE(h->A.use_st64, "no staged segments");
+    ihipStream_t s[4], graph;
+    graph.capture = true;
+    std::vector<double> x((size_t)n, 1.0), y((size_t)n);
+    auto on = [&](ihipStream_t &st) { REQUIRE(cg_set_stream(h, &st) == CG_OK, "set_stream"); };
+    auto product = [&] { REQUIRE(cg_spmv(h, x.data(), y.data()) == CG_OK, "spmv"); };
+    on(s[0]);
+    product();
+    product();
+    REQUIRE(g_waits == 0, "%d waits on one stream", g_waits);
+    for (int k : {1, 0, 2, 2, 1}) {
+        on(s[k]);
+        product();
+    }
+    on(graph);   // an eager product is pending: a captured one leaves it so
+    product();
+    on(s[3]);
+    cg_result res;
+    REQUIRE(cg_solve(h, x.data(), y.data(), 0.0, 1, &res) >= 0, "solve");
+    REQUIRE(g_fault.empty(), "%s", g_fault.c_str());
+    cg_destroy(h);
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "staged" && argc == 5) check_staged(std::atoi(argv[2]), std::atoi(argv[3]), std::atoi(argv[4]));
-    else die("usage: host_checks staged ROWS COLS PER_ROW");
+    else if (what == "streams") check_streams();
+    else die("usage: host_checks staged ROWS COLS PER_ROW | streams");
     std::printf("ok\n");
     return 0;
 }

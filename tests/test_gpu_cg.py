@@ -1396,3 +1396,36 @@ def test_staged_segments_at_the_end_of_the_vector(cg, n, cols, per_row):
     with cg.Solver(A) as s:
         assert used_kind(s, n) == 1
         assert np.array_equal(host(s.spmv(dev(x))), oracle.spmv(A, x))
+
+
+def test_staged_products_on_several_streams(cg):
+    """Products through one handle queued on two streams without a
+    synchronisation between them, and one captured in a graph that is replayed
+    between eager ones: each the product of its own vector, bit for bit (the
+    groups' sums of a product are in memory of the handle)."""
+    n = 299_521
+    A = prefix_rows(n, n, 33)
+    xs = [dev(np.random.default_rng(k).uniform(-1, 1, n)) for k in range(2)]
+    ys = [torch.empty_like(x) for x in xs]
+    streams = [torch.cuda.Stream() for _ in xs]
+    with cg.Solver(A) as s:
+        want = [s.spmv(x).clone() for x in xs]
+        torch.cuda.synchronize()
+        for rep in range(10):
+            for x, y, st in zip(xs, ys, streams):
+                s.set_stream(st)
+                s.spmv(x, y)
+            torch.cuda.synchronize()
+            assert all(torch.equal(y, w) for y, w in zip(ys, want)), rep
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            s.set_stream(torch.cuda.current_stream())
+            s.spmv(xs[0], ys[0])
+        s.set_stream(streams[1])
+        for rep in range(3):
+            ys[0].zero_()
+            graph.replay()
+            torch.cuda.synchronize()
+            s.spmv(xs[1], ys[1])
+            torch.cuda.synchronize()
+            assert all(torch.equal(y, w) for y, w in zip(ys, want)), rep

@@ -39,3 +39,10 @@ def test_staged_segments_stay_in_their_buffers(host_checks, rows, cols, last):
 def test_staged_segments_need_one_per_group(host_checks, rows, cols, per_row):
     """Fewer segments than groups: no layout is built."""
     assert "not built" in host_checks("staged", rows, cols, per_row)
+
+
+def test_products_on_several_streams_are_ordered(host_checks):
+    """Products and a solve through one handle on several streams: each that
+    shares the staged sums waits for the one before, and nothing is recorded
+    or waited for under capture."""
+    host_checks("streams")
