@@ -64,16 +64,15 @@ template <int CH>
 __device__ __forceinline__ void segment_load(const StagedDev &D, const double *__restrict__ p, int seg,
                                              Piece (&r)[CH]) {
     constexpr int E = 16 / sizeof(double);
-    const int s = min(seg, D.nseg - 1);
-    const double *const base = p + (int64_t)s * D.seg_cols;   // uniform
+    const double *const base = p + (int64_t)min(seg, D.nseg - 1) * D.seg_cols;   // uniform
     if (seg < D.nseg - 1 && D.seg_cols == CH * kST * E) {
 #pragma unroll
         for (int u = 0; u < CH; ++u) __builtin_memcpy(&r[u], base + u * kST * E + (uint32_t)threadIdx.x * E, 16);
     } else {
-        const int last = staged_last_pair(D.ncols - s * D.seg_cols, D.seg_cols);
-        const double *const from = base + staged_pair_base(last);
+        const int last = staged_last_pair(D.ncols - min(seg, D.nseg - 1) * D.seg_cols, D.seg_cols);
 #pragma unroll
-        for (int u = 0; u < CH; ++u) __builtin_memcpy(&r[u], from + staged_pair((u * kST + (int)threadIdx.x) * E, last), 16);
+        for (int u = 0; u < CH; ++u)
+            __builtin_memcpy(&r[u], base + (uint32_t)min((u * kST + (int)threadIdx.x) * E, last), 16);
     }
 }
 
@@ -261,7 +260,8 @@ __global__ __launch_bounds__(kBlock) void k_staged_end(int32_t m, int32_t ngroup
 hipError_t launch_sums(const StagedDev &D, const double *p, const DevState *st, hipStream_t s) {
     const size_t lds = staged_lds(D.seg_cols, D.max_slots);
     const int chunks = (int)((D.seg_cols * sizeof(double) / 16 + kST - 1) / kST);
-    if (lds > kStagedLds || chunks > kStagedChunks) return hipErrorInvalidValue;
+    if (lds > kStagedLds || chunks > kStagedChunks || D.ncols - (D.nseg - 1) * D.seg_cols < 2)
+        return hipErrorInvalidValue;
 #define CGMI_STAGED(CH, K)                                                                                    \
     hipLaunchKernelGGL((k_staged_sums<CH, K>), dim3(D.nblocks * D.ngroups), dim3(kST), lds, s, D, p, D.off, \
                        D.idx, D.val, st)

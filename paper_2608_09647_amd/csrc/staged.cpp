@@ -132,11 +132,11 @@ void staged_build(DevMatrix &M, int cus, StagedMem &S) {
             }
             if (r < m) return;   // the cap left rows over
         }
-        int32_t seg = (int32_t)std::min<size_t>(max_seg, (kStagedLds - sizeof(double) * ((size_t)max_slots + 1)) /
-                                                             (2 * sizeof(double)));
-        seg = seg / 256 * 256;
+        const int32_t seg = staged_width(
+            ncols, (int32_t)std::min<size_t>(max_seg, (kStagedLds - sizeof(double) * ((size_t)max_slots + 1)) /
+                                                          (2 * sizeof(double))));
+        if (!seg) return;
         const int32_t nseg = (ncols + seg - 1) / seg;
-        seg = std::min(seg, ((ncols + nseg - 1) / nseg + 255) / 256 * 256);
         if (nseg < groups) return;   // a group would have no segment, its first list none to begin at
         const int32_t lists = nseg * kStagedWaves;   // per block
         std::vector<int32_t> off((size_t)nb * lists + 1, 0);

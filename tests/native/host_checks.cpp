@@ -10,6 +10,8 @@
 //         columns below COLS: every index the product's kernel forms lies in
 //         its buffer, and the sums are the rows' own.  Says whether the
 //         schedule runs its products on them
+//     host_checks widths
+//         the widths of segments for numbers of columns and widest segments
 //     host_checks streams
 //         products and a solve through one handle on several streams: where
 //         they share the staged sums, each runs after the one before
@@ -189,7 +191,7 @@ std::vector<double> staged_product(const StagedDev &S, const std::vector<double>
                 int64_t at = first + k;
                 if (!(seg < S.nseg - 1 && S.seg_cols == chunks * threads * E)) {
                     const int32_t last = staged_last_pair(S.ncols - s * S.seg_cols, S.seg_cols);
-                    at = first + staged_pair_base(last) + (int64_t)staged_pair(k, last);
+                    at = first + (int64_t)(uint32_t)std::min(k, last);
                 }
                 REQUIRE(at >= 0 && at + E <= S.ncols, "segment %d of %d reads p[%lld] of %d", (int)seg, S.nseg,
                         (long long)at, S.ncols);
@@ -262,6 +264,23 @@ void check_staged(int32_t rows, int32_t cols, int32_t per_row) {
     dm_free(M);
 }
 
+// Every remainder of the last segment but one column, none of them empty; the
+// equal parts as long as their last one is no single column.
+void check_widths() {
+    std::mt19937 rng(3);
+    for (int32_t widest = 256; widest <= 8192; widest += 256)
+        for (int32_t k = 0; k < 20000; ++k) {
+            // whole segments and up to 3 columns more, and any number
+            const int32_t n = k & 1 ? widest * (2 + k / 8) + (k / 2) % 4 : 16384 + (int32_t)(rng() % 4000000u);
+            const int32_t w = staged_width(n, widest + (int32_t)(rng() % 256u));
+            if (w == 0) continue;
+            const int32_t nseg = (n + w - 1) / w, left = n - (nseg - 1) * w;
+            REQUIRE(w % 256 == 0 && w > 0 && w <= widest, "%d columns, at most %d: %d", n, widest, w);
+            REQUIRE(left >= 2 && left <= w, "%d columns by %d: %d left", n, w, left);
+        }
+    REQUIRE(staged_width(299521, 7771) == 7424 && staged_width(299522, 7771) == 7680, "299521 and 299522 columns");
+}
+
 void check_streams() {
     const int32_t n = 299521;
     const Matrix A = random_rows(n, n, 33);
@@ -295,8 +314,9 @@ void check_streams() {
 int main(int argc, char **argv) {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "staged" && argc == 5) check_staged(std::atoi(argv[2]), std::atoi(argv[3]), std::atoi(argv[4]));
+    else if (what == "widths") check_widths();
     else if (what == "streams") check_streams();
-    else die("usage: host_checks staged ROWS COLS PER_ROW | streams");
+    else die("usage: host_checks staged ROWS COLS PER_ROW | widths | streams");
     std::printf("ok\n");
     return 0;
 }

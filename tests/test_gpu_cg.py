@@ -1385,12 +1385,14 @@ def prefix_rows(n, cols, per_row, seed=13):
 
 
 @pytest.mark.parametrize("n,cols,per_row", [
-    (299_521, 299_521, 33), (299_522, 299_522, 33), (299_519, 299_519, 33),   # 1, 2 and all columns but one
+    # one column over equal parts, 2 in the last one, all columns but one
+    (299_521, 299_521, 33), (299_522, 299_522, 33), (299_519, 299_519, 33),
     (262_144, 52_993, 24)])                                                     # a prefix of the columns
 def test_staged_segments_at_the_end_of_the_vector(cg, n, cols, per_row):
-    """Products on staged column segments whose last segment has one column,
-    two or all but one, and with columns that no row uses: exact sums of
-    integers, x ending where its allocation does."""
+    """Products on staged column segments where equal parts would leave one
+    column for the last segment, where that has two or all but one, and with
+    columns that no row uses: exact sums of integers, x ending where its
+    allocation does."""
     A = prefix_rows(n, cols, per_row)
     x = np.random.default_rng(15).integers(-8, 9, n).astype(np.float64)
     with cg.Solver(A) as s:

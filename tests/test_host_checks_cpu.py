@@ -25,14 +25,20 @@ def host_checks():
 
 
 @pytest.mark.parametrize("rows,cols,last", [
-    (299_521, 299_521, 1), (299_522, 299_522, 2), (299_523, 299_523, 3), (299_519, 299_519, 7679),
+    (299_521, 299_521, 2561), (307_201, 307_201, 2817), (299_522, 299_522, 2), (299_523, 299_523, 3), (299_519, 299_519, 7679),
     (299_520, 299_520, 7680), (262_144, 52_993, 4353)])
 def test_staged_segments_stay_in_their_buffers(host_checks, rows, cols, last):
-    """Staged column segments whose last one has one column, two, three, all
-    but one and all, and columns past the last used one: every index of the
+    """Staged column segments of numbers of columns that equal parts would leave
+    one over (the first two), whose last segment has two columns, three, all
+    but one and all, and with columns that no row uses: every index of the
     product inside its buffer, the sums exact."""
     out = host_checks("staged", rows, cols, 33 if cols > 53_000 else 24)
     assert out.startswith("taken") and f"{last} in the last" in out
+
+
+def test_staged_segments_have_no_single_last_column(host_checks):
+    """The width of segments over numbers of columns and widest segments."""
+    host_checks("widths")
 
 
 @pytest.mark.parametrize("rows,cols,per_row", [(262_144, 33_000, 12), (196_608, 16_384, 4), (196_608, 40_000, 20)])
