@@ -584,8 +584,9 @@ int one_launch_result(const DevState &s, double t_gpu, cg_result *res) {
         res->status = status;
         res->iterations = s.iter;
         res->converged = status == CG_OK;
-        res->rel_res_recur = s.bb > 0.0 ? std::sqrt(s.rr) / std::sqrt(s.bb) : 0.0;
-        res->rel_res_true = s.bb > 0.0 ? std::sqrt(s.rr_true) / std::sqrt(s.bb) : 0.0;
+        // (b = 0: x = 0; a norm that is not a number stays one)
+        res->rel_res_recur = s.bb == 0.0 ? 0.0 : std::sqrt(s.rr) / std::sqrt(s.bb);
+        res->rel_res_true = s.bb == 0.0 ? 0.0 : std::sqrt(s.rr_true) / std::sqrt(s.bb);
         res->t_gpu = t_gpu;
     }
     return status;

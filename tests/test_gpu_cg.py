@@ -1431,3 +1431,28 @@ def test_staged_products_on_several_streams(cg):
             s.spmv(xs[1], ys[1])
             torch.cuda.synchronize()
             assert all(torch.equal(y, w) for y, w in zip(ys, want)), rep
+
+
+@pytest.mark.parametrize("bad", [np.nan, np.inf])
+@pytest.mark.parametrize("name", ["one_workgroup", "row_per_thread", "window", "preconditioned"])
+def test_one_launch_solves_report_what_is_not_finite(cg, name, bad):
+    """A right-hand side with an entry that is not finite: the solves in one
+    launch end as the separate kernels do, with a breakdown, x as given and
+    no finite residual."""
+    side = {"one_workgroup": 40, "row_per_thread": 150, "window": 530, "preconditioned": 150}[name]
+    A = I.diffusion2d(I.log_normal_field(side, side, 3, 0.5))
+    b = np.ones(A.n)
+    b[A.n // 3] = bad
+    x0 = np.random.default_rng(2).uniform(-1, 1, A.n)
+    out = {}
+    for small in (1, 0):
+        with cg.Solver(A) as s:
+            if name == "preconditioned":
+                s.fsai_classic()
+            s.set_opts(small_path=small, precond=cg.PC_FSAI if name == "preconditioned" else cg.PC_NONE)
+            x, res = s.solve(dev(b), dev(x0), tol=1e-8, maxit=50)
+            out[small] = host(x), res
+    for x, res in out.values():
+        assert res["code"] == cg.CG_EBREAKDOWN and res["iterations"] == 0 and not res["converged"]
+        assert np.array_equal(x, x0)
+        assert not np.isfinite(res["rel_res_true"]) and not np.isfinite(res["rel_res_recur"])
