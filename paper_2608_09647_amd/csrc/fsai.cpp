@@ -754,15 +754,17 @@ int ensure_capacity(T **p, size_t &cap, size_t need) {
     return CG_OK;
 }
 
-// The device staging buffer and its page-locked source, at least `need` bytes
-// (no step is in flight: every step ends with a synchronisation).
+// The device staging buffer and its page-locked source, both of stage_cap
+// bytes, at least `need` (no step is in flight: every step ends with a
+// synchronisation).  After a failure the source may be missing while the
+// device buffer is larger than the next need.
 int ensure_stage(cg_fsai_trainer *t, size_t need) {
     if (need <= t->stage_cap && t->h_stage) return CG_OK;
     const int rc = ensure_capacity(&t->d_stage, t->stage_cap, need);
     if (rc) return rc;
     (void)hipHostFree(t->h_stage);
     t->h_stage = nullptr;
-    if (hipHostMalloc(reinterpret_cast<void **>(&t->h_stage), need) != hipSuccess)
+    if (hipHostMalloc(reinterpret_cast<void **>(&t->h_stage), t->stage_cap) != hipSuccess)
         return fail(CG_ENOMEM, "trainer staging: page-locked memory");
     return CG_OK;
 }

@@ -12,6 +12,9 @@
 //         schedule runs its products on them
 //     host_checks widths
 //         the widths of segments for numbers of columns and widest segments
+//     host_checks stage
+//         a trainer's steps after a page-locked allocation failed: none writes
+//         past the buffer that a later one got
 //     host_checks streams
 //         products and a solve through one handle on several streams: where
 //         they share the staged sums, each runs after the one before
@@ -25,7 +28,9 @@
 #include <string>
 #include <vector>
 
+#include "../../include/cgmi_fsai.h"
 #include "../../paper_2608_09647_amd/csrc/cgmi_host.h"
+#include "../../paper_2608_09647_amd/csrc/fsai_internal.h"
 
 using namespace cgmi;
 
@@ -48,8 +53,26 @@ hipError_t hipMemset(void *d, int v, size_t n) {
 }
 hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind k, hipStream_t) { return hipMemcpy(d, s, n, k); }
 hipError_t hipMemsetAsync(void *d, int v, size_t n, hipStream_t) { return hipMemset(d, v, n); }
-hipError_t hipHostMalloc(void **p, size_t n, unsigned) { return hipMalloc(p, n); }
-hipError_t hipHostFree(void *p) { return hipFree(p); }
+// Page-locked memory: its size in front, kGuard bytes behind that nothing writes.
+constexpr size_t kHead = 64, kGuard = 1 << 16;
+static bool g_no_pinned = false, g_overrun = false;
+hipError_t hipHostMalloc(void **p, size_t n, unsigned) {
+    if (g_no_pinned) return hipErrorOutOfMemory;
+    unsigned char *const b = static_cast<unsigned char *>(std::malloc(kHead + n + kGuard));
+    std::memcpy(b, &n, sizeof n);
+    std::memset(b + kHead + n, 0xA5, kGuard);
+    *p = b + kHead;
+    return hipSuccess;
+}
+hipError_t hipHostFree(void *p) {
+    if (!p) return hipSuccess;
+    unsigned char *const b = static_cast<unsigned char *>(p) - kHead;
+    size_t n;
+    std::memcpy(&n, b, sizeof n);
+    for (size_t i = 0; i < kGuard; ++i) g_overrun |= b[kHead + n + i] != 0xA5;
+    std::free(b);
+    return hipSuccess;
+}
 hipError_t hipGetDeviceCount(int *n) { return *n = 1, hipSuccess; }
 hipError_t hipGetDevice(int *d) { return *d = 0, hipSuccess; }
 hipError_t hipSetDevice(int) { return hipSuccess; }
@@ -119,6 +142,27 @@ hipError_t launch_update_r(int32_t, int, double *, const double *, double *, Par
 }
 hipError_t launch_update_pxb(int32_t, int, double *, const double *, const double *, double *, Partials, DevState *, int,
                              hipStream_t) {
+    return hipSuccess;
+}
+hipError_t fsai_prepare(int32_t, const int32_t *, const int32_t *, const double *, int32_t *, float *, double *,
+                        uint16_t *, int32_t *, hipStream_t) {
+    return hipSuccess;
+}
+hipError_t fsai_forward_outputs(int32_t, const int32_t *, int64_t, const uint16_t *, const float *, float *, int64_t *,
+                                hipStream_t) {
+    return hipSuccess;
+}
+hipError_t fsai_loss(int32_t, int32_t, const int32_t *, const int64_t *, const int32_t *, const float *,
+                     const int32_t *, const float *, int64_t *, float, double *, hipStream_t) {
+    return hipSuccess;
+}
+hipError_t fsai_backward(int32_t, const int32_t *, const uint16_t *, const float *, const float *, const int64_t *,
+                         const int32_t *, float *, int32_t, hipStream_t) {
+    return hipSuccess;
+}
+hipError_t fsai_adam(int32_t, const double *, double *loss, int32_t, const float *, float *, float *, float *, float *,
+                     int32_t, float, hipStream_t) {
+    *loss = 0.0;
     return hipSuccess;
 }
 bool spmv_dir_applies(const CsrDev &, const Schedule &, int, const void *, const void *, const void *, const void *,
@@ -281,6 +325,32 @@ void check_widths() {
     REQUIRE(staged_width(299521, 7771) == 7424 && staged_width(299522, 7771) == 7680, "299521 and 299522 columns");
 }
 
+void check_stage() {
+    constexpr int32_t nsys = 4, n = 64;
+    std::vector<int32_t> rp(n + 1), ci(n), sizes(nsys, n), sys{0, 1, 2, 3}, rows(4 * 1024, 1);
+    std::vector<double> val(n, 1.0);
+    for (int32_t i = 0; i <= n; ++i) rp[(size_t)i] = i;
+    for (int32_t i = 0; i < n; ++i) ci[(size_t)i] = i;
+    const std::vector<int64_t> nnz(nsys, n);
+    const std::vector<const int32_t *> rps(nsys, rp.data()), cis(nsys, ci.data());
+    const std::vector<const double *> vals(nsys, val.data());
+    const std::vector<float> theta(kNParams, 0.0f);
+    cg_fsai_trainer *t = nullptr;
+    REQUIRE(cg_fsai_trainer_create(nsys, sizes.data(), nnz.data(), rps.data(), cis.data(), vals.data(), theta.data(),
+                                   &t) == CG_OK, "%s", cg_last_error());
+    std::vector<float> grad(kNParams);
+    double loss = 0.0;
+    auto step = [&](int32_t nsel, int32_t per) {
+        return cg_fsai_loss_grad(t, nullptr, nsel, sys.data(), per, rows.data(), &loss, grad.data(), nullptr);
+    };
+    g_no_pinned = true;
+    REQUIRE(step(4, 1024) == CG_ENOMEM, "no page-locked memory");   // the device buffer has grown
+    g_no_pinned = false;
+    REQUIRE(step(1, 16) == CG_OK && step(2, 512) == CG_OK && step(4, 1024) == CG_OK, "%s", cg_last_error());
+    cg_fsai_trainer_destroy(t);
+    REQUIRE(!g_overrun, "a step wrote past its page-locked buffer");
+}
+
 void check_streams() {
     const int32_t n = 299521;
     const Matrix A = random_rows(n, n, 33);
@@ -315,8 +385,9 @@ int main(int argc, char **argv) {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "staged" && argc == 5) check_staged(std::atoi(argv[2]), std::atoi(argv[3]), std::atoi(argv[4]));
     else if (what == "widths") check_widths();
+    else if (what == "stage") check_stage();
     else if (what == "streams") check_streams();
-    else die("usage: host_checks staged ROWS COLS PER_ROW | widths | streams");
+    else die("usage: host_checks staged ROWS COLS PER_ROW | widths | stage | streams");
     std::printf("ok\n");
     return 0;
 }

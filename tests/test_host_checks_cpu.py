@@ -52,3 +52,9 @@ def test_products_on_several_streams_are_ordered(host_checks):
     shares the staged sums waits for the one before, and nothing is recorded
     or waited for under capture."""
     host_checks("streams")
+
+
+def test_trainer_stage_after_a_failed_allocation(host_checks):
+    """Steps of a trainer, smaller and then larger, after its page-locked
+    allocation failed once: none writes past the buffer."""
+    host_checks("stage")
