@@ -25,6 +25,8 @@
 #include <math.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "cgmi_internal.h"
 #include "fsai_internal.h"
 
@@ -500,15 +502,33 @@ __global__ __launch_bounds__(256, 8) void k_fsai_loss(int32_t nsamp, int32_t row
 // rows of one unit per lane, where the forward fragments hold four units of
 // one row: 16x16 blocks transposed.  A fragment read as an A operand is its
 // block transposed already, so one product with the identity returns it in the
-// other layout, exactly (each sum has one nonzero term, a bfloat16 value).
-// Through LDS the 72 two-byte writes a tile took, four to a bank, were 1.5 us
-// of its 2.7.
+// other layout, exactly as long as the block is finite (each sum has one
+// nonzero term, a bfloat16 value; an infinity would meet the identity's zeros
+// and turn its line into NaN).  Through LDS the 72 two-byte writes a tile took,
+// four to a bank, were 1.5 us of its 2.7; a wavefront whose gradients hold
+// something not finite goes over its tiles again that way.
 __device__ __forceinline__ bf16x4 transpose16(bf16x4 x, bf16x4 ident) {
     const f32x4 c = mfma(x, ident, zero4());
     // the upper halves of the float32 values
     const uint32_t lo = __builtin_amdgcn_perm(__float_as_uint(c[1]), __float_as_uint(c[0]), 0x07060302);
     const uint32_t hi = __builtin_amdgcn_perm(__float_as_uint(c[3]), __float_as_uint(c[2]), 0x07060302);
     return __builtin_bit_cast(bf16x4, (uint64_t)lo | (uint64_t)hi << 32);
+}
+
+// The same for any values, through the wavefront's 16 x 16 entries of LDS.
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+__device__ __forceinline__ bf16x4 transpose16_lds(bf16x4 x, uint16_t (*flip)[16]) {
+    const int l = threadIdx.x & (kW - 1), r = l & 15, q = l >> 4;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) flip[4 * q + v][r] = (uint16_t)x[v];
+    wave_sync();
+    const bf16x4 t = lds4(&flip[r][4 * q]);
+    wave_sync();   // the next block overwrites them
+    return t;
 }
 
 template <int CTRL>
@@ -533,6 +553,7 @@ __global__ __launch_bounds__(256) void k_fsai_backward(int32_t ntiles, const int
                                                        const int32_t *__restrict__ scol,
                                                        float *__restrict__ gpart) {
     __shared__ float grad[4][kNParams];
+    __shared__ alignas(16) uint16_t flip[4][16][16];
     const int l = threadIdx.x & (kW - 1);
     const int r = l & 15, q = l >> 4;
     const int wv = threadIdx.x / kW;
@@ -554,21 +575,7 @@ __global__ __launch_bounds__(256) void k_fsai_backward(int32_t ntiles, const int
 #pragma unroll
             for (int j = 0; j < 8; ++j) w2t[t][h][j] = (short)P.w2[unit32(h, q, j)][16 * t + r];
     f32x4 gw1[4], gw2[4][4], gw3[4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        gw1[t] = zero4();
-        gw3[t] = zero4();
-#pragma unroll
-        for (int s = 0; s < 4; ++s) gw2[t][s] = zero4();
-    }
     float gb1[4][4], gb2[4][4], gb3[4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) gb1[t][v] = gb2[t][v] = 0.f;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) gb3[v] = 0.f;
-
     const int wave = blockIdx.x * 4 + wv;
     const int nwaves = gridDim.x * 4;
     // what a tile reads is loaded while the one before is computed, its row
@@ -593,69 +600,101 @@ __global__ __launch_bounds__(256) void k_fsai_backward(int32_t ntiles, const int
     bf16x4 ident;   // B operand
 #pragma unroll
     for (int v = 0; v < 4; ++v) ident[v] = 4 * q + v == r ? (short)0x3F80 : (short)0;
-    TileIn next = load_in(row_of(wave));
-    int64_t row_next = row_of(wave + nwaves);
-    for (int tt = wave; tt < ntiles; tt += nwaves) {
-        const TileIn in = next;
-        next = load_in(row_next);
-        row_next = row_of(tt + 2 * nwaves);
-        Fwd Y;
-        forward_tile(W, P, in.fin, Y);
-        // dz3 (outputs 4q+v of row r)
-        // dL/do of row r from dL/dG~: through the softplus for C, directly for
-        // the W and S slots the row has, zero for the unused E and N
-        bf16x4 d3;
-        const float sig = 1.f / (1.f + expf(-in.oc));
-        float dgr[3];
+    // the wavefront's tiles; by_lds: the blocks transposed there
+    auto all_tiles = [&](auto by_lds) {
+        auto flipped = [&](bf16x4 x) {
+            if constexpr (decltype(by_lds)::value) return transpose16_lds(x, flip[wv]);
+            else return transpose16(x, ident);
+        };
 #pragma unroll
-        for (int b = 0; b < 3; ++b) dgr[b] = (float)((double)in.dg[b] * (1.0 / kDgScale));
-        const float dv[4] = {dgr[0] * sig, in.w >= 0 ? dgr[1] : 0.f, 0.f, in.s >= 0 ? dgr[2] : 0.f};
+        for (int t = 0; t < 4; ++t) {
+            gw1[t] = zero4();
+            gw3[t] = zero4();
+#pragma unroll
+            for (int s = 0; s < 4; ++s) gw2[t][s] = zero4();
+        }
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) gb1[t][v] = gb2[t][v] = 0.f;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) gb3[v] = 0.f;
+        TileIn next = load_in(row_of(wave));
+        int64_t row_next = row_of(wave + nwaves);
+        for (int tt = wave; tt < ntiles; tt += nwaves) {
+            const TileIn in = next;
+            next = load_in(row_next);
+            row_next = row_of(tt + 2 * nwaves);
+            Fwd Y;
+            forward_tile(W, P, in.fin, Y);
+            // dz3 (outputs 4q+v of row r)
+            // dL/do of row r from dL/dG~: through the softplus for C, directly for
+            // the W and S slots the row has, zero for the unused E and N
+            bf16x4 d3;
+            const float sig = 1.f / (1.f + expf(-in.oc));
+            float dgr[3];
+#pragma unroll
+            for (int b = 0; b < 3; ++b) dgr[b] = (float)((double)in.dg[b] * (1.0 / kDgScale));
+            const float dv[4] = {dgr[0] * sig, in.w >= 0 ? dgr[1] : 0.f, 0.f, in.s >= 0 ? dgr[2] : 0.f};
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const float g = q == 0 ? dv[v] : 0.f;
+                gb3[v] += g;
+                d3[v] = (short)bf16_bits(g);
+            }
+            // dz2 = (W3^T dz3) * (z2 > 0)
+            bf16x4 d2[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const f32x4 c = mfma(w3t[t], d3, zero4());
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const float g = Y.z2[t][v] > 0.f ? c[v] : 0.f;
+                    gb2[t][v] += g;
+                    d2[t][v] = (short)bf16_bits(g);
+                }
+            }
+            // dz1 = (W2^T dz2) * (z1 > 0)
+            bf16x4 d1[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                f32x4 c = zero4();
+#pragma unroll
+                for (int h = 0; h < 2; ++h) c = mfma32(w2t[t][h], cat(d2[2 * h], d2[2 * h + 1]), c);
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const float g = Y.z1[t][v] > 0.f ? c[v] : 0.f;
+                    gb1[t][v] += g;
+                    d1[t][v] = (short)bf16_bits(g);
+                }
+            }
+            // weight gradients: sums over the tile's 16 rows
+            const bf16x4 ft = flipped(in.fin), d3t = flipped(d3);
+            bf16x4 h1t[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) h1t[t] = flipped(half(Y.h1[t >> 1], t & 1));
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                gw1[t] = mfma(flipped(d1[t]), ft, gw1[t]);
+                const bf16x4 a2 = flipped(d2[t]);
+#pragma unroll
+                for (int s = 0; s < 4; ++s) gw2[t][s] = mfma(a2, h1t[s], gw2[t][s]);
+                gw3[t] = mfma(d3t, flipped(half(Y.h2[t >> 1], t & 1)), gw3[t]);
+            }
+        }
+    };
+    all_tiles(std::false_type{});
+    float check = 0.f;   // or NaN, where a gradient is not finite (0.6 us of a pass of 96)
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            const float g = q == 0 ? dv[v] : 0.f;
-            gb3[v] += g;
-            d3[v] = (short)bf16_bits(g);
+            check = fmaf(gw1[t][v], 0.f, check);
+            check = fmaf(gw3[t][v], 0.f, check);
+#pragma unroll
+            for (int s = 0; s < 4; ++s) check = fmaf(gw2[t][s][v], 0.f, check);
         }
-        // dz2 = (W3^T dz3) * (z2 > 0)
-        bf16x4 d2[4];
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            const f32x4 c = mfma(w3t[t], d3, zero4());
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const float g = Y.z2[t][v] > 0.f ? c[v] : 0.f;
-                gb2[t][v] += g;
-                d2[t][v] = (short)bf16_bits(g);
-            }
-        }
-        // dz1 = (W2^T dz2) * (z1 > 0)
-        bf16x4 d1[4];
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            f32x4 c = zero4();
-#pragma unroll
-            for (int h = 0; h < 2; ++h) c = mfma32(w2t[t][h], cat(d2[2 * h], d2[2 * h + 1]), c);
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const float g = Y.z1[t][v] > 0.f ? c[v] : 0.f;
-                gb1[t][v] += g;
-                d1[t][v] = (short)bf16_bits(g);
-            }
-        }
-        // weight gradients: sums over the tile's 16 rows
-        const bf16x4 ft = transpose16(in.fin, ident), d3t = transpose16(d3, ident);
-        bf16x4 h1t[4];
-#pragma unroll
-        for (int t = 0; t < 4; ++t) h1t[t] = transpose16(half(Y.h1[t >> 1], t & 1), ident);
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            gw1[t] = mfma(transpose16(d1[t], ident), ft, gw1[t]);
-            const bf16x4 a2 = transpose16(d2[t], ident);
-#pragma unroll
-            for (int s = 0; s < 4; ++s) gw2[t][s] = mfma(a2, h1t[s], gw2[t][s]);
-            gw3[t] = mfma(d3t, transpose16(half(Y.h2[t >> 1], t & 1), ident), gw3[t]);
-        }
-    }
+    if (__any(!(check == 0.f))) all_tiles(std::true_type{});
     // bias sums: reduce over the 16 rows held by lanes r = 0..15
 #pragma unroll
     for (int t = 0; t < 4; ++t)

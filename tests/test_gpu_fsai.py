@@ -132,6 +132,47 @@ def test_loss_and_gradient_match_oracle(cg, seed):
     tr.close()
 
 
+def test_gradient_beside_infinite_activations(cg):
+    """A hidden unit that overflows in a few rows, none of which a sample
+    reaches: its own output weights' gradients are NaN (0 x infinity), every
+    other one is the oracle's (whose unit stays at 0 there)."""
+    A = field(36, 28, 12)
+    F = OF.bf16(OF.features(A))
+    j, p, u = 4, 9, 21                                     # feature, first and second hidden unit
+    vals = np.unique(F[:, j])
+    cut = int(0.98 * vals.size)
+    thr = 0.5 * (vals[cut - 1] + vals[cut])
+    scale = float(OF.bf16(np.array([1e30]))[0])
+    far = F[:, j] > thr
+    near_far = far.astype(np.float64)
+    M = A.scipy().copy()
+    M.data[:] = 1.0
+    for _ in range(8):
+        near_far = M @ near_far
+    rows = np.flatnonzero(near_far == 0)[::4].astype(np.int32)
+    assert far.sum() >= 5 and rows.size >= 50
+    P = OF.unpack(theta_with_biases(4).astype(np.float64))
+    P["W1"][p] = 0.0
+    P["W1"][p, j] = scale
+    P["b1"][p] = -thr * scale
+    P["W2"][:, p] = 0.0
+    P["W2"][u] = 0.0
+    P["b2"][u] = 0.0
+    P["W3"][:, u] = 1.0
+    ref_theta = OF.pack(P)
+    P["W2"][u, p] = scale                                  # 1e30 x about 1e30 where far, 0 elsewhere
+    tr = cg.FsaiTrainer([A], OF.pack(P).astype(np.float32))
+    loss, grad = tr.loss_grad([0], rows[None, :])
+    tr.close()
+    L, g = OF.network_loss(ref_theta, A, rows, round_bf16=True)
+    G, R = OF.unpack(grad.astype(np.float64)), OF.unpack(g)
+    assert abs(loss - L) <= 1e-4 * L
+    assert np.all(np.isnan(G["W3"][[0, 1, 3], u]))
+    G["W3"][:, u] = R["W3"][:, u]
+    assert np.all(np.isfinite(OF.pack(G)))
+    assert_blockwise_close(OF.pack(G), OF.pack(R), "infinite")
+
+
 def test_multi_system_loss_is_sample_weighted_mean(cg):
     systems = [field(24, 24, 20), field(30, 20, 21), field(16, 40, 22)]
     th = theta_with_biases(2)
