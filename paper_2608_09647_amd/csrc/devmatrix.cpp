@@ -827,6 +827,7 @@ int dm_schedule(DevMatrix &M, int kind_opt, int grid_opt, int cus, int grid_cap,
     // as they are, move the solution it stops at within its tolerance (1e-9 at
     // 700K rows and 1e-11), which is kept as it was
     M.use_st64 = false;
+    if (need_f32) staged_free(M.st64);   // 0.4 GB at 700K rows of 41 entries; built again if float64 returns
     if (!need_f32 && kind_opt == 0 &&
         ((M.sched.kind == kTileColBlocked && block_cols <= 0) || M.sched.kind == kTileVector) && !M.h_val.empty()) {
         int32_t ncols = 0;

@@ -12,6 +12,9 @@
 //         schedule runs its products on them
 //     host_checks widths
 //         the widths of segments for numbers of columns and widest segments
+//     host_checks mixed
+//         a handle turned to mixed precision keeps no staged column segments,
+//         and has the same ones when it is turned back
 //     host_checks stage
 //         a trainer's steps after a page-locked allocation failed: none writes
 //         past the buffer that a later one got
@@ -325,6 +328,25 @@ void check_widths() {
     REQUIRE(staged_width(299521, 7771) == 7424 && staged_width(299522, 7771) == 7680, "299521 and 299522 columns");
 }
 
+void check_mixed() {
+    const int32_t n = 200003;
+    const Matrix A = random_rows(n, n, 33);
+    DevMatrix M;
+    REQUIRE(dm_upload(M, n, A.rp.data(), A.ci.data(), A.val.data(), 0) == CG_OK, "upload");
+    auto schedule = [&](bool mixed) { REQUIRE(dm_schedule(M, 0, 0, 256, 4096, mixed) == CG_OK, "schedule"); };
+    schedule(false);
+    REQUIRE(M.use_st64, "no staged segments");
+    const size_t lists = (size_t)M.st64.dev.nblocks * kStagedWaves * M.st64.dev.nseg;
+    const std::vector<int32_t> off(M.st64.dev.off, M.st64.dev.off + lists + 1);
+    const std::vector<uint32_t> idx(M.st64.dev.idx, M.st64.dev.idx + off[lists]);
+    schedule(true);
+    REQUIRE(!M.use_st64 && !M.st64.dev.idx && !M.st64.dev.part, "still held");
+    schedule(false);
+    REQUIRE(M.use_st64 && std::equal(off.begin(), off.end(), M.st64.dev.off) &&
+                std::equal(idx.begin(), idx.end(), M.st64.dev.idx), "another layout");
+    dm_free(M);
+}
+
 void check_stage() {
     constexpr int32_t nsys = 4, n = 64;
     std::vector<int32_t> rp(n + 1), ci(n), sizes(nsys, n), sys{0, 1, 2, 3}, rows(4 * 1024, 1);
@@ -385,9 +407,10 @@ int main(int argc, char **argv) {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "staged" && argc == 5) check_staged(std::atoi(argv[2]), std::atoi(argv[3]), std::atoi(argv[4]));
     else if (what == "widths") check_widths();
+    else if (what == "mixed") check_mixed();
     else if (what == "stage") check_stage();
     else if (what == "streams") check_streams();
-    else die("usage: host_checks staged ROWS COLS PER_ROW | widths | stage | streams");
+    else die("usage: host_checks staged ROWS COLS PER_ROW | widths | mixed | stage | streams");
     std::printf("ok\n");
     return 0;
 }

@@ -58,3 +58,8 @@ def test_trainer_stage_after_a_failed_allocation(host_checks):
     """Steps of a trainer, smaller and then larger, after its page-locked
     allocation failed once: none writes past the buffer."""
     host_checks("stage")
+
+
+def test_mixed_precision_keeps_no_staged_segments(host_checks):
+    """Their memory is given back, and float64 builds the same layout again."""
+    host_checks("mixed")
