@@ -149,16 +149,7 @@ typedef struct cg_opts {
                               <= 64 nonzeros and slicing pads by <= 25%,
                               else 2 where every row fits a run and the
                               block has >= 262,144 rows of mean length <= 64
-                              or >= 131,072 of mean length <= 32, else 1.
-                              Float64 products of an automatic 1 or 5 (of the
-                              default width) run on staged column segments
-                              instead, where a model of both says they are
-                              faster: from 196,608 rows on, some 6 million
-                              entries at least, none over 4096 in a row.
-                              Segments of the vector pass through LDS, and a
-                              row's entries are summed in several parts, the
-                              same ones in every product; cg_create builds
-                              this second layout (12 bytes per entry).        */
+                              or >= 131,072 of mean length <= 32, else 1.     */
     int32_t spmv_colblock; /* columns per block of the column-blocked tiling
                               (spmv_kind 5); 0: 262,144 (2 MB of float64 p)     */
     double refine_delta;   /* mixed precision: a float64 refinement is made
@@ -220,9 +211,7 @@ typedef struct cg_result {
     int32_t spmv_kind;       /* SpMV tiling used on the GPU rows: 1 vector bins,
                                 2 stream tiles, 3 sliced tiles, 4 dictionary-
                                 sliced tiles, 5 column blocks, 6 stencil slices,
-                                7 gap-coded slices (0: no GPU rows); where
-                                staged column segments take the place of an
-                                automatic 1 or 5, still that number              */
+                                7 gap-coded slices (0: no GPU rows)              */
     int32_t fused_dir;       /* 1 if the direction update ran inside the SpMV
                                 (cg_opts.fuse_dir)                               */
 } cg_result;

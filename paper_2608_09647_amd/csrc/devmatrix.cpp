@@ -821,15 +821,16 @@ int dm_schedule(DevMatrix &M, int kind_opt, int grid_opt, int cus, int grid_cap,
     const int waves_needed = M.sched.ntiles + M.sched.huge_count * (kBlock / kWaveSize);
     const int auto_grid = ((waves_needed / (kBlock / kWaveSize) + 8) / 8) * 8;
     const int grid = std::max(8, std::min(grid_opt > 0 ? grid_opt : std::min(cus * 8, auto_grid), grid_cap) / 8 * 8);
-    // staged column segments in place of vector bins and of column blocks of the
-    // default width, where these were chosen automatically.  Not in mixed precision: a float32
+    // staged column segments in place of vector bins chosen automatically and
+    // of column blocks of the default width.  Not in mixed precision: a float32
     // inner solve follows the rounding of its products, and other sums, as exact
     // as they are, move the solution it stops at within its tolerance (1e-9 at
     // 700K rows and 1e-11), which is kept as it was
     M.use_st64 = false;
     if (need_f32) staged_free(M.st64);   // 0.4 GB at 700K rows of 41 entries; built again if float64 returns
-    if (!need_f32 && kind_opt == 0 &&
-        ((M.sched.kind == kTileColBlocked && block_cols <= 0) || M.sched.kind == kTileVector) && !M.h_val.empty()) {
+    if (!need_f32 &&
+        ((M.sched.kind == kTileColBlocked && (kind_opt == 0 || kind_opt == 5) && block_cols <= 0) ||
+         (M.sched.kind == kTileVector && kind_opt == 0)) && !M.h_val.empty()) {
         int32_t ncols = 0;
 #pragma omp parallel for reduction(max : ncols) schedule(static)
         for (int32_t i = 0; i < M.m; ++i)

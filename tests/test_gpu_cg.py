@@ -1456,21 +1456,3 @@ def test_one_launch_solves_report_what_is_not_finite(cg, name, bad):
         assert res["code"] == cg.CG_EBREAKDOWN and res["iterations"] == 0 and not res["converged"]
         assert np.array_equal(x, x0)
         assert not np.isfinite(res["rel_res_true"]) and not np.isfinite(res["rel_res_recur"])
-
-
-def test_column_blocks_asked_for_are_column_blocks(cg):
-    """spmv_kind 5 runs its passes over column blocks also where an automatic
-    choice would run staged column segments: the bits of blocks whose width is
-    given, not those of the staged product."""
-    A = scattered(200_003, 40, 30)
-    x = dev(np.random.default_rng(17).uniform(-1, 1, A.n))
-    with cg.Solver(A) as s:
-        staged = s.spmv(x).clone()
-        s.set_opts(spmv_kind=5)
-        default = s.spmv(x).clone()
-        s.set_opts(spmv_kind=5, spmv_colblock=262_144)
-        given = s.spmv(x).clone()
-        s.set_opts(spmv_kind=0, spmv_colblock=0)
-        again = s.spmv(x)
-        assert torch.equal(default, given) and torch.equal(staged, again)
-        assert not torch.equal(default, staged)
