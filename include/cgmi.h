@@ -105,9 +105,13 @@ typedef struct cg_opts {
                               5) whose share of a compute unit fits its
                               registers and LDS (up to about 10,000 rows,
                               7,000 with a factor), where profile is off,
-                              fuse_dir automatic and spmv_kind 0 or 6;
+                              fuse_dir automatic and spmv_kind 0 or 6
+                              (spmv_grid and check_every have no part in a
+                              solve of one launch);
                               0: always several kernels                    */
-    int32_t spmv_grid;     /* workgroups of the SpMV kernels (0: automatic)      */
+    int32_t spmv_grid;     /* workgroups of the SpMV kernels (0: automatic); of
+                              staged column segments, of the kernel that ends a
+                              product                                          */
     int32_t spmv_kind;     /* SpMV tiling: 0 automatic, 1 vector CSR row-length
                               bins (L lanes per row), 2 stream tiles (runs of
                               at most 64 rows with at most 509 nonzeros,
@@ -126,7 +130,9 @@ typedef struct cg_opts {
                               in natural order with lanes for half the
                               block's mean row length, or length bins when a
                               block has a row over 4096 entries; for
-                              scattered columns),
+                              scattered columns; with spmv_colblock 0 float64
+                              products run on staged column segments instead
+                              where those pay, see below),
                               6 stencil slices (slot j of a 64-row slice holds
                               the entries at the slice's j-th column offset, so
                               columns are row + a slice-uniform offset and a
@@ -149,9 +155,22 @@ typedef struct cg_opts {
                               <= 64 nonzeros and slicing pads by <= 25%,
                               else 2 where every row fits a run and the
                               block has >= 262,144 rows of mean length <= 64
-                              or >= 131,072 of mean length <= 32, else 1.     */
+                              or >= 131,072 of mean length <= 32, else 1.
+                              Staged column segments take the place of an
+                              automatic 1, and of 5 with spmv_colblock 0, in
+                              float64 products where a model of both says they
+                              are faster: from 196,608 rows on, some 6 million
+                              entries at least, none over 4096 in a row.
+                              Segments of the vector pass through LDS, and a
+                              row's entries are summed in several parts, the
+                              same ones in every product.  cg_create and
+                              cg_set_opts build this second layout (12 bytes
+                              per entry; 75 ms for 44 million, which some 240
+                              products earn back).                             */
     int32_t spmv_colblock; /* columns per block of the column-blocked tiling
-                              (spmv_kind 5); 0: 262,144 (2 MB of float64 p)     */
+                              (spmv_kind 5); 0: 262,144 (2 MB of float64 p), or
+                              staged column segments where those pay; 262144
+                              asks for the blocks themselves                    */
     double refine_delta;   /* mixed precision: a float64 refinement is made
                               when the float32 residual drops by this factor    */
     int32_t vectors;       /* CG_VECTORS_DEVICE (default): b, x, y of cg_spmv
@@ -211,7 +230,9 @@ typedef struct cg_result {
     int32_t spmv_kind;       /* SpMV tiling used on the GPU rows: 1 vector bins,
                                 2 stream tiles, 3 sliced tiles, 4 dictionary-
                                 sliced tiles, 5 column blocks, 6 stencil slices,
-                                7 gap-coded slices (0: no GPU rows)              */
+                                7 gap-coded slices (0: no GPU rows); where
+                                staged column segments take the place of 1 or
+                                5, still that number                             */
     int32_t fused_dir;       /* 1 if the direction update ran inside the SpMV
                                 (cg_opts.fuse_dir)                               */
 } cg_result;

@@ -1456,3 +1456,21 @@ def test_one_launch_solves_report_what_is_not_finite(cg, name, bad):
         assert res["code"] == cg.CG_EBREAKDOWN and res["iterations"] == 0 and not res["converged"]
         assert np.array_equal(x, x0)
         assert not np.isfinite(res["rel_res_true"]) and not np.isfinite(res["rel_res_recur"])
+
+
+def test_column_blocks_of_a_given_width(cg):
+    """spmv_kind 5 runs the staged product with the default block width where
+    that pays, and column blocks with the same width given."""
+    A = scattered(200_003, 40, 30)
+    x = np.random.default_rng(17).uniform(-1, 1, A.n)
+    ref = oracle.spmv(A, x)
+    out = {}
+    with cg.Solver(A) as s:
+        for name, opts in (("automatic", {}), ("blocks", {"spmv_kind": 5, "spmv_colblock": 262_144}),
+                           ("default", {"spmv_kind": 5, "spmv_colblock": 0})):
+            s.set_opts(**opts)
+            out[name] = host(s.spmv(dev(x)))
+            assert used_kind(s, A.n) == (1 if name == "automatic" else 5)
+            assert spmv_err(A, x, out[name], ref) <= 1e-12
+    assert np.array_equal(out["default"], out["automatic"])
+    assert not np.array_equal(out["blocks"], out["default"])
