@@ -620,6 +620,7 @@ int one_launch_args(cg_handle *h, const double *b, double *x, double tol, int32_
     int rate_khz = 0;
     if (hipDeviceGetAttribute(&rate_khz, hipDeviceAttributeWallClockRate, h->dev) != hipSuccess || rate_khz <= 0)
         rate_khz = 100000;
+    a.start_ticks = (int64_t)rate_khz * 1000;          // 1 s
     a.timeout_ticks = (int64_t)rate_khz * 1000 * 20;   // 20 s
     HIP_TRY(hipMemsetAsync(a.words, 0, sizeof(uint64_t) * resident_words(groups), h->stream));
     return CG_OK;
@@ -806,10 +807,11 @@ int solve_plain(cg_handle *h, const PlainWork &w, const double *b, double *x, do
             hipSuccess) {
             const int rc = work_state_read(h, w);
             if (rc) return rc;
-            if (w.h_state->done == kDoneRunning) return fail(CG_EDEVICE, "a wait of the one-launch solve timed out");
-            return one_launch_result(*w.h_state, now() - t0, res);
+            if (w.h_state->done != kDoneRunning) return one_launch_result(*w.h_state, now() - t0, res);
+        } else {
+            (void)hipGetLastError();   // not launchable here
         }
-        (void)hipGetLastError();   // not launchable here: the kernels below
+        // not launchable, or abandoned (ResidentArgs): the kernels below
     }
     HIP_TRY(hipMemcpyAsync(w.x, x, sizeof(double) * n, hipMemcpyDeviceToDevice, st));
     int rc = work_state_init(h, w, tol, maxit);

@@ -368,7 +368,13 @@ struct ResidentArgs {
     DevState *st;             // done stays kDoneRunning when the launch was abandoned
     double tol;
     int32_t maxit;
-    int64_t timeout_ticks;    // wall-clock ticks a wait may take
+    // Wall-clock ticks a wait may take: the launch's first one, which ends when
+    // all workgroups have been given a compute unit (with other work on the GPU,
+    // a second process's launch like this one for instance, some may not be as
+    // long as the others hold theirs), and any later one.  A launch that is
+    // abandoned has left x as it was given (or, in its last two sums, at the
+    // end); the solve is then made with separate kernels.
+    int64_t start_ticks, timeout_ticks;
 };
 // 64-bit words of the exchanged sums and the error flag behind them.
 constexpr inline size_t resident_words(int groups) { return 4 * kResidentCopies * (size_t)groups + 1; }

@@ -258,11 +258,11 @@ int solve_gpu_pcg(cg_handle *h, const double *b, double *x, double tol, int32_t 
         if (launch_pcg_window(a, win, st) == hipSuccess) {
             rc = gpu_state_read(h);
             if (rc) return rc;
-            if (h->h_state->done == kDoneRunning)
-                return fail(CG_EDEVICE, "a wait of the one-launch solve timed out");
-            return one_launch_result(*h->h_state, now() - t0, res);
+            if (h->h_state->done != kDoneRunning) return one_launch_result(*h->h_state, now() - t0, res);
+        } else {
+            (void)hipGetLastError();   // not launchable here
         }
-        (void)hipGetLastError();   // not launchable here: the kernels below
+        // not launchable, or abandoned (ResidentArgs): the kernels below
     }
     const int Ga = h->A.grid, Gg = h->G.grid, Gt = h->GT.grid, Gv = h->vec_grid;
     // the fused r/t kernel: one row per thread (CSR), or two 64-row slices per

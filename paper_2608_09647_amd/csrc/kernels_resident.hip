@@ -24,7 +24,8 @@
 // is posted.  (r in such words too, needing no wait and loaded while r^T r is
 // still being summed, gained nothing at 20K rows and lost 1.4 us per iteration
 // at 262K, for twice the bytes.)  Waits are bounded by a wall-clock limit; on
-// expiry the error flag ends every workgroup.
+// expiry the error flag ends every workgroup, and the host makes the solve with
+// the separate kernels.
 #include <hip/hip_runtime.h>
 #include <math.h>
 
@@ -109,10 +110,10 @@ __device__ __forceinline__ double pair_value(uint64_t lo, uint64_t hi) {
 
 // Spin `spin` of a wait that began at t0: false when the launch is being
 // abandoned (looked at every 64 spins).
-__device__ __forceinline__ bool wait_on(const ResidentArgs &a, int spin, uint64_t t0) {
+__device__ __forceinline__ bool wait_on(const ResidentArgs &a, int spin, uint64_t t0, int64_t limit) {
     if ((spin & 63) != 63) return true;
     if (__hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) return false;
-    if ((int64_t)(wall_clock64() - t0) <= a.timeout_ticks) return true;
+    if ((int64_t)(wall_clock64() - t0) <= limit) return true;
     __hip_atomic_store(a.err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     return false;
 }
@@ -163,7 +164,7 @@ __device__ __forceinline__ bool grid_sum(const ResidentArgs &a, double v, uint32
             for (int q = 0; q < Q; ++q)
                 if (q * kWave < T) all &= tagged(l[q], h[q], no);
             if (__all(all)) break;
-            if (!__all(wait_on(a, spin, t0))) {
+            if (!__all(wait_on(a, spin, t0, no == 1 ? a.start_ticks : a.timeout_ticks))) {
                 ok = false;
                 break;
             }

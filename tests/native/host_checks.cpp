@@ -18,6 +18,9 @@
 //     host_checks stage
 //         a trainer's steps after a page-locked allocation failed: none writes
 //         past the buffer that a later one got
+//     host_checks abandoned
+//         a solve in one launch whose workgroups did not all run at once is
+//         made with the separate kernels
 //     host_checks streams
 //         products and a solve through one handle on several streams: where
 //         they share the staged sums, each runs after the one before
@@ -78,6 +81,7 @@ hipError_t hipHostFree(void *p) {
 }
 hipError_t hipGetDeviceCount(int *n) { return *n = 1, hipSuccess; }
 hipError_t hipGetDevice(int *d) { return *d = 0, hipSuccess; }
+hipError_t hipDeviceGetAttribute(int *v, hipDeviceAttribute_t, int) { return *v = 100000, hipSuccess; }
 hipError_t hipSetDevice(int) { return hipSuccess; }
 hipError_t hipGetLastError() { return hipSuccess; }
 const char *hipGetErrorString(hipError_t) { return "error"; }
@@ -129,11 +133,19 @@ hipError_t staged_setup() { return hipSuccess; }
 hipError_t scratch_setup() { return hipSuccess; }
 int device_cu_count() { return 256; }
 int small_path_max_rows() { return 4096; }
-int resident_groups(int32_t, int32_t, int) { return 0; }
+// One launch, which is abandoned: the state keeps saying that it runs.
+static bool g_one_launch = false;
+static int g_launches = 0;
+int resident_groups(int32_t, int32_t, int) { return g_one_launch ? 8 : 0; }
+hipError_t launch_cg_resident(const ResidentArgs &a, int32_t, int, hipStream_t) {
+    ++g_launches;
+    a.st->done = kDoneRunning;
+    return hipSuccess;
+}
 // Ends a solve at once: the state copied back says so (all memory is the host's).
 hipError_t launch_spmv(const CsrDev &A, const Schedule &, int, const double *, double *, const double *, const double *,
                        double *, double *, Partials, Partials, DevState *st, int, int, hipStream_t s) {
-    if (A.st64 && !s->capture) {
+    if (A.st64 && s && !s->capture) {
         if (std::max(s->after, g_ended) < g_products) g_fault = "a product beside one that is not known to have ended";
         s->after = ++g_products;
     }
@@ -373,6 +385,21 @@ void check_stage() {
     REQUIRE(!g_overrun, "a step wrote past its page-locked buffer");
 }
 
+void check_abandoned() {
+    const int32_t n = 8192;
+    std::vector<int32_t> rp((size_t)n + 1), ci((size_t)n);
+    std::vector<double> val((size_t)n, 2.0), b((size_t)n, 1.0), x((size_t)n, 0.0);
+    for (int32_t i = 0; i <= n; ++i) rp[(size_t)i] = i;
+    for (int32_t i = 0; i < n; ++i) ci[(size_t)i] = i;
+    cg_handle *h = nullptr;
+    REQUIRE(cg_create(n, n, rp.data(), ci.data(), val.data(), 0, n, &h) == CG_OK, "create");
+    g_one_launch = true;
+    cg_result res;
+    const int rc = cg_solve(h, b.data(), x.data(), 1e-8, 10, &res);
+    REQUIRE(rc == CG_OK && g_launches == 1, "%d: %s", rc, cg_last_error());
+    cg_destroy(h);
+}
+
 void check_streams() {
     const int32_t n = 299521;
     const Matrix A = random_rows(n, n, 33);
@@ -409,8 +436,9 @@ int main(int argc, char **argv) {
     else if (what == "widths") check_widths();
     else if (what == "mixed") check_mixed();
     else if (what == "stage") check_stage();
+    else if (what == "abandoned") check_abandoned();
     else if (what == "streams") check_streams();
-    else die("usage: host_checks staged ROWS COLS PER_ROW | widths | mixed | stage | streams");
+    else die("usage: host_checks staged ROWS COLS PER_ROW | widths | mixed | stage | abandoned | streams");
     std::printf("ok\n");
     return 0;
 }

@@ -63,3 +63,8 @@ def test_trainer_stage_after_a_failed_allocation(host_checks):
 def test_mixed_precision_keeps_no_staged_segments(host_checks):
     """Their memory is given back, and float64 builds the same layout again."""
     host_checks("mixed")
+
+
+def test_abandoned_launch_is_solved_with_separate_kernels(host_checks):
+    """A one-launch solve whose workgroups did not all run at once."""
+    host_checks("abandoned")
