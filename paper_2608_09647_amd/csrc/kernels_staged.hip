@@ -267,8 +267,8 @@ hipError_t launch_sums(const StagedDev &D, const double *p, const DevState *st, 
                        D.idx, D.val, st)
     // as many steps ahead as a list has at the most on average: a step costs
     // its instructions also where the list has ended (900K rows of 49 entries,
-    // 2.6 steps a list: 211 us with 6, 190 with 3, 198 with 2; 700K of 41 158
-    // and 133 with 6 and 3)
+    // 2.6 steps a list: 211 us with 6, 170 with 3, 182 with 2; 700K of 41: 150,
+    // 122 and 128)
     const int K = std::min(std::max(D.ahead, 2), kStagedAhead);
     if (chunks <= 3) {
         if (K == 2) CGMI_STAGED(3, 2);
