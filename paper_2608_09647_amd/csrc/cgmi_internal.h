@@ -369,9 +369,10 @@ struct ResidentArgs {
     double tol;
     int32_t maxit;
     // Wall-clock ticks a wait may take: the launch's first one, which ends when
-    // all workgroups have been given a compute unit (with other work on the GPU,
-    // a second process's launch like this one for instance, some may not be as
-    // long as the others hold theirs), and any later one.  A launch that is
+    // all workgroups have been given a compute unit (beside other work some may
+    // not be as long as the others hold theirs: an ordinary launch of workgroups
+    // that wait for each other; cooperative ones follow one another, and a second
+    // process's is refused meanwhile), and any later one.  A launch that is
     // abandoned has left x as it was given (or, in its last two sums, at the
     // end); the solve is then made with separate kernels.
     int64_t start_ticks, timeout_ticks;
