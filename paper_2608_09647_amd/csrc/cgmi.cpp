@@ -185,12 +185,9 @@ static bool capturing(hipStream_t s) {
 // Before the handle's stream is given work that may use the staged sums.
 static int staged_wait(cg_handle *h) {
     if (!h->staged_pending || h->staged_stream == h->stream || capturing(h->stream)) return CG_OK;
-    if (h->ev_staged) {
-        HIP_TRY(hipStreamWaitEvent(h->stream, h->ev_staged, 0));
-    } else {
-        HIP_TRY(hipDeviceSynchronize());
-        HIP_TRY(hipEventCreateWithFlags(&h->ev_staged, hipEventDisableTiming));
-    }
+    if (h->ev_staged) HIP_TRY(hipStreamWaitEvent(h->stream, h->ev_staged, 0));
+    else HIP_TRY(hipDeviceSynchronize());
+    h->staged_several = true;
     h->staged_pending = false;
     return CG_OK;
 }
@@ -198,7 +195,10 @@ static int staged_wait(cg_handle *h) {
 // After a product has been queued and left.
 static int staged_queued(cg_handle *h) {
     if (!h->A.use_st64 || capturing(h->stream)) return CG_OK;
-    if (h->ev_staged) HIP_TRY(hipEventRecord(h->ev_staged, h->stream));
+    if (h->staged_several) {   // (cg_solve_noalloc waits too, but makes no event)
+        if (!h->ev_staged) HIP_TRY(hipEventCreateWithFlags(&h->ev_staged, hipEventDisableTiming));
+        HIP_TRY(hipEventRecord(h->ev_staged, h->stream));
+    }
     h->staged_stream = h->stream;
     h->staged_pending = true;
     return CG_OK;

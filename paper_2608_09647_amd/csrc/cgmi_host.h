@@ -209,7 +209,7 @@ struct cg_handle {
     // behind it
     hipEvent_t ev_staged = nullptr;
     hipStream_t staged_stream = nullptr;
-    bool staged_pending = false;
+    bool staged_pending = false, staged_several = false;
     int cus = 256;
 
     // host copy of the matrix (the host complement uses its rows)

@@ -96,11 +96,14 @@ struct ihipStream_t {
 struct ihipEvent_t {
     int after = 0;
 };
-static int g_products = 0, g_ended = 0, g_waits = 0;
+static int g_products = 0, g_ended = 0, g_waits = 0, g_events = 0;
 static std::string g_fault;
 
 extern "C" {
-hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) { return *e = new ihipEvent_t(), hipSuccess; }
+hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) {
+    ++g_events;
+    return *e = new ihipEvent_t(), hipSuccess;
+}
 hipError_t hipEventDestroy(hipEvent_t e) {
     delete e;
     return hipSuccess;
@@ -125,12 +128,23 @@ hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus *status) {
     *status = s->capture ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
     return hipSuccess;
 }
-hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t s) {
+    if (s) g_ended = std::max(g_ended, s->after);
+    return hipSuccess;
+}
 }
 
 namespace cgmi {
 hipError_t staged_setup() { return hipSuccess; }
+static std::vector<unsigned char> g_scratch(kScratchBytes);
 hipError_t scratch_setup() { return hipSuccess; }
+hipError_t scratch_region(int, void **p, size_t *n) { return *p = g_scratch.data(), *n = g_scratch.size(), hipSuccess; }
+hipError_t launch_state_init(DevState *st, double tol, int32_t maxit, double, hipStream_t) {
+    *st = DevState{};
+    st->tol = tol;
+    st->maxit = maxit;
+    return hipSuccess;
+}
 int device_cu_count() { return 256; }
 int small_path_max_rows() { return 4096; }
 // One launch, which is abandoned: the state keeps saying that it runs.
@@ -415,6 +429,12 @@ void check_streams() {
     product();
     product();
     REQUIRE(g_waits == 0, "%d waits on one stream", g_waits);
+    on(s[3]);   // the solve without allocations: the wait alone
+    cg_result res;
+    REQUIRE(cg_solve_noalloc(h, x.data(), y.data(), 0.0, 1, &res) >= 0 && g_waits == 1 && g_events == 0,
+            "%d waits, %d events: %s", g_waits, g_events, cg_last_error());
+    on(s[0]);
+    product();
     for (int k : {1, 0, 2, 2, 1}) {
         on(s[k]);
         product();
@@ -422,7 +442,6 @@ void check_streams() {
     on(graph);   // an eager product is pending: a captured one leaves it so
     product();
     on(s[3]);
-    cg_result res;
     REQUIRE(cg_solve(h, x.data(), y.data(), 0.0, 1, &res) >= 0, "solve");
     REQUIRE(g_fault.empty(), "%s", g_fault.c_str());
     cg_destroy(h);
