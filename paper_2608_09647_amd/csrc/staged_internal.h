@@ -43,8 +43,9 @@ CGMI_HD constexpr inline int32_t staged_last_pair(int32_t left, int32_t seg_cols
     return (left < seg_cols + 2 ? left : seg_cols + 2) / 2 * 2 - 2;
 }
 constexpr int32_t kStagedUnit = 256;                 // a segment's columns are a multiple
-// The columns of a segment: as few as `widest` of them need, in equal parts,
-// and not so that the last segment holds a single one.  0: there is none.
+// The columns of a segment, at most `widest`: equal parts of as few segments as
+// that allows, or fewer columns where the last segment would hold a single one.
+// 0: no width does.
 inline int32_t staged_width(int32_t ncols, int32_t widest) {
     widest = widest / kStagedUnit * kStagedUnit;
     if (widest <= 0) return 0;
